@@ -56,7 +56,7 @@ struct Step {
     int kind = 0;
     int variant = 0;                // front-kernel variant of a group factor step (autotuned)
     std::vector<LocalGroup> groups;
-    std::vector<int4> tasks;        // x (the instance) is filled in by the batch
+    std::vector<int4> tasks;        // large path: (slot, supernode, a, b); the batch makes the records
     size_t lds = 0;                 // shared memory of a large-supernode solve kernel
 };
 
@@ -65,6 +65,8 @@ struct Device {
     hipStream_t stream = nullptr;
     InstPtrs hI{};                 // host copy of the instance descriptor
     std::vector<Step> fac, fwd, bwd;
+    std::vector<int64_t> u_off;    // update blocks' places in the pool
+    std::vector<int32_t> fused;    // supernodes whose Newton-step forward solve runs with their factorization
     std::vector<Step> fwd_rest;   // forward steps of the supernodes whose Newton-step forward solve is not fused
     int fac_launches = 0;          // kernel launches of one factorization
     int64_t stored_l = 0, nnzj = 0, nnzw = 0;
@@ -117,7 +119,7 @@ struct Batch {
     Ctl* ctl = nullptr;
     IpmSpaces spaces{};
     Group* groups = nullptr;
-    int4* tasks = nullptr;
+    BigTask* tasks = nullptr;
     std::vector<BLaunch> fac, fwd, bwd, fwd_rest;
     bool has_distill = false, has_plate = false, has_reflux = false;
     // generated kernels of the stage models among the members (one entry per
@@ -307,7 +309,25 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
     // memory
     const size_t lim = lds_limit_bytes();
     std::vector<Group> gl;
-    std::vector<int4> tl;
+    std::vector<BigTask> tl;
+    auto record = [](const Device& D, int inst, const int4& t) {
+        const Symbolic& sy = D.owner->sym;
+        const int sn = t.y;
+        BigTask r{};
+        r.L = D.hI.L + sy.l_off[sn];
+        r.U = D.hI.U + D.u_off[sn];
+        r.uv = sy.uv_off[sn];
+        r.inst = inst;
+        r.sn = sn;
+        r.a = t.z;
+        r.b = t.w;
+        r.f = sy.sn_ptr[sn];
+        r.w = sy.sn_ptr[sn + 1] - r.f;
+        r.m = (int32_t)(sy.sn_rows_ptr[sn + 1] - sy.sn_rows_ptr[sn]);
+        r.fused = D.fused[sn];
+        r.slot = t.x;
+        return r;
+    };
     auto merge = [&](std::vector<BLaunch>& dst, std::vector<Step> Device::*list) {
         size_t len = 0;
         for (auto* D : members) len = std::max(len, (D->*list).size());
@@ -315,7 +335,7 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
             std::vector<Group> g_lds, g_glob, g_sol;
             size_t b_lds = 0, b_sol = 0;
             int gkind = 0, variant = 0, vfront = -1;
-            std::vector<std::vector<int4>> by_kind(32);
+            std::vector<std::vector<BigTask>> by_kind(32);
             std::vector<size_t> kind_lds(32, 0);
             for (int i = 0; i < ni; ++i) {
                 const auto& L = members[i]->*list;
@@ -346,10 +366,7 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
                         }
                     }
                 } else {
-                    for (int4 t : st.tasks) {
-                        t.x = i;
-                        by_kind[st.kind].push_back(t);
-                    }
+                    for (const int4& t : st.tasks) by_kind[st.kind].push_back(record(*members[i], i, t));
                     kind_lds[st.kind] = std::max(kind_lds[st.kind], st.lds);
                 }
             }
@@ -820,32 +837,37 @@ nmpc_status device_init(Problem& p, std::string& err) {
         for (int32_t sn : bigs) wmax = std::max(wmax, width_of(sn));
         for (int64_t kb = 0; kb < wmax; kb += kBigOuter) {
             for (int64_t ki = kb; ki < std::min<int64_t>(wmax, kb + kBigOuter); ki += kBigPanel) {
-                std::vector<int4> po, tr, up;
-                for (int32_t sn : bigs) {
+                std::vector<int4> pn, up;
+                for (size_t q = 0; q < bigs.size(); ++q) {
+                    const int32_t sn = bigs[q];
+                    const int slot = (int)q;
                     const int64_t w = width_of(sn), m = rows_of(sn);
                     if (ki >= w) continue;
                     const int64_t pw = std::min<int64_t>(kBigPanel, w - ki);
-                    po.push_back(int4{0, sn, (int)ki, 0});
-                    const int64_t below = m - ki - pw;
-                    for (int rb = 0; rb < ceil_div(below, RB); ++rb) tr.push_back(int4{0, sn, (int)ki, rb});
+                    const int nrb = std::max(1, ceil_div(m - ki - pw, RB));
+                    for (int rb = 0; rb < nrb; ++rb) pn.push_back(int4{slot, sn, (int)ki, rb});
                     const int64_t cend = std::min<int64_t>(w, kb + kBigOuter), t0 = ki + pw;
                     if (cend > t0) {   // the rest of the outer panel
                         const int trn = ceil_div(m - t0, TL), tcn = ceil_div(cend - t0, TL);
                         for (int ti = 0; ti < trn; ++ti)
-                            for (int tj = 0; tj < tcn && tj <= ti; ++tj) up.push_back(int4{0, sn, (int)ki, ti * tcn + tj});
+                            for (int tj = 0; tj < tcn && tj <= ti; ++tj) up.push_back(int4{slot, sn, (int)ki, ti * tcn + tj});
+                        // a block factored by several workgroups waits in dfac until none of them reads the original
+                        if (nrb > 1) up.push_back(int4{slot, sn, (int)ki, -1});
                     }
                 }
-                push(D.fac, kBigPotrf, std::move(po));
-                push(D.fac, kBigTrsm, std::move(tr));
+                push(D.fac, kBigPanelStep, std::move(pn));
                 push(D.fac, kBigUpdateInner, std::move(up));
             }
             std::vector<int4> up;
-            for (int32_t sn : bigs) {
+            for (size_t q = 0; q < bigs.size(); ++q) {
+                const int32_t sn = bigs[q];
                 const int64_t w = width_of(sn), m = rows_of(sn);
                 if (kb >= w) continue;
+                const int64_t kl = kb + (std::min<int64_t>(kBigOuter, w - kb) - 1) / kBigPanel * kBigPanel;   // its last panel
+                if (m - std::min<int64_t>(w, kl + kBigPanel) > RB) up.push_back(int4{(int)q, sn, (int)kl, -1});
                 const int64_t kw = std::min<int64_t>(kBigOuter, w - kb);
                 const int T = ceil_div(m - kb - kw, TL);
-                for (int tt = 0; tt < T * (T + 1) / 2; ++tt) up.push_back(int4{0, sn, (int)kb, tt});
+                for (int tt = 0; tt < T * (T + 1) / 2; ++tt) up.push_back(int4{(int)q, sn, (int)kb, tt});
             }
             push(D.fac, kBigUpdate, std::move(up));
         }
@@ -1048,6 +1070,15 @@ nmpc_status device_init(Problem& p, std::string& err) {
             k_fpos[t] = r == c ? ~(int32_t)q : (int32_t)q;
         }
     }
+    // factored diagonal blocks of the large fronts of one level
+    size_t max_bigs = 0;
+    for (int Lv = 0; Lv < sy.depth; ++Lv) {
+        size_t cnt = 0;
+        for (int i = sy.level_ptr[Lv]; i < sy.level_ptr[Lv + 1]; ++i) cnt += big_fac[sy.level_list[i]] ? 1 : 0;
+        max_bigs = std::max(max_bigs, cnt);
+    }
+    D.u_off = u_off;
+    D.fused = fused;
     // global front buffers for the medium groups of one step
     int max_global = 0;
     for (const auto& stp : D.fac) {
@@ -1163,6 +1194,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
     for (int k = 0; k < kNumSpaces; ++k) pblocks = std::max(pblocks, nblocks(space_size(I, k)));
     DTRY(dalloc(A, I.part, (size_t)kMaxQ * std::max(1, pblocks)));
     DTRY(dalloc(A, I.filter, (size_t)2 * kFilterCapMax));
+    DTRY(dalloc(A, I.dfac, (size_t)kBigDiag * max_bigs));
     if (gstride > 0) DTRY(dalloc(A, I.gscratch, (size_t)gstride * max_global));
 #undef DTRY
     std::vector<Device*> one{&D};
@@ -1832,6 +1864,8 @@ nmpc_status seeds_build(Problem& p, std::string& err) {
         c->fwd = D.fwd;
         c->bwd = D.bwd;
         c->fwd_rest = D.fwd_rest;
+        c->u_off = D.u_off;
+        c->fused = D.fused;
         D.seed_devs.push_back(c);
     }
     const nmpc_status rc = batch_build(D.seed_devs, D.stream, D.seeds, err);

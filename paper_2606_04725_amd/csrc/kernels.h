@@ -172,6 +172,7 @@ struct InstPtrs {
     double* gscratch;
     int64_t gstride;
     const int32_t* kcol_ptr;   // KKT slots of each permuted column: [kcol_ptr[j], kcol_ptr[j + 1])
+    double* dfac;     // factored diagonal blocks on their way into the panels: kBigDiag doubles per large front of a level
     double* bsum;     // large-supernode backward solves: rows-below products per column
     double* part;     // reduction partials: kMaxQ rows of this instance's blocks
     double* filter;   // (theta, phi) pairs, kFilterCapMax of them
@@ -328,22 +329,32 @@ hipError_t linalg_configure(size_t max_lds_bytes);
 // ---- large supernodes (kernels_big.hip) ---------------------------------------------
 constexpr int kBigPanel = 64;   // pivot columns per panel step of a large front
 constexpr int kBigOuter = 512;  // columns per outer panel (one trailing update each)
+constexpr int kBigDiag = kBigPanel * kBigPanel + kBigPanel;   // doubles of a factored diagonal block kept aside
+// One workgroup's share of a step: the front's storage and sizes, then what the
+// kind below names (a, b).  slot: the front's place in the instance's dfac.
+struct BigTask {
+    double *L, *U;        // panel (m x w), update block ((m - w) x (m - w))
+    int64_t uv;           // update vector of the front, an offset into uvec
+    int32_t inst, sn, a, b;
+    int32_t f, w, m, fused;
+    int32_t slot, pad;
+};
+static_assert(sizeof(BigTask) == 64, "one scalar load of 16 words");
 enum BigKind : int {
-    kBigInit = 1,       // task (inst, s, column, -)
-    kBigExtend = 2,     // task (inst, s, child position, child column)
-    kBigPotrf = 3,      // task (inst, s, kb, -)
-    kBigTrsm = 4,       // task (inst, s, kb, row block)
-    kBigUpdate = 5,     // task (inst, s, kb, lower-triangle tile)
-    kBigFwdTri = 6,     // task (inst, s, chunk, -)
-    kBigFwdGemv = 7,    // task (inst, s, chunk, row block)
-    kBigBwdBelow = 8,   // task (inst, s, column block, -)
-    kBigBwdTri = 9,     // task (inst, s, chunk, -)
-    kBigUpdateInner = 10,  // task (inst, s, ki, rectangular tile)
-    kBigBwdGemvT = 11   // task (inst, s, chunk, column block)
+    kBigInit = 1,       // a: column
+    kBigExtend = 2,     // a: child position, b: child column
+    kBigPanelStep = 3,  // a: kb, b: row block
+    kBigUpdate = 5,     // a: kb, b: lower-triangle tile; b < 0: keep the diagonal block of columns a
+    kBigFwdTri = 6,     // a: chunk
+    kBigFwdGemv = 7,    // a: chunk, b: row block
+    kBigBwdBelow = 8,   // a: column block
+    kBigBwdTri = 9,     // a: chunk
+    kBigUpdateInner = 10,  // a: ki, b: rectangular tile; b < 0: keep the diagonal block of columns a
+    kBigBwdGemvT = 11   // a: chunk, b: column block
 };
 // One step for every task of a list (predicate and eta as for the groups;
 // which selects the solve vectors).
-void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs* I, const int4* tasks, int count,
+void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs* I, const BigTask* tasks, int count,
                 size_t lds_bytes, hipStream_t st);
 int big_row_block();
 int big_tile();

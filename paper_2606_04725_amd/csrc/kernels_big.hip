@@ -24,6 +24,7 @@
 // is split over column blocks, then one workgroup solves with the transposed
 // diagonal block.
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.h"
 #include "front_chol.h"
@@ -48,15 +49,10 @@ struct Front {
     int f, w, m;
 };
 
-__device__ inline Front front_of(const InstPtrs& I, int s) {
-    Front F;
-    F.f = I.S.sn_ptr[s];
-    F.w = I.S.sn_ptr[s + 1] - F.f;
-    F.m = (int)(I.S.rows_ptr[s + 1] - I.S.rows_ptr[s]);
-    F.L = I.L + I.S.l_off[s];
-    F.U = I.U + I.S.u_off[s];
-    return F;
-}
+// The front of a task: its storage and sizes come with the task record, so the
+// first data loads wait for one dependent load, not for a chain through the
+// instance and its supernode tables.
+__device__ inline Front front_of(const BigTask& t) { return Front{t.L, t.U, t.f, t.w, t.m}; }
 
 // address of front entry (i, j), i >= j
 __device__ inline double* at(const Front& F, int i, int j) {
@@ -70,23 +66,23 @@ __device__ inline double* at(const Front& F, int i, int j) {
 // and the rows below take the panel's product as their rows are solved.
 // Entry i lives in xp (i < w) or in the supernode's update vector (i >= w),
 // where the unfused solve leaves them too.
-__device__ inline bool fwd_fused(const InstPtrs& I, int s, int pred) { return pred == kPredFactor && I.S.fused[s]; }
-__device__ inline double* fwd_entry(const InstPtrs& I, const Front& F, int s, int i) {
-    return i < F.w ? I.xp + F.f + i : I.uvec + I.S.uv_off[s] + (i - F.w);
+__device__ inline bool fwd_fused(const BigTask& t, int pred) { return pred == kPredFactor && t.fused; }
+__device__ inline double* fwd_entry(const InstPtrs& I, const Front& F, const BigTask& t, int i) {
+    return i < F.w ? I.xp + F.f + i : I.uvec + t.uv + (i - F.w);
 }
 
 // ---- factorization ---------------------------------------------------------------
 // task (inst, s, j, -): zero column j of the front, then scatter the KKT slots
 // of column j (j < w), eta added on the diagonal.
 __global__ void __launch_bounds__(kBlock)
-k_big_init(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred, double eta_force) {
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
+k_big_init(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, double eta_force) {
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
     const double eta = pred == kPredAll ? eta_force : I.ctl->eta;
-    const Front F = front_of(I, tk.y);
-    const int j = tk.z;
-    if (threadIdx.x == 0 && fwd_fused(I, tk.y, pred)) *fwd_entry(I, F, tk.y, j) = j < F.w ? I.rhs[I.perm[F.f + j]] : 0.0;
+    const Front F = front_of(tk);
+    const int j = tk.a;
+    if (threadIdx.x == 0 && fwd_fused(tk, pred)) *fwd_entry(I, F, tk, j) = j < F.w ? I.rhs[I.perm[F.f + j]] : 0.0;
     for (int i = j + threadIdx.x; i < F.m; i += blockDim.x) *at(F, i, j) = 0.0;
     if (j >= F.w) return;
     __syncthreads();
@@ -103,19 +99,19 @@ k_big_init(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int 
 // task (inst, s, child position, child column jc): add column jc of the child's
 // update block into the front through the child's relative row positions.
 __global__ void __launch_bounds__(kBlock)
-k_big_extend(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred) {
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
+k_big_extend(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
-    const int c = I.S.child_list[I.S.child_ptr[tk.y] + tk.z];
+    const Front F = front_of(tk);
+    const int c = I.S.child_list[I.S.child_ptr[tk.sn] + tk.a];
     const int wc = I.S.sn_ptr[c + 1] - I.S.sn_ptr[c];
     const int nc = (int)(I.S.rows_ptr[c + 1] - I.S.rows_ptr[c]) - wc;
     const double* Uc = I.U + I.S.u_off[c];
     const int32_t* rel = I.S.rel + I.S.rel_off[c];
-    const int jc = tk.w;
+    const int jc = tk.b;
     const int rj = rel[jc];
-    if (threadIdx.x == 0 && fwd_fused(I, tk.y, pred)) *fwd_entry(I, F, tk.y, rj) += I.uvec[I.S.uv_off[c] + jc];
+    if (threadIdx.x == 0 && fwd_fused(tk, pred)) *fwd_entry(I, F, tk, rj) += I.uvec[I.S.uv_off[c] + jc];
     const auto* uc = global(Uc) + (int64_t)jc * nc;
     const auto* rg = global(rel);
     // kExtendDepth rows per thread at a time: their loads are issued together
@@ -138,165 +134,239 @@ k_big_extend(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, in
     }
 }
 
-// task (inst, s, kb, -): factor the diagonal block D of columns [kb, kb + pw)
-// in shared memory (panel-blocked, see partial_cholesky) and store it.  A pivot
-// that is not positive and finite sets the instance's failure flag (eq. 12) and
-// the arithmetic continues with pivot 1.
-__global__ void __launch_bounds__(kBlock)
-k_big_potrf(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred) {
-    static_assert(kBigPanel == kWave, "diagonal blocks are staged as 64 x 64 triangles");
-    __shared__ double D[kTri];
-    __shared__ double fv[kBigPanel];   // the fused forward solve's entries of the panel
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
-    if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
-    const int kb = tk.z;
-    const int pw = min(kBigPanel, F.w - kb);
-    constexpr int ldd = kBigPanel + 1;
-    {
-        double t[kStage];
-#pragma unroll
-        for (int s = 0; s < kStage; ++s) {
-            const int e = threadIdx.x + s * kBlock, i = e % kBigPanel, j = e / kBigPanel;
-            t[s] = (i < pw && j <= i) ? global(F.L)[(kb + i) + (int64_t)(kb + j) * F.m] : 0.0;
-        }
-#pragma unroll
-        for (int s = 0; s < kStage; ++s) {
-            const int e = threadIdx.x + s * kBlock;
-            D[e % kBigPanel + (e / kBigPanel) * ldd] = t[s];
-        }
-    }
-    const bool fw = fwd_fused(I, tk.y, pred);
-    if (fw && (int)threadIdx.x < pw) fv[threadIdx.x] = *fwd_entry(I, F, tk.y, kb + threadIdx.x);
-    __syncthreads();
-    partial_cholesky<8>(D, SquareIdx{ldd}, pw, pw, &I.ctl->fail, fw ? fv : nullptr);
-    for (int e = threadIdx.x; e < kBigPanel * kBigPanel; e += blockDim.x) {
-        const int i = e % kBigPanel, j = e / kBigPanel;
-        if (i < pw && j <= i) global(F.L)[(kb + i) + (int64_t)(kb + j) * F.m] = D[i + j * ldd];
-    }
-    if (fw && (int)threadIdx.x < pw) I.xp[F.f + kb + threadIdx.x] = fv[threadIdx.x];
+// One panel of a front: task a = kb, b = row block.  Every workgroup factors the
+// 64 x 64 diagonal block D of columns [kb, kb + pw) itself, so that the rows
+// below are solved in the same launch, as soon as a 16-column block of D is
+// factored.  Wave 0 holds D's rows one per lane and takes 16 pivot columns at a
+// time in registers: t, the 16 pivot rows copied to each 16-lane group, gives
+// every lane L(j, k) by a row broadcast of the vector unit (no shared memory,
+// no barrier inside the 16 columns); between blocks the next 16 columns take
+// their update on the matrix cores.  Waves 1-4 solve 16 rows each, x D^T = a,
+// block after block: the solved blocks' products on the matrix cores, then the
+// 16 columns by broadcasts within the 16 lanes of a row group.  Wave 5 does the
+// same for the fused forward solve, whose right-hand side is one more row.
+// Columns past pw are padded with the identity.  The factored block of a front
+// with several workgroups goes to dfac, from where the next update launch puts
+// it into the panel: another workgroup may still have to read the original.
+// A pivot that is not positive and finite sets the instance's failure flag
+// (eq. 12) and the arithmetic continues with pivot 1.
+constexpr int kPanelRowWaves = 4;
+constexpr int kPanelThreads = (kPanelRowWaves + 2) * kWave;
+constexpr int kLdx = 17;   // leading dimension of a wave's 16 rows in shared memory
+constexpr int kLdd = kBigPanel + 1;
+
+// Value of v in lane K of the caller's 16-lane group.
+template <int K>
+__device__ __attribute__((always_inline)) inline double group_lane(double v) {
+    return __builtin_amdgcn_mov_dpp(v, 0x150 + K, 0xf, 0xf, true);   // row_newbcast:K
 }
 
-// task (inst, s, kb, row block): solve x D^T = a for the rows
-// [kb + pw + rb kRowBlock, ...) below the factored diagonal block D.  A full
-// panel goes by blocks of 16 columns (blocked substitution): wave v holds its
-// 16 rows in shared memory (leading dimension kLdx); for column block j the
-// wave takes the block's 16 x 16 tile in the matrix-core layout (lane (li, lk)
-// holds rows lk, lk + 4, lk + 8, lk + 12 of column li), subtracts the solved
-// blocks' products with D's strict lower blocks on v_mfma_f64_16x16x4f64, then
-// solves with D's 16 x 16 diagonal block column by column: the lanes of
-// column k scale it by 1 / d_kk and the value reaches the later columns'
-// lanes of its row by a shuffle.  A narrower last panel is solved in place,
-// one lane per row.
-constexpr int kLdx = 17;   // leading dimension of a wave's 16 rows in shared memory
-__global__ void __launch_bounds__(kBlock)
-k_big_trsm(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred) {
-    __shared__ double D[kTri];   // strict lower triangle
-    __shared__ double rd[kBigPanel];
-    __shared__ double Xs[kBlock / kWave][kLdx * kBigPanel];
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
-    if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
-    const int kb = tk.z;
-    const int pw = min(kBigPanel, F.w - kb);
-    constexpr int ldd = kBigPanel + 1;
-    const int tid = threadIdx.x;
-    const int r0 = kb + pw + tk.w * kRowBlock;
-    if (r0 >= F.m) return;
-    {
-        double t[kStage];
+template <int N, class F>
+__device__ __attribute__((always_inline)) inline void static_for(F&& f) {
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
+}
+
+// 16 pivot columns of D (shared memory, kLdd) from column c0, by one wave; the
+// reciprocals of the diagonal to rd.
+__device__ __attribute__((always_inline)) inline bool factor_16(double* D, double* rd, int c0) {
+    const int lane = threadIdx.x & (kWave - 1), li = lane & 15;
+    double a[16], t[16];
 #pragma unroll
-        for (int s = 0; s < kStage; ++s) {
-            const int e = tid + s * kBlock, i = e % kBigPanel, j = e / kBigPanel;
-            t[s] = (i < pw && j <= i) ? global(F.L)[(kb + i) + (int64_t)(kb + j) * F.m] : 0.0;
+    for (int c = 0; c < 16; ++c) {
+        a[c] = D[lane + (c0 + c) * kLdd];   // rows above c0 hold zeros there
+        t[c] = D[(c0 + li) + (c0 + c) * kLdd];
+    }
+    bool bad = false;
+    double rv = 1.0;
+    auto recip = [&](double piv) {
+        if (!(piv > 0.0) || !(piv < INFINITY)) {
+            bad = true;
+            piv = 1.0;
         }
+        return rsqrt(piv);
+    };
+    double inv = recip(group_lane<0>(t[0]));
+    static_for<16>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        rv = li == k ? inv : rv;
+        t[k] *= inv;
+        a[k] *= inv;
+        // the next pivot first, so that its reciprocal root is formed while the
+        // other columns take their updates
+        static_for<15 - k>([&](auto jc) {
+            constexpr int j = k + 1 + decltype(jc)::value;
+            const double b = group_lane<j>(t[k]);
+            t[j] = fma(-t[k], b, t[j]);
+            if constexpr (j == k + 1) inv = recip(group_lane<j>(t[j]));
+            a[j] = fma(-a[k], b, a[j]);
+        });
+        __builtin_amdgcn_sched_barrier(0);   // one pivot at a time: the broadcasts would fill the registers
+    });
 #pragma unroll
-        for (int s = 0; s < kStage; ++s) {
-            const int e = tid + s * kBlock, i = e % kBigPanel, j = e / kBigPanel;
-            D[i + j * ldd] = i == j ? 0.0 : t[s];
-            if (i == j) rd[i] = i < pw ? 1.0 / t[s] : 1.0;
+    for (int c = 0; c < 16; ++c) D[lane + (c0 + c) * kLdd] = a[c];   // above the diagonal: never read again
+    if (lane < 16) rd[c0 + lane] = rv;
+    return bad;
+}
+
+// Solve the 16 columns c0 of a 16-row tile in the matrix-core layout (lane (li,
+// lk) holds rows lk, lk + 4, lk + 8, lk + 12 of column li) against D's diagonal
+// block there.
+__device__ __attribute__((always_inline)) inline void solve_16(f64x4& acc, const double* D, const double* rd, int c0) {
+    const int li = threadIdx.x & 15;
+    double T[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const double v = D[(c0 + li) + (c0 + k) * kLdd];
+        T[k] = li > k ? v : 0.0;
+    }
+    const double r = rd[c0 + li];
+    static_for<15>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = fma(-group_lane<k>(acc[q] * r), T[k], acc[q]);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] *= r;
+}
+
+__global__ void __launch_bounds__(kPanelThreads)
+k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
+    static_assert(kBigPanel == kWave && kRowBlock == 16 * kPanelRowWaves, "a lane per row of D, 16 rows per wave");
+    __shared__ double D[kTri];
+    __shared__ double rd[kBigPanel];
+    __shared__ double Xs[kPanelRowWaves + 1][kLdx * kBigPanel];
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
+    if (!ctl_active(I.ctl, pred)) return;
+    const Front F = front_of(tk);
+    const int kb = tk.a, pw = min(kBigPanel, F.w - kb), np = (pw + 15) / 16;
+    const bool fw = fwd_fused(tk, pred);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, li = lane & 15, lk = lane >> 4;
+    const bool rhs_wave = wv == kPanelRowWaves + 1;
+    const int rw = kb + pw + tk.b * kRowBlock + 16 * (wv - 1);   // first row of a row wave
+    const bool row_wave = wv >= 1 && !rhs_wave && rw < F.m;
+    const bool works = row_wave || (rhs_wave && fw);
+    double* X = Xs[wv >= 1 ? wv - 1 : 0];
+    const gdouble* Lg = global(F.L);
+    {
+        // every load of the thread (D and its wave's rows) before the first
+        // store, from clamped addresses (no branch around a load)
+        constexpr int kDiagStage = (kBigPanel * kBigPanel + kPanelThreads - 1) / kPanelThreads;
+        double t[kDiagStage], x[16];
+#pragma unroll
+        for (int s = 0; s < kDiagStage; ++s) {
+            const int e = tid + s * kPanelThreads, i = min(e % kBigPanel, pw - 1), j = min(e / kBigPanel, i);
+            t[s] = Lg[(kb + i) + (int64_t)(kb + j) * F.m];
+        }
+        const gdouble* src = rhs_wave ? global(I.xp) + F.f + kb : Lg + (int64_t)kb * F.m + min(rw + li, F.m - 1);
+        const int64_t stride = rhs_wave ? 1 : F.m;
+        const bool in = rhs_wave ? fw && li == 0 : rw + li < F.m;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = src[min(4 * u + lk, pw - 1) * stride];
+#pragma unroll
+        for (int s = 0; s < kDiagStage; ++s) {
+            const int e = tid + s * kPanelThreads, i = e % kBigPanel, j = e / kBigPanel;
+            const double v = (i < pw && j <= i) ? t[s] : (i == j ? 1.0 : 0.0);
+            if (e < kBigPanel * kBigPanel) D[i + j * kLdd] = v;
+        }
+        if (works) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) X[li + (4 * u + lk) * kLdx] = in && 4 * u + lk < pw ? x[u] : 0.0;
         }
     }
     __syncthreads();
-    const bool fw = fwd_fused(I, tk.y, pred);
-    if (pw == kBigPanel) {
-        static_assert(kRowBlock == 16 * (kBlock / kWave), "a wave takes 16 rows of the block");
-        const int lane = tid & (kWave - 1), wv = tid / kWave, li = lane & 15, lk = lane >> 4;
-        const int rw = r0 + 16 * wv;
-        if (rw >= F.m) return;   // the whole wave (no barrier follows)
-        double* X = Xs[wv];
-        {
-            double t[16];
+    bool bad = false;
+    for (int p = 0; p < np; ++p) {
+        const int c0 = 16 * p;
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        if (wv == 0) {
+            bad |= factor_16(D, rd, c0);
+        } else if (works) {   // the solved blocks' part, while wave 0 factors
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int col = 4 * u + lk, r = rw + li;
-                t[u] = r < F.m ? global(F.L)[r + (int64_t)(kb + col) * F.m] : 0.0;
+            for (int r = 0; r < 4; ++r) acc[r] = X[(4 * r + lk) + (c0 + li) * kLdx];
+            for (int i = 0; i < c0; i += 4) {
+                const double av = -X[li + (i + lk) * kLdx];
+                const double bv = D[(c0 + li) + (i + lk) * kLdd];
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
             }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) X[li + (4 * u + lk) * kLdx] = t[u];
         }
-        __builtin_amdgcn_wave_barrier();   // the wave's own shared-memory rows: program order suffices
+        __syncthreads();
+        if (wv == 0) {
+            if (p + 1 < np) {   // the next 16 columns take the factored ones' update
+                const int n0 = c0 + 16;
+                for (int ti = p + 1; ti < np; ++ti) {
+                    f64x4 u = {0.0, 0.0, 0.0, 0.0};
+                    for (int i = 0; i < n0; i += 4) {
+                        const double av = D[(16 * ti + li) + (i + lk) * kLdd];
+                        const double bv = D[(n0 + li) + (i + lk) * kLdd];
+                        u = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, u, 0, 0, 0);
+                    }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            f64x4 acc;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] = X[(4 * r + lk) + (16 * j + li) * kLdx];
-#pragma unroll
-            for (int i = 0; i < j; ++i)
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const double av = -X[li + (16 * i + 4 * s + lk) * kLdx];
-                    const double bv = D[(16 * j + li) + (16 * i + 4 * s + lk) * ldd];
-                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+                    for (int r = 0; r < 4; ++r) {
+                        const int i = 16 * ti + 4 * r + lk, j = n0 + li;
+                        if (j <= i) D[i + j * kLdd] -= u[r];
+                    }
                 }
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const double rdk = rd[16 * j + k];
-                const double dkl = D[(16 * j + li) + (16 * j + k) * ldd];   // zero unless li > k
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const double own = li == k ? acc[r] * rdk : acc[r];
-                    const double xk = __shfl(own, (lane & ~15) | k, kWave);
-                    acc[r] = li > k ? fma(-xk, dkl, own) : own;
-                }
+                __builtin_amdgcn_wave_barrier();   // the same wave reads them next: program order suffices
             }
+        } else if (works) {
+            solve_16(acc, D, rd, c0);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) X[(4 * r + lk) + (16 * j + li) * kLdx] = acc[r];
+            for (int r = 0; r < 4; ++r) X[(4 * r + lk) + (c0 + li) * kLdx] = acc[r];
             __builtin_amdgcn_wave_barrier();
         }
+    }
+    if (bad && tid == 0) I.ctl->fail = 1;
+    if (fw) __syncthreads();   // the forward solve's row is read by the row waves
+    if (row_wave) {
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int col = 4 * u + lk, r = rw + li;
-            if (r < F.m) global(F.L)[r + (int64_t)(kb + col) * F.m] = X[li + col * kLdx];
+            if (r < F.m && col < pw) global(F.L)[r + (int64_t)(kb + col) * F.m] = X[li + col * kLdx];
         }
         if (fw) {   // each row takes the panel's product with its solution: lane (li, lk) sums 16 columns
-            const double* xs = I.xp + F.f + kb + 16 * lk;
+            const double* y = Xs[kPanelRowWaves];
             double dot = 0.0;
 #pragma unroll
-            for (int c = 0; c < 16; ++c) dot = fma(X[li + (16 * lk + c) * kLdx], xs[c], dot);
+            for (int c = 0; c < 16; ++c)   // columns past 16 np are not solved: zero from the load
+                dot = fma(X[li + (16 * lk + c) * kLdx], y[(16 * lk + c) * kLdx], dot);
             dot += __shfl_xor(dot, 16, kWave);
             dot += __shfl_xor(dot, 32, kWave);
-            if (lk == 0 && rw + li < F.m) *fwd_entry(I, F, tk.y, rw + li) -= dot;
+            if (lk == 0 && rw + li < F.m) *fwd_entry(I, F, tk, rw + li) -= dot;
         }
-    } else if (tid < kRowBlock) {
-        // the last, narrower panel of a supernode: in place, one lane per row;
-        // D's diagonal was zeroed, its reciprocal is in rd
-        const int r = r0 + tid;
-        if (r >= F.m) return;
-        gdouble* row = global(F.L) + r + (int64_t)kb * F.m;
-        const double* xs = I.xp + F.f + kb;
-        double dot = 0.0;
-        for (int k = 0; k < pw; ++k) {
-            double acc = row[(int64_t)k * F.m];
-            for (int j = 0; j < k; ++j) acc = fma(-row[(int64_t)j * F.m], D[k + j * ldd], acc);
-            const double lk = acc * rd[k];
-            row[(int64_t)k * F.m] = lk;
-            if (fw) dot = fma(lk, xs[k], dot);
-        }
-        if (fw) *fwd_entry(I, F, tk.y, r) -= dot;
     }
+    if (tk.b == 0 && (wv == 0 || rhs_wave)) {
+        const bool aside = F.m - kb - pw > kRowBlock;   // other workgroups share the block
+        gdouble* scr = global(I.dfac) + (int64_t)tk.slot * kBigDiag;
+        if (wv == 0) {
+            for (int j = 0; j < pw; ++j)
+                if (lane >= j && lane < pw) {
+                    if (aside) scr[lane + j * kBigPanel] = D[lane + j * kLdd];
+                    else global(F.L)[(kb + lane) + (int64_t)(kb + j) * F.m] = D[lane + j * kLdd];
+                }
+        } else if (fw && lane < pw) {
+            const double v = X[lane * kLdx];
+            if (aside) scr[kBigPanel * kBigPanel + lane] = v;
+            else I.xp[F.f + kb + lane] = v;
+        }
+    }
+}
+
+// The factored diagonal block of columns kb (and the forward solve's entries)
+// from dfac into the front's storage.
+__device__ inline void keep_diagonal(const InstPtrs& I, const BigTask& tk, int pred) {
+    const int kb = tk.a, pw = min(kBigPanel, tk.w - kb);
+    const gdouble* scr = global(I.dfac) + (int64_t)tk.slot * kBigDiag;
+    for (int e = threadIdx.x; e < kBigPanel * kBigPanel; e += blockDim.x) {
+        const int i = e % kBigPanel, j = e / kBigPanel;
+        if (i < pw && j <= i) global(tk.L)[(kb + i) + (int64_t)(kb + j) * tk.m] = scr[e];
+    }
+    if (fwd_fused(tk, pred) && (int)threadIdx.x < pw)
+        I.xp[tk.f + kb + threadIdx.x] = scr[kBigPanel * kBigPanel + threadIdx.x];
 }
 
 // Tiles of one launch are handed out XCD by XCD: workgroups are dealt to the 8
@@ -315,25 +385,29 @@ __device__ inline int xcd_tile(int b, int n) {
 // min(kBigPanel, w - ki).  Wave v computes the 32 x 32 quarter (v / 2, v % 2).
 template <bool Inner>
 __global__ void __launch_bounds__(kBlock)
-k_big_update(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred) {
-    const int4 tk = tasks[xcd_tile(blockIdx.x, gridDim.x)];
-    const InstPtrs& I = Ia[tk.x];
+k_big_update(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
+    const BigTask tk = tasks[xcd_tile(blockIdx.x, gridDim.x)];
+    const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
-    const int k0 = tk.z;
+    if (tk.b < 0) {
+        keep_diagonal(I, tk, pred);
+        return;
+    }
+    const Front F = front_of(tk);
+    const int k0 = tk.a;
     const int kw = min(Inner ? kBigPanel : kBigOuter, F.w - k0);
     const int t0 = k0 + kw;
     int ti, tj;
     if (Inner) {
         const int cend = min(F.w, k0 - k0 % kBigOuter + kBigOuter);
         const int tc = (cend - t0 + kTile - 1) / kTile;
-        ti = tk.w / tc;
-        tj = tk.w - ti * tc;
+        ti = tk.b / tc;
+        tj = tk.b - ti * tc;
     } else {
-        ti = (int)((sqrt(8.0 * tk.w + 1.0) - 1.0) * 0.5);
-        while ((ti + 1) * (ti + 2) / 2 <= tk.w) ++ti;
-        while (ti * (ti + 1) / 2 > tk.w) --ti;
-        tj = tk.w - ti * (ti + 1) / 2;
+        ti = (int)((sqrt(8.0 * tk.b + 1.0) - 1.0) * 0.5);
+        while ((ti + 1) * (ti + 2) / 2 <= tk.b) ++ti;
+        while (ti * (ti + 1) / 2 > tk.b) --ti;
+        tj = tk.b - ti * (ti + 1) / 2;
     }
     const int cmax = Inner ? min(F.w, k0 - k0 % kBigOuter + kBigOuter) : F.m;
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
@@ -427,19 +501,19 @@ __device__ inline double lane_value(double v, int k) {
 // in xp, by blocks of 64 columns (the block's triangle staged in shared memory,
 // wave 0 solves it, then the chunk's later rows take the block's update).
 __global__ void __launch_bounds__(kBlock)
-k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred, int which) {
+k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, int which) {
     __shared__ double T[kTri];
     __shared__ double rd[kWave];
     __shared__ double v[kChunk];
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
-    const int s = tk.y, tid = threadIdx.x, nthr = blockDim.x;
+    const Front F = front_of(tk);
+    const int s = tk.sn, tid = threadIdx.x, nthr = blockDim.x;
     double* xs = I.xp + F.f;
-    if (tk.z == 0) {
+    if (tk.a == 0) {
         const double* rhs = solve_in(I, which);
-        double* us = I.uvec + I.S.uv_off[s];
+        double* us = I.uvec + tk.uv;
         for (int k = tid; k < F.w; k += nthr) xs[k] = rhs[I.perm[F.f + k]];
         for (int i = tid; i < F.m - F.w; i += nthr) us[i] = 0.0;
         __syncthreads();
@@ -456,7 +530,7 @@ k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, in
             __syncthreads();
         }
     }
-    const int c0 = tk.z * kChunk, cw = min(kChunk, F.w - c0);
+    const int c0 = tk.a * kChunk, cw = min(kChunk, F.w - c0);
     for (int k = tid; k < cw; k += nthr) v[k] = xs[c0 + k];
     for (int b0 = 0; b0 < cw; b0 += kWave) {
         const int bw = min(kWave, cw - b0), b1 = b0 + bw;
@@ -496,37 +570,37 @@ k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, in
 // per thread): v[i] -= L[i, c0:c1) x[c0, c1), in xp (i < w) or in the update
 // vector (i >= w).
 __global__ void __launch_bounds__(kBlock)
-k_bigfwd_gemv(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred) {
+k_bigfwd_gemv(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
     __shared__ double x[kChunk];
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
-    const int c0 = tk.z * kChunk, cw = min(kChunk, F.w - c0), c1 = c0 + cw;
+    const Front F = front_of(tk);
+    const int c0 = tk.a * kChunk, cw = min(kChunk, F.w - c0), c1 = c0 + cw;
     for (int k = threadIdx.x; k < cw; k += blockDim.x) x[k] = I.xp[F.f + c0 + k];
     __syncthreads();
-    const int i = c1 + tk.w * kSolveRows + threadIdx.x;
+    const int i = c1 + tk.b * kSolveRows + threadIdx.x;
     if (i >= F.m) return;
     const gdouble* Li = global(F.L) + i + (int64_t)c0 * F.m;
     double acc = 0.0;
 #pragma unroll 16
     for (int k = 0; k < cw; ++k) acc = fma(Li[(int64_t)k * F.m], x[k], acc);
     if (i < F.w) I.xp[F.f + i] -= acc;
-    else I.uvec[I.S.uv_off[tk.y] + (i - F.w)] -= acc;
+    else I.uvec[tk.uv + (i - F.w)] -= acc;
 }
 
 // backward, task (inst, s, column block): bsum[f + k] = L[w:m, k]^T x(rows below)
 // for the block's columns; wave v takes columns k0 + v, k0 + v + 4, ..., lanes
 // walk the rows (a butterfly sums the lanes).
 __global__ void __launch_bounds__(kBlock)
-k_bigbwd_below(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred) {
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
+k_bigbwd_below(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
-    const int32_t* rows = I.S.rows + I.S.rows_ptr[tk.y];
+    const Front F = front_of(tk);
+    const int32_t* rows = I.S.rows + I.S.rows_ptr[tk.sn];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    const int k0 = tk.z * kSolveCols;
+    const int k0 = tk.a * kSolveCols;
     for (int k = k0 + wv; k < min(F.w, k0 + kSolveCols); k += nw) {
         double acc = 0.0;
 #pragma unroll 4
@@ -545,17 +619,17 @@ __device__ inline bool bsum_live(const Front& F, int c) { return F.m > F.w || (c
 // staged in shared memory, wave 0 solves it, then the chunk's earlier columns
 // take the block's rows of L); writes xp and the unpermuted solution.
 __global__ void __launch_bounds__(kBlock)
-k_bigbwd_tri(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred, int which) {
+k_bigbwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, int which) {
     __shared__ double T[kTri];
     __shared__ double rd[kWave];
     __shared__ double v[kChunk];
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
+    const Front F = front_of(tk);
     const int tid = threadIdx.x, nthr = blockDim.x;
-    const int c0 = tk.z * kChunk, cw = min(kChunk, F.w - c0);
-    const bool live = bsum_live(F, tk.z);
+    const int c0 = tk.a * kChunk, cw = min(kChunk, F.w - c0);
+    const bool live = bsum_live(F, tk.a);
     for (int k = tid; k < cw; k += nthr) v[k] = I.xp[F.f + c0 + k] - (live ? I.bsum[F.f + c0 + k] : 0.0);
     const int nblk = (cw + kWave - 1) / kWave;
     for (int bi = nblk - 1; bi >= 0; --bi) {
@@ -599,18 +673,18 @@ k_bigbwd_tri(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, in
 // k < c0, bsum[f + k] (+)= L[c0:c1, k]^T x[c0, c1) (the first contribution of a
 // supernode without rows below sets it); wave per column, lanes over the rows.
 __global__ void __launch_bounds__(kBlock)
-k_bigbwd_gemvt(const InstPtrs* __restrict__ Ia, const int4* __restrict__ tasks, int pred) {
+k_bigbwd_gemvt(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
     __shared__ double x[kChunk];
-    const int4 tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.x];
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(I, tk.y);
-    const int c0 = tk.z * kChunk, cw = min(kChunk, F.w - c0);
+    const Front F = front_of(tk);
+    const int c0 = tk.a * kChunk, cw = min(kChunk, F.w - c0);
     for (int k = threadIdx.x; k < cw; k += blockDim.x) x[k] = I.xp[F.f + c0 + k];
     __syncthreads();
-    const bool live = bsum_live(F, tk.z);
+    const bool live = bsum_live(F, tk.a);
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    const int k0 = tk.w * kSolveCols;
+    const int k0 = tk.b * kSolveCols;
     for (int k = k0 + wv; k < min(c0, k0 + kSolveCols); k += nw) {
         const gdouble* lk = global(F.L) + (int64_t)k * F.m + c0;
         double acc = 0.0;
@@ -628,7 +702,7 @@ int big_solve_rows() { return kSolveRows; }
 int big_solve_cols() { return kSolveCols; }
 int big_chunk() { return kChunk; }
 
-void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs* I, const int4* tasks, int count,
+void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs* I, const BigTask* tasks, int count,
                 size_t lds_bytes, hipStream_t st) {
     if (count <= 0) return;
     switch (kind) {
@@ -638,11 +712,8 @@ void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs*
         case kBigExtend:
             hipLaunchKernelGGL(k_big_extend, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);
             break;
-        case kBigPotrf:
-            hipLaunchKernelGGL(k_big_potrf, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);
-            break;
-        case kBigTrsm:
-            hipLaunchKernelGGL(k_big_trsm, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);
+        case kBigPanelStep:
+            hipLaunchKernelGGL(k_big_panel, dim3(count), dim3(kPanelThreads), 0, st, I, tasks, pred);
             break;
         case kBigUpdate:
             hipLaunchKernelGGL(k_big_update<false>, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);

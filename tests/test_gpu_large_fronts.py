@@ -1,0 +1,70 @@
+"""Large-front kernels at the edges of their tiles: every supernodal panel of a
+factorization against a dense Cholesky factorization, and a solve with it, on
+plates whose fronts end panels of 64 columns and blocks of 16 columns and rows
+at full, partial and empty remainders."""
+import sys
+
+import numpy as np
+import pytest
+import scipy.linalg as sla
+
+from paper_2606_04725_amd import nmpc as N
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -53
+
+
+def _note(msg):
+    print(f"[gpu-case] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+def _matrix(pat, n, seed):
+    """A symmetric diagonally dominant matrix on the pattern, its slot values."""
+    rng = np.random.default_rng(seed)
+    r, c = pat["k_rows"].astype(np.int64), pat["k_cols"].astype(np.int64)
+    v = rng.uniform(-1.0, 1.0, r.size)
+    off = r != c
+    weight = np.bincount(r[off], np.abs(v[off]), n) + np.bincount(c[off], np.abs(v[off]), n)
+    v[~off] = 1.0 + weight[r[~off]]
+    K = np.zeros((n, n))
+    K[r, c] = v
+    K[c, r] = v
+    return v, K
+
+
+@pytest.mark.parametrize("G,H", [(16, 6), (20, 5), (12, 20), (16, 14)])
+def test_large_front_factor_and_solve(G, H):
+    p = N.Problem(N.plate_structure(G, H, 0.01))
+    p.analyze()
+    z = p.export_symbolic()
+    sp, rp, rows, perm = z["snode_ptr"], z["snode_rows_ptr"], z["snode_rows"], z["perm"]
+    w, m = np.diff(sp), np.diff(rp)
+    large = m >= 200   # such a front's packed triangle exceeds shared memory
+    _note(f"plate {G} x {G} x {H}: {large.sum()} large fronts, up to {m.max()} rows and {w.max()} columns")
+    assert large.any()
+    kv, K = _matrix(p.patterns(), p.n, 7 * G + H)
+    ok, lv = p.factor(kv, eta=0.25)
+    assert ok
+    A = K[np.ix_(perm, perm)] + 0.25 * np.eye(p.n)
+    L = sla.cholesky(A, lower=True)
+    # |L - L_ref| <= c n u cond(A) |L| for either factorization; the matrix is
+    # diagonally dominant by 1.25 with rows of norm <= 2 |diagonal|
+    scale = np.max(np.abs(L))
+    cond = 2.0 * np.max(np.diag(A)) / 1.25
+    tol = 2 * p.n * U * cond * scale
+    off = 0
+    for s in range(len(w)):
+        P = lv[off:off + m[s] * w[s]].reshape(w[s], m[s]).T
+        off += m[s] * w[s]
+        R = rows[rp[s]:rp[s + 1]]
+        want = L[np.ix_(R, np.arange(sp[s], sp[s + 1]))]
+        low = np.tril(np.ones((m[s], w[s]), bool))
+        d = np.max(np.abs(P[low] - want[low]))
+        assert d <= tol, (s, int(w[s]), int(m[s]), d, tol)
+    b = np.random.default_rng(G).normal(size=p.n)
+    x = p.linear_solve(b)
+    M = K + 0.25 * np.eye(p.n)
+    back = np.max(np.abs(M @ x - b)) / (np.max(np.sum(np.abs(M), 1)) * np.max(np.abs(x)) + np.max(np.abs(b)))
+    assert back <= m.max() * U, back
