@@ -104,7 +104,6 @@ struct GenFns {
 // off + count)) or a large-supernode step (tasks[off .. off + count)).
 struct BLaunch {
     int kind, off, count;
-    bool lds;
     size_t bytes;
     int variant;
     int step;       // index of the instances' step it comes from
@@ -305,8 +304,7 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
     }
     // schedules: step j of the batch holds step j of every instance (the
     // forward lists aligned at the leaves, the backward lists at the roots), one
-    // launch per kind; factor groups split by whether their fronts fit in shared
-    // memory
+    // launch per kind
     const size_t lim = lds_limit_bytes();
     std::vector<Group> gl;
     std::vector<BigTask> tl;
@@ -332,8 +330,8 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
         size_t len = 0;
         for (auto* D : members) len = std::max(len, (D->*list).size());
         for (size_t j = 0; j < len; ++j) {
-            std::vector<Group> g_lds, g_glob, g_sol;
-            size_t b_lds = 0, b_sol = 0;
+            std::vector<Group> g_fac, g_sol;
+            size_t b_fac = 0, b_sol = 0;
             int gkind = 0, variant = 0, vfront = -1;
             std::vector<std::vector<BigTask>> by_kind(32);
             std::vector<size_t> kind_lds(32, 0);
@@ -351,17 +349,12 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
                             variant = st.variant;
                         }
                     }
-                    int slot = 0;
                     for (const auto& g : st.groups) {
                         if (st.kind == kStepGroupFactor) {
-                            if (g.lds_factor <= lim) {
-                                g_lds.push_back(Group{i, g.begin, g.end, 0});
-                                b_lds = std::max(b_lds, g.lds_factor);
-                            } else {
-                                g_glob.push_back(Group{i, g.begin, g.end, slot++});
-                            }
+                            g_fac.push_back(Group{i, g.begin, g.end});
+                            b_fac = std::max(b_fac, g.lds_factor);
                         } else {
-                            g_sol.push_back(Group{i, g.begin, g.end, 0});
+                            g_sol.push_back(Group{i, g.begin, g.end});
                             b_sol = std::max(b_sol, g.lds_solve);
                         }
                     }
@@ -370,17 +363,16 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
                     kind_lds[st.kind] = std::max(kind_lds[st.kind], st.lds);
                 }
             }
-            auto emit_groups = [&](const std::vector<Group>& g, int kind, bool lds, size_t bytes) {
+            auto emit_groups = [&](const std::vector<Group>& g, int kind, size_t bytes) {
                 if (g.empty()) return;
-                dst.push_back(BLaunch{kind, (int)gl.size(), (int)g.size(), lds, bytes, variant, (int)j});
+                dst.push_back(BLaunch{kind, (int)gl.size(), (int)g.size(), bytes, variant, (int)j});
                 gl.insert(gl.end(), g.begin(), g.end());
             };
-            emit_groups(g_lds, kStepGroupFactor, true, b_lds);
-            emit_groups(g_glob, kStepGroupFactor, false, 0);
-            emit_groups(g_sol, gkind, true, b_sol);
+            emit_groups(g_fac, kStepGroupFactor, b_fac);
+            emit_groups(g_sol, gkind, b_sol);
             for (int k = 0; k < 32; ++k) {
                 if (by_kind[k].empty()) continue;
-                dst.push_back(BLaunch{k, (int)tl.size(), (int)by_kind[k].size(), false, kind_lds[k], 0, (int)j});
+                dst.push_back(BLaunch{k, (int)tl.size(), (int)by_kind[k].size(), kind_lds[k], 0, (int)j});
                 tl.insert(tl.end(), by_kind[k].begin(), by_kind[k].end());
             }
         }
@@ -436,7 +428,7 @@ void cold_guess(Batch& B) {
 void run_launch(Batch& B, const BLaunch& L, int pred, double eta_force, int which) {
     switch (L.kind) {
         case kStepGroupFactor:
-            launch_factor_groups(L.lds, L.variant, pred, eta_force, B.dI, B.groups + L.off, L.count, L.bytes,
+            launch_factor_groups(L.variant, pred, eta_force, B.dI, B.groups + L.off, L.count, L.bytes,
                                  B.stream);
             break;
         case kStepGroupFwd:
@@ -739,35 +731,30 @@ nmpc_status device_init(Problem& p, std::string& err) {
         I.ntr = st.H;
     }
     // Supernode classes.  Small: the front fits in shared memory (one workgroup
-    // factors it there).  Medium: it does not, but has at most kMediumFront rows
-    // (one workgroup factors it in a global buffer).  Large: the multi-workgroup
-    // path works on it in place.  Solves use one workgroup when the panel fits
-    // in shared memory, the multi-workgroup path otherwise.
+    // factors it there).  Large: it does not (from 200 rows on), and the
+    // multi-workgroup path works on it in place: on one workgroup in a global
+    // buffer, which fronts of up to 256 rows once had, a level of them took
+    // 167 us (32 x 32 x 50 plate), their share of the large path about 15 us.
+    // Solves use one workgroup when the panel fits in shared memory, the
+    // multi-workgroup path otherwise.
     const size_t lim = lds_limit_bytes();
     const int nsn = sy.nsn;
     std::vector<char> big_fac(nsn, 0), big_sol(nsn, 0);
     auto rows_of = [&](int sn) { return (int64_t)(sy.sn_rows_ptr[sn + 1] - sy.sn_rows_ptr[sn]); };
     auto width_of = [&](int sn) { return (int64_t)(sy.sn_ptr[sn + 1] - sy.sn_ptr[sn]); };
-    // a shared-memory front is its packed lower triangle; a global one is square
-    auto packed_bytes = [&](int sn) {
-        const size_t mr = (size_t)rows_of(sn);
-        return mr * (mr + 1) / 2 * sizeof(double);
-    };
-    // plus m values of the fused forward solve (shared memory in both cases)
+    // a shared-memory front is its packed lower triangle, plus m values of the
+    // fused forward solve
     auto fac_bytes = [&](int sn) {
-        const size_t mr = (size_t)rows_of(sn), vb = mr * sizeof(double);
-        return packed_bytes(sn) + vb <= lim ? packed_bytes(sn) + vb : mr * (mr | 1) * sizeof(double);
+        const size_t mr = (size_t)rows_of(sn);
+        return (mr * (mr + 1) / 2 + mr) * sizeof(double);
     };
     auto sol_bytes = [&](int sn) {
         const size_t mr = (size_t)rows_of(sn), w = (size_t)width_of(sn);
         return (mr * (w | 1) + mr + 2 * w) * sizeof(double);
     };
-    int medium_max = 0;
     for (int sn = 0; sn < nsn; ++sn) {
-        const int64_t mr = rows_of(sn);
-        big_fac[sn] = fac_bytes(sn) > lim && mr > kMediumFront;
+        big_fac[sn] = fac_bytes(sn) > lim;
         big_sol[sn] = sol_bytes(sn) > lim;
-        if (!big_fac[sn] && fac_bytes(sn) > lim) medium_max = std::max<int>(medium_max, (int)mr);
     }
     // Fused forward solves: a supernode whose children all run it runs the
     // Newton step's forward solve with its factorization (their update vectors
@@ -782,7 +769,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
             for (int c = sy.child_ptr[sn]; ok && c < sy.child_ptr[sn + 1]; ++c) ok = fused[sy.child_list[c]] != 0;
             fused[sn] = ok ? 1 : 0;
         }
-    // Schedule: per level (bottom-up) one group step for its small and medium
+    // Schedule: per level (bottom-up) one group step for its small
     // supernodes and the step sequence of the large path for its large ones; the
     // top levels that hold at most kTailWidth supernodes (a chain), none large, form a
     // single group walked by one workgroup (a chain costs one launch).
@@ -1037,36 +1024,16 @@ nmpc_status device_init(Problem& p, std::string& err) {
         for (const auto& ch : chains) gb.groups.push_back(make_group(std::vector<int32_t>(ch.rbegin(), ch.rend())));
         D.bwd.push_back(gb);
     }
-    D.fac_launches = 0;
-    for (const auto& stp : D.fac) {
-        if (stp.kind != kStepGroupFactor) {
-            ++D.fac_launches;
-            continue;
-        }
-        bool in_lds = false, global = false;
-        for (const auto& g : stp.groups) (g.lds_factor <= lim ? in_lds : global) = true;
-        D.fac_launches += (int)in_lds + (int)global;
-    }
-    // front positions of the original entries: the large path keeps r + c (m | 1);
-    // a one-workgroup front takes the layout of its group (packed lower in shared
-    // memory; square with leading dimension m | 1 in a global buffer when any
-    // front of the group is too large for shared memory), a diagonal entry
-    // complemented (it takes + eta)
-    std::vector<char> square(nsn, 0);
-    for (const auto& stp : D.fac) {
-        if (stp.kind != kStepGroupFactor) continue;
-        for (const auto& g : stp.groups)
-            if (g.lds_factor > lim)
-                for (int i = g.begin; i < g.end; ++i) square[nodes[i]] = 1;
-    }
+    D.fac_launches = (int)D.fac.size();
+    // front positions of the original entries: the large path keeps r + c (m | 1),
+    // a one-workgroup front is packed, a diagonal entry complemented (it takes + eta)
     std::vector<int32_t> k_fpos = sy.k_fpos;
     for (int sn = 0; sn < nsn; ++sn) {
         if (big_fac[sn]) continue;
         const int64_t mr = rows_of(sn), ld = mr | 1;
-        const bool packed = !square[sn];
         for (int32_t t = sy.k_ptr[sn]; t < sy.k_ptr[sn + 1]; ++t) {
             const int64_t pos = sy.k_fpos[t], r = pos % ld, c = pos / ld;
-            const int64_t q = packed ? c * mr - c * (c + 1) / 2 + r : pos;
+            const int64_t q = c * mr - c * (c + 1) / 2 + r;
             k_fpos[t] = r == c ? ~(int32_t)q : (int32_t)q;
         }
     }
@@ -1079,17 +1046,6 @@ nmpc_status device_init(Problem& p, std::string& err) {
     }
     D.u_off = u_off;
     D.fused = fused;
-    // global front buffers for the medium groups of one step
-    int max_global = 0;
-    for (const auto& stp : D.fac) {
-        if (stp.kind != kStepGroupFactor) continue;
-        int cnt = 0;
-        for (const auto& g : stp.groups)
-            if (g.lds_factor > lim) ++cnt;
-        max_global = std::max(max_global, cnt);
-    }
-    const int64_t gstride = max_global > 0 ? (int64_t)medium_max * (medium_max | 1) : 0;
-    I.gstride = gstride;
     std::vector<void*>& A = D.allocs;
     DTRY(upload_c(A, I.jptr, st.jptr));
     DTRY(upload_c(A, I.jcol, st.jcol));
@@ -1195,7 +1151,6 @@ nmpc_status device_init(Problem& p, std::string& err) {
     DTRY(dalloc(A, I.part, (size_t)kMaxQ * std::max(1, pblocks)));
     DTRY(dalloc(A, I.filter, (size_t)2 * kFilterCapMax));
     DTRY(dalloc(A, I.dfac, (size_t)kBigDiag * max_bigs));
-    if (gstride > 0) DTRY(dalloc(A, I.gscratch, (size_t)gstride * max_global));
 #undef DTRY
     std::vector<Device*> one{&D};
     nmpc_status rc = batch_build(one, D.stream, D.self, err);

@@ -13,11 +13,6 @@ constexpr int kCholWave = 64;
 // Index maps of a front's lower triangle: base(j) + i is the position of
 // entry (i, j), i >= j.  Front orders stay far below 2^12, so the products
 // fit the full-rate 24-bit multiplier.
-struct SquareIdx {   // column-major, leading dimension ld
-    int ld;
-    __device__ int base(int j) const { return __mul24(j, ld); }
-    __device__ int operator()(int i, int j) const { return i + base(j); }
-};
 struct PackedIdx {   // lower triangle packed by columns: column j holds rows j .. m-1
     int m;
     __device__ int base(int j) const { return __mul24(j, m) - (__mul24(j, j + 1) >> 1); }

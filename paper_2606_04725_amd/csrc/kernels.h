@@ -21,7 +21,6 @@ namespace nmpc {
 constexpr int kBlock = 256;          // threads per block of every vector kernel
 constexpr int kFactorBlock = 256;    // threads per supernode group
 constexpr int kPanel = 8;            // pivot columns per blocked step of a front
-constexpr int kMediumFront = 256;    // largest front one workgroup factors in a global buffer
 constexpr int kMaxQ = 12;            // reduced quantities per phase
 constexpr int kMaxSeed = 16;         // controls per stage the sensitivity seed can hold
 constexpr int kFilterCapMax = 256;   // filter entries an instance can hold
@@ -169,8 +168,6 @@ struct InstPtrs {
     double *adj_rhs, *adj_w, *adj_out, *adj_b, *adj_d, *adj_lam, *adj_qr;
     double* adj_seed;   // seed of the sensitivities: u1 part (nu values), then the objective's
     const int32_t *wf_ptr, *wf_slot, *wf_col;   // Hessian rows, both triangles: (slot, column)
-    double* gscratch;
-    int64_t gstride;
     const int32_t* kcol_ptr;   // KKT slots of each permuted column: [kcol_ptr[j], kcol_ptr[j + 1])
     double* dfac;     // factored diagonal blocks on their way into the panels: kBigDiag doubles per large front of a level
     double* bsum;     // large-supernode backward solves: rows-below products per column
@@ -240,9 +237,9 @@ struct DevOpts {
 };
 
 // One group of supernodes of one instance: sched_nodes[begin .. end), walked in
-// order by one workgroup; slot selects the workgroup's global front buffer.
+// order by one workgroup.
 struct Group {
-    int inst, begin, end, slot;
+    int inst, begin, end;
 };
 
 // ---- model evaluation (kernels_model.hip) -------------------------------------------
@@ -311,11 +308,11 @@ void launch_adj_refine(int step, const InstPtrs* I, const IpmSpaces& S, double e
 // Multifrontal Cholesky (eqs. 20-21) of a list of groups, one workgroup per
 // group, for instances matching pred (kPredFactor during a solve) with eta
 // from the control block, or every instance with eta_force (pred kPredAll).
-// lds: fronts in shared memory (lds_bytes), else in the instance's gscratch.
+// The fronts stay in shared memory (lds_bytes).
 // variant: (threads per workgroup, panel width) = 0 (256, 8), 1 (512, 8),
 // 2 (128, 8), 3 (256, 4), 4 (512, 4); the same arithmetic up to the panel width.
 constexpr int kFactorVariants = 5;
-void launch_factor_groups(bool lds, int variant, int pred, double eta_force, const InstPtrs* I, const Group* g,
+void launch_factor_groups(int variant, int pred, double eta_force, const InstPtrs* I, const Group* g,
                           int groups, size_t lds_bytes, hipStream_t st);
 // Forward (eq. 23, rhs permutation fused) and back (eqs. 24-25, inverse
 // permutation fused) substitution over groups, vectors chosen by which.

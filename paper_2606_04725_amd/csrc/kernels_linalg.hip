@@ -13,7 +13,6 @@
 // walked by one workgroup, so a chain of fronts costs one launch.  Every sum is
 // taken in a fixed order, so results do not depend on scheduling.
 #include <cmath>
-#include <type_traits>
 
 #include "kernels.h"
 #include "front_chol.h"
@@ -130,21 +129,18 @@ __device__ __attribute__((always_inline)) inline int first_node(const InstPtrs& 
 }
 
 // One supernode: assemble the front, factor it, store the L panel and update.
-// Shared-memory fronts are packed lower triangles; the global buffer of a
-// medium front is square with an odd leading dimension.
-template <bool Lds, int P>
+// The front is a packed lower triangle in shared memory.
+template <int P>
 __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S, const double* __restrict__ kv, double eta, double* __restrict__ L,
                            double* __restrict__ U, int* __restrict__ fail, double* F, double* v, const InstPtrs& I,
                            bool fwd) {
-    using Idx = typename std::conditional<Lds, PackedIdx, SquareIdx>::type;
     // the first two children's records hang off the supernode itself, so they
     // are read with its sizes (one level of dependent loads less for the rounds)
     const ChildRec rec0 = child_rec_at(S.first_recs, 2 * s), rec1 = child_rec_at(S.first_recs, 2 * s + 1);
     const int f = global(S.sn_ptr)[s];
     const int w = global(S.sn_ptr)[s + 1] - f;
     const int m = (int)(global(S.rows_ptr)[s + 1] - global(S.rows_ptr)[s]);
-    Idx ix;
-    if constexpr (Lds) ix.m = m; else ix.ld = m | 1;
+    const PackedIdx ix{m};
     const int nb = m - w;
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave, nw = nthr / kWave;
@@ -205,7 +201,7 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
     bool hb = issue(rb, ib);
     double rv = 0.0;
     if (fw && tid < w) rv = global(I.rhs)[pk0];
-    const int fsize = Lds ? (m * (m + 1)) / 2 : m * (m | 1);
+    const int fsize = (m * (m + 1)) / 2;
     for (int e = tid; e < fsize; e += nthr) F[e] = 0.0;
     __syncthreads();
     auto place = [&](int pos, double v) {
@@ -271,7 +267,7 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
 }
 
 // Variants (threads per workgroup, panel width) the autotuner chooses from.
-template <bool Lds, int Threads, int P>
+template <int Threads, int P>
 __global__ void __launch_bounds__(Threads)
 k_factor_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ groups, int pred, double eta_force) {
     extern __shared__ double lds[];
@@ -280,15 +276,12 @@ k_factor_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ group
     const int s0 = first_node(I, g, pred);
     if (s0 < 0) return;
     const double eta = pred == kPredAll ? eta_force : I.ctl->eta;
-    // the front: shared memory, or the instance's global scratch for medium
-    // fronts; then the fused forward solve's vector in shared memory
-    double* F = Lds ? lds : I.gscratch + (int64_t)g.slot * I.gstride;
     const bool fwd = pred == kPredFactor;   // in a pass: the Newton step's right-hand side is assembled
     for (int i = g.begin; i < g.end; ++i) {
         const int s = i == g.begin ? s0 : I.S.sched_nodes[i];
         const int m = (int)(I.S.rows_ptr[s + 1] - I.S.rows_ptr[s]);
-        double* v = Lds ? lds + (m * (m + 1)) / 2 : lds;
-        factor_one<Lds, P>(s, I.S, I.kv, eta, I.L, I.U, &I.ctl->fail, F, v, I, fwd);
+        double* v = lds + (m * (m + 1)) / 2;   // the fused forward solve's vector
+        factor_one<P>(s, I.S, I.kv, eta, I.L, I.U, &I.ctl->fail, lds, v, I, fwd);
     }
 }
 
@@ -587,11 +580,11 @@ k_bwd_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ groups, 
 }  // namespace
 
 hipError_t linalg_configure(size_t max_lds_bytes) {
-    const void* fns[] = {reinterpret_cast<const void*>(k_factor_groups<true, 256, 8>),
-                         reinterpret_cast<const void*>(k_factor_groups<true, 512, 8>),
-                         reinterpret_cast<const void*>(k_factor_groups<true, 128, 8>),
-                         reinterpret_cast<const void*>(k_factor_groups<true, 256, 4>),
-                         reinterpret_cast<const void*>(k_factor_groups<true, 512, 4>),
+    const void* fns[] = {reinterpret_cast<const void*>(k_factor_groups<256, 8>),
+                         reinterpret_cast<const void*>(k_factor_groups<512, 8>),
+                         reinterpret_cast<const void*>(k_factor_groups<128, 8>),
+                         reinterpret_cast<const void*>(k_factor_groups<256, 4>),
+                         reinterpret_cast<const void*>(k_factor_groups<512, 4>),
                          reinterpret_cast<const void*>(k_fwd_groups), reinterpret_cast<const void*>(k_bwd_groups)};
     for (const void* fn : fns) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds_bytes);
@@ -601,25 +594,20 @@ hipError_t linalg_configure(size_t max_lds_bytes) {
 }
 
 template <int Threads, int P>
-void launch_variant(bool lds, int pred, double eta_force, const InstPtrs* I, const Group* g, int groups,
+void launch_variant(int pred, double eta_force, const InstPtrs* I, const Group* g, int groups,
                     size_t lds_bytes, hipStream_t st) {
-    if (lds)
-        hipLaunchKernelGGL((k_factor_groups<true, Threads, P>), dim3(groups), dim3(Threads), lds_bytes, st, I, g, pred,
-                           eta_force);
-    else
-        hipLaunchKernelGGL((k_factor_groups<false, Threads, P>), dim3(groups), dim3(Threads),
-                           kMediumFront * sizeof(double), st, I, g, pred, eta_force);
+    hipLaunchKernelGGL((k_factor_groups<Threads, P>), dim3(groups), dim3(Threads), lds_bytes, st, I, g, pred, eta_force);
 }
 
-void launch_factor_groups(bool lds, int variant, int pred, double eta_force, const InstPtrs* I, const Group* g,
+void launch_factor_groups(int variant, int pred, double eta_force, const InstPtrs* I, const Group* g,
                           int groups, size_t lds_bytes, hipStream_t st) {
     if (groups <= 0) return;
     switch (variant) {
-        case 1: launch_variant<512, 8>(lds, pred, eta_force, I, g, groups, lds_bytes, st); break;
-        case 2: launch_variant<128, 8>(lds, pred, eta_force, I, g, groups, lds_bytes, st); break;
-        case 3: launch_variant<256, 4>(lds, pred, eta_force, I, g, groups, lds_bytes, st); break;
-        case 4: launch_variant<512, 4>(lds, pred, eta_force, I, g, groups, lds_bytes, st); break;
-        default: launch_variant<256, 8>(lds, pred, eta_force, I, g, groups, lds_bytes, st); break;
+        case 1: launch_variant<512, 8>(pred, eta_force, I, g, groups, lds_bytes, st); break;
+        case 2: launch_variant<128, 8>(pred, eta_force, I, g, groups, lds_bytes, st); break;
+        case 3: launch_variant<256, 4>(pred, eta_force, I, g, groups, lds_bytes, st); break;
+        case 4: launch_variant<512, 4>(pred, eta_force, I, g, groups, lds_bytes, st); break;
+        default: launch_variant<256, 8>(pred, eta_force, I, g, groups, lds_bytes, st); break;
     }
 }
 
