@@ -474,8 +474,8 @@ nmpc_status nmpc_closed_loop_dev(nmpc_problem* p, int32_t steps, const double* t
 
 /* Autotuner of the supernode front kernels (the batched form's tile shapes):
  * for every factor launch of the problem's schedule, time each variant of the
- * one-workgroup front kernel (threads per workgroup 128 / 256 / 512, panel
- * width 4 / 8) on a diagonally dominant matrix with the problem's pattern and
+ * one-workgroup front kernel (256 or 512 threads per workgroup) on a diagonally
+ * dominant matrix with the problem's pattern and
  * keep the fastest; the symbolic partition is not changed.  Choices are cached
  * per structure hash for the life of the process, so problems of equal
  * structure are tuned once.  reps: timed repetitions per variant (>= 1);

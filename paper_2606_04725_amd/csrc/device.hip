@@ -54,7 +54,7 @@ struct LocalGroup {
 };
 struct Step {
     int kind = 0;
-    int variant = 0;                // front-kernel variant of a group factor step (autotuned)
+    int variant = 0, preset = 0;    // front-kernel variant of a group factor step: now (autotuned), and by rule
     std::vector<LocalGroup> groups;
     std::vector<int4> tasks;        // large path: (slot, supernode, a, b); the batch makes the records
     size_t lds = 0;                 // shared memory of a large-supernode solve kernel
@@ -731,7 +731,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
         I.ntr = st.H;
     }
     // Supernode classes.  Small: the front fits in shared memory (one workgroup
-    // factors it there).  Large: it does not (from 200 rows on), and the
+    // factors it there).  Large: it does not (from 201 rows on), and the
     // multi-workgroup path works on it in place: on one workgroup in a global
     // buffer, which fronts of up to 256 rows once had, a level of them took
     // 167 us (32 x 32 x 50 plate), their share of the large path about 15 us.
@@ -742,11 +742,11 @@ nmpc_status device_init(Problem& p, std::string& err) {
     std::vector<char> big_fac(nsn, 0), big_sol(nsn, 0);
     auto rows_of = [&](int sn) { return (int64_t)(sy.sn_rows_ptr[sn + 1] - sy.sn_rows_ptr[sn]); };
     auto width_of = [&](int sn) { return (int64_t)(sy.sn_ptr[sn + 1] - sy.sn_ptr[sn]); };
-    // a shared-memory front is its packed lower triangle, plus m values of the
-    // fused forward solve
+    // a shared-memory front is a packed lower triangle of one more row (the
+    // fused forward solve's)
     auto fac_bytes = [&](int sn) {
         const size_t mr = (size_t)rows_of(sn);
-        return (mr * (mr + 1) / 2 + mr) * sizeof(double);
+        return (mr + 1) * (mr + 2) / 2 * sizeof(double);
     };
     auto sol_bytes = [&](int sn) {
         const size_t mr = (size_t)rows_of(sn), w = (size_t)width_of(sn);
@@ -792,6 +792,17 @@ nmpc_status device_init(Problem& p, std::string& err) {
         }
         g.end = (int)nodes.size();
         return g;
+    };
+    // Threads of a factor launch by its largest front: with up to 64 rows one
+    // wave takes the whole panel and few tiles are left for others (10 x 20
+    // column: 13.6 us per launch with 256 threads, 13.8 with 512); larger fronts
+    // have tiles for eight waves (40 x 100 column: 19.6 and 16.2 us, 24 uneven
+    // columns: 32.3 and 28.5); 1024 threads gained nothing anywhere (16.9, 33.0).
+    auto preset_variant = [&](Step& stp) {
+        int64_t mr = 0;
+        for (const auto& g : stp.groups)
+            for (int i = g.begin; i < g.end; ++i) mr = std::max(mr, rows_of(nodes[i]));
+        stp.variant = stp.preset = mr > 64 ? 1 : 0;
     };
     auto ceil_div = [](int64_t a, int64_t b) { return (int)((a + b - 1) / b); };
     const int RB = big_row_block(), TL = big_tile(), SR = big_solve_rows(), SC = big_solve_cols(), CH = big_chunk();
@@ -919,6 +930,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
                 if (!fused[sn]) rest.push_back(sn);
             if (!rest.empty()) gr.groups.push_back(make_group(rest));
         }
+        preset_variant(gf);
         D.fac.push_back(gf);
         D.fwd.push_back(gs);
         if (!gr.groups.empty()) D.fwd_rest.push_back(gr);
@@ -940,6 +952,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
                 if (!fused[sn]) gr.groups.push_back(gs.groups.back());
             }
         }
+        preset_variant(gf);
         if (!gf.groups.empty()) D.fac.push_back(gf);
         big_factor_steps(bigs);
         if (!gs.groups.empty()) D.fwd.push_back(gs);
@@ -983,6 +996,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
             D.fwd_rest.push_back(gr);
         }
         gb.groups.push_back(make_group(std::vector<int32_t>(tail_nodes.rbegin(), tail_nodes.rend())));
+        preset_variant(gf);
         D.fac.push_back(gf);
         D.fwd.push_back(gs);
         D.bwd.push_back(gb);
@@ -1026,14 +1040,14 @@ nmpc_status device_init(Problem& p, std::string& err) {
     }
     D.fac_launches = (int)D.fac.size();
     // front positions of the original entries: the large path keeps r + c (m | 1),
-    // a one-workgroup front is packed, a diagonal entry complemented (it takes + eta)
+    // a one-workgroup front is packed (order m + 1), a diagonal entry complemented (it takes + eta)
     std::vector<int32_t> k_fpos = sy.k_fpos;
     for (int sn = 0; sn < nsn; ++sn) {
         if (big_fac[sn]) continue;
         const int64_t mr = rows_of(sn), ld = mr | 1;
         for (int32_t t = sy.k_ptr[sn]; t < sy.k_ptr[sn + 1]; ++t) {
             const int64_t pos = sy.k_fpos[t], r = pos % ld, c = pos / ld;
-            const int64_t q = c * mr - c * (c + 1) / 2 + r;
+            const int64_t q = c * (mr + 1) - c * (c + 1) / 2 + r;
             k_fpos[t] = r == c ? ~(int32_t)q : (int32_t)q;
         }
     }
@@ -2128,7 +2142,7 @@ nmpc_status device_autotune(Problem& p, int reps, int* changed, std::string& err
     apply_variants(D, best);
     D.adj_ready = false;   // the tuning runs overwrote the factor
     int nchg = 0;
-    for (size_t j = 0; j < D.fac.size(); ++j) nchg += D.fac[j].kind == kStepGroupFactor && best[j] != 0;
+    for (size_t j = 0; j < D.fac.size(); ++j) nchg += D.fac[j].kind == kStepGroupFactor && best[j] != D.fac[j].preset;
     if (changed) *changed = nchg;
     return NMPC_OK;
 }

@@ -20,7 +20,7 @@ namespace nmpc {
 
 constexpr int kBlock = 256;          // threads per block of every vector kernel
 constexpr int kFactorBlock = 256;    // threads per supernode group
-constexpr int kPanel = 8;            // pivot columns per blocked step of a front
+constexpr int kPanel = 8;            // columns per blocked step of a forward solve
 constexpr int kMaxQ = 12;            // reduced quantities per phase
 constexpr int kMaxSeed = 16;         // controls per stage the sensitivity seed can hold
 constexpr int kFilterCapMax = 256;   // filter entries an instance can hold
@@ -309,9 +309,9 @@ void launch_adj_refine(int step, const InstPtrs* I, const IpmSpaces& S, double e
 // group, for instances matching pred (kPredFactor during a solve) with eta
 // from the control block, or every instance with eta_force (pred kPredAll).
 // The fronts stay in shared memory (lds_bytes).
-// variant: (threads per workgroup, panel width) = 0 (256, 8), 1 (512, 8),
-// 2 (128, 8), 3 (256, 4), 4 (512, 4); the same arithmetic up to the panel width.
-constexpr int kFactorVariants = 5;
+// variant: threads per workgroup, 0: 256, 1: 512 (the same arithmetic).  Fewer
+// would leave rows of the largest front without a lane.
+constexpr int kFactorVariants = 2;
 void launch_factor_groups(int variant, int pred, double eta_force, const InstPtrs* I, const Group* g,
                           int groups, size_t lds_bytes, hipStream_t st);
 // Forward (eq. 23, rhs permutation fused) and back (eqs. 24-25, inverse

@@ -24,7 +24,6 @@
 // is split over column blocks, then one workgroup solves with the transposed
 // diagonal block.
 #include <cmath>
-#include <type_traits>
 
 #include "kernels.h"
 #include "front_chol.h"
@@ -138,9 +137,8 @@ k_big_extend(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks,
 // 64 x 64 diagonal block D of columns [kb, kb + pw) itself, so that the rows
 // below are solved in the same launch, as soon as a 16-column block of D is
 // factored.  Wave 0 holds D's rows one per lane and takes 16 pivot columns at a
-// time in registers: t, the 16 pivot rows copied to each 16-lane group, gives
-// every lane L(j, k) by a row broadcast of the vector unit (no shared memory,
-// no barrier inside the 16 columns); between blocks the next 16 columns take
+// time in registers (factor_rows: no shared memory, no barrier inside the 16
+// columns); between blocks the next 16 columns take
 // their update on the matrix cores.  Waves 1-4 solve 16 rows each, x D^T = a,
 // block after block: the solved blocks' products on the matrix cores, then the
 // 16 columns by broadcasts within the 16 lanes of a row group.  Wave 5 does the
@@ -155,59 +153,21 @@ constexpr int kPanelThreads = (kPanelRowWaves + 2) * kWave;
 constexpr int kLdx = 17;   // leading dimension of a wave's 16 rows in shared memory
 constexpr int kLdd = kBigPanel + 1;
 
-// Value of v in lane K of the caller's 16-lane group.
-template <int K>
-__device__ __attribute__((always_inline)) inline double group_lane(double v) {
-    return __builtin_amdgcn_mov_dpp(v, 0x150 + K, 0xf, 0xf, true);   // row_newbcast:K
-}
-
-template <int N, class F>
-__device__ __attribute__((always_inline)) inline void static_for(F&& f) {
-    if constexpr (N > 0) {
-        static_for<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
-}
-
-// 16 pivot columns of D (shared memory, kLdd) from column c0, by one wave; the
-// reciprocals of the diagonal to rd.
+// 16 pivot columns of D (shared memory, kLdd) from column c0, by one wave (a row
+// from c0 on per lane); the reciprocals of the diagonal to rd.
 __device__ __attribute__((always_inline)) inline bool factor_16(double* D, double* rd, int c0) {
-    const int lane = threadIdx.x & (kWave - 1), li = lane & 15;
-    double a[16], t[16];
+    const int lane = threadIdx.x & (kWave - 1), row = min(c0 + lane, kBigPanel - 1);
+    double a[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) a[c] = D[row + (c0 + c) * kLdd];
+    const bool bad = factor_rows<16>(a, 16);
+    double dg = 1.0;
 #pragma unroll
     for (int c = 0; c < 16; ++c) {
-        a[c] = D[lane + (c0 + c) * kLdd];   // rows above c0 hold zeros there
-        t[c] = D[(c0 + li) + (c0 + c) * kLdd];
+        if (c0 + lane < kBigPanel) D[row + (c0 + c) * kLdd] = a[c];   // above the diagonal: never read again
+        dg = lane == c ? a[c] : dg;
     }
-    bool bad = false;
-    double rv = 1.0;
-    auto recip = [&](double piv) {
-        if (!(piv > 0.0) || !(piv < INFINITY)) {
-            bad = true;
-            piv = 1.0;
-        }
-        return rsqrt(piv);
-    };
-    double inv = recip(group_lane<0>(t[0]));
-    static_for<16>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        rv = li == k ? inv : rv;
-        t[k] *= inv;
-        a[k] *= inv;
-        // the next pivot first, so that its reciprocal root is formed while the
-        // other columns take their updates
-        static_for<15 - k>([&](auto jc) {
-            constexpr int j = k + 1 + decltype(jc)::value;
-            const double b = group_lane<j>(t[k]);
-            t[j] = fma(-t[k], b, t[j]);
-            if constexpr (j == k + 1) inv = recip(group_lane<j>(t[j]));
-            a[j] = fma(-a[k], b, a[j]);
-        });
-        __builtin_amdgcn_sched_barrier(0);   // one pivot at a time: the broadcasts would fill the registers
-    });
-#pragma unroll
-    for (int c = 0; c < 16; ++c) D[lane + (c0 + c) * kLdd] = a[c];   // above the diagonal: never read again
-    if (lane < 16) rd[c0 + lane] = rv;
+    if (lane < 16) rd[c0 + lane] = 1.0 / dg;
     return bad;
 }
 

@@ -27,6 +27,15 @@ __device__ inline double shfl(double v, int lane) { return __shfl(v, lane, kWave
 
 constexpr int kBatch = 8;   // independent global loads in flight per thread
 
+// Entry k of a read-only array, k the same in every lane of the launch's
+// workgroup: a scalar load.  Sizes and offsets read this way stay in scalar
+// registers, so that the loops and branches they bound are scalar too and
+// their address arithmetic leaves the vector unit alone.
+template <class T>
+__device__ __attribute__((always_inline)) inline T uniform_at(const T* p, int k) {
+    return ((const __attribute__((address_space(4))) T*)p)[k];
+}
+
 // Copy n values from global to shared memory, kBatch loads in flight per thread.
 template <class T>
 __device__ void g2s(T* dst, const T* __restrict__ src, int64_t n) {
@@ -46,67 +55,25 @@ __device__ void g2s(T* dst, const T* __restrict__ src, int64_t n) {
     }
 }
 
-// Entry e of the lower triangle of an n x n matrix packed by columns, as (i, j)
-// (n <= 256 here, so b^2 - 8e is exact in single precision; the integer steps
-// correct the rounded root).
-__device__ __attribute__((always_inline)) inline void unpack_lower(int e, int n, int& i, int& j) {
-    const float b = 2.0f * (float)n + 1.0f;
-    int c = (int)((b - sqrtf(b * b - 8.0f * (float)e)) * 0.5f);
-    c = max(0, min(c, n - 1));
-    while (c > 0 && c * n - ((c * (c - 1)) >> 1) > e) --c;
-    while (c + 1 < n && (c + 1) * n - (((c + 1) * c) >> 1) <= e) ++c;
-    j = c;
-    i = c + (e - (c * n - ((c * (c - 1)) >> 1)));
-}
-
-// Loads of one round of a child's update block: entries e0 + tid + u nthr of
-// its packed lower triangle (ne entries), each as a value and the front rows of
-// its row and column (the child's relative row positions; -1: no entry).  The
-// front position is formed only when the entry is added, so the round's loads
-// stay in flight until then.
-// A child's first round can also carry the first kUvec nthr entries of its
-// update vector (fused forward solve).
-constexpr int kUvec = 2;
+// Loads of one round of a child's update block (nc x nc, lower triangle):
+// row block rb (a row per lane), columns jb + kCols wave, ..., kCols per wave.
+// A column is contiguous over the lanes, the columns' positions in the front
+// are the same for the whole wave (scalar loads), and the entries' places are
+// formed only when they are added, so the round's loads stay in flight until
+// then.  The first round of a row block also carries the block's entries of the
+// child's update vector (fused forward solve), on wave 0.
+constexpr int kCols = 8;
 struct ChildRound {
-    double v[kBatch];
-    int ri[kBatch], rj[kBatch];
-    double uv[kUvec];
-    int ur[kUvec];
+    double v[kCols];
+    int rj[kCols];   // front columns, wave-uniform
+    int ri;          // front row of the lane
+    double uv;
 };
 
-__device__ __attribute__((always_inline)) inline void child_round(const double* __restrict__ Uc, const int32_t* __restrict__ rel, int nc, int ne,
-                                   int e0, ChildRound& r, const double* __restrict__ uvec = nullptr) {
-    const int tid = threadIdx.x, nthr = blockDim.x;
-#pragma unroll
-    for (int u = 0; u < kUvec; ++u) {
-        const int i = tid + u * nthr;
-        r.ur[u] = -1;
-        r.uv[u] = 0.0;
-        if (uvec && i < nc) {
-            r.uv[u] = global(uvec)[i];
-            r.ur[u] = global(rel)[i];
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-        const int e = e0 + tid + u * nthr;
-        r.ri[u] = -1;
-        r.rj[u] = 0;
-        r.v[u] = 0.0;
-        if (e < ne) {
-            int i, j;
-            unpack_lower(e, nc, i, j);
-            r.v[u] = global(Uc)[i + (int64_t)j * nc];
-            r.ri[u] = global(rel)[i];
-            r.rj[u] = global(rel)[j];
-        }
-    }
-}
-
-// A child record read through a global-address-space pointer (field by field:
-// a structure copy does not cross address spaces).
+// A child record by scalar loads (field by field: a structure copy does not
+// cross address spaces).
 __device__ __attribute__((always_inline)) inline ChildRec child_rec_at(const ChildRec* recs, int k) {
-    const auto* g = global(recs) + k;
+    const auto* g = (const __attribute__((address_space(4))) ChildRec*)recs + k;
     ChildRec r;
     r.u_off = g->u_off;
     r.rel_off = g->rel_off;
@@ -120,37 +87,38 @@ __device__ __attribute__((always_inline)) inline ChildRec child_rec_at(const Chi
 // phase.  Both reads are issued before either is waited for (groups are never
 // empty, so the schedule entry exists whatever the phase).
 __device__ __attribute__((always_inline)) inline int first_node(const InstPtrs& I, const Group& g, int pred) {
-    const int32_t* sched = I.S.sched_nodes;
     const Ctl* c = I.ctl;   // every instance has its control block
-    const int s0 = global(sched)[g.begin];
-    const int ph = global(c)->phase;
+    const int s0 = uniform_at(I.S.sched_nodes, g.begin);
+    const int ph = __builtin_amdgcn_readfirstlane(global(c)->phase);   // written by earlier kernels: a vector load
     const bool active = pred == kPredAll || (pred == kPredFactor ? (ph == kPhB || ph == kPhF) : ph == pred);
     return active ? s0 : -1;
 }
 
 // One supernode: assemble the front, factor it, store the L panel and update.
-// The front is a packed lower triangle in shared memory.
-template <int P>
+// The front is a packed lower triangle in shared memory, of order m + 1: its last
+// row holds the fused forward solve's right-hand side (zeros without it), which
+// so takes every step as one more row, and its last entry is the spare slot.
 __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S, const double* __restrict__ kv, double eta, double* __restrict__ L,
-                           double* __restrict__ U, int* __restrict__ fail, double* F, double* v, const InstPtrs& I,
+                           double* __restrict__ U, int* __restrict__ fail, double* F, const InstPtrs& I,
                            bool fwd) {
     // the first two children's records hang off the supernode itself, so they
     // are read with its sizes (one level of dependent loads less for the rounds)
     const ChildRec rec0 = child_rec_at(S.first_recs, 2 * s), rec1 = child_rec_at(S.first_recs, 2 * s + 1);
-    const int f = global(S.sn_ptr)[s];
-    const int w = global(S.sn_ptr)[s + 1] - f;
-    const int m = (int)(global(S.rows_ptr)[s + 1] - global(S.rows_ptr)[s]);
-    const PackedIdx ix{m};
+    const int f = uniform_at(S.sn_ptr, s);
+    const int w = uniform_at(S.sn_ptr, s + 1) - f;
+    const int m = (int)(uniform_at(S.rows_ptr, s + 1) - uniform_at(S.rows_ptr, s));
+    const PackedIdx ix{m + 1};
     const int nb = m - w;
+    const int spare = ((m + 1) * (m + 2)) / 2 - 1;
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave, nw = nthr / kWave;
-    const bool fw = fwd && global(S.fused)[s];
+    const bool fw = fwd && uniform_at(S.fused, s);
     // original entries of the condensed matrix in this supernode's columns, the
     // first kBatch per thread loaded before the children's rounds (so that
     // waiting for them does not wait for the rounds); a diagonal entry's
     // position is stored complemented and takes + eta
-    const int kt0 = global(S.k_ptr)[s], kt1 = global(S.k_ptr)[s + 1];
-    const int c0 = global(S.child_ptr)[s], c1 = global(S.child_ptr)[s + 1];   // read with the entry range
+    const int kt0 = uniform_at(S.k_ptr, s), kt1 = uniform_at(S.k_ptr, s + 1);
+    const int c0 = uniform_at(S.child_ptr, s), c1 = uniform_at(S.child_ptr, s + 1);
     int kp[kBatch];
     double kx[kBatch];
 #pragma unroll
@@ -159,18 +127,16 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
         kp[u] = t < kt1 ? global(S.k_fpos)[t] : 0;
         kx[u] = t < kt1 ? global(kv)[t] : 0.0;
     }
-    // The children's update blocks go in rounds (kBatch entries per thread),
-    // child after child; the loads of two rounds are in flight ahead of the one
+    // The children's update blocks go in rounds, child after child, row block
+    // after row block; the loads of two rounds are in flight ahead of the one
     // being added, the first two issued before the front is cleared.  The
     // records of the current and the next child are read ahead of their rounds.
-    const int step = nthr * kBatch;
+    const int wvu = __builtin_amdgcn_readfirstlane(wv);
     struct RoundInfo {   // what the adds of an issued round need
-        int child, nc;
-        bool first;
-        const int32_t* rel;
-        const double* uv;
+        int child, nc, i0, j0;
+        bool uv;
     };
-    int pci = c0, pe0 = 0;   // the next round to issue
+    int pci = c0, prb = 0, pjb = 0;   // the next round to issue
     ChildRec prec = rec0, pnext = rec1;
     // the fused forward solve's right-hand side of the supernode's columns:
     // the permutation is read before the rounds, thread i's entry of the
@@ -179,19 +145,29 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
     const int pk0 = fw && tid < w ? global(I.perm)[f + tid] : 0;
     auto issue = [&](ChildRound& r, RoundInfo& info) -> bool {
         if (pci >= c1) return false;
-        const int nc = prec.nc, ne = (nc * (nc + 1)) / 2;
-        const int32_t* rel = S.rel + prec.rel_off;
-        const double* uvc = fw ? I.uvec + prec.uv_off : nullptr;
-        const bool first = pe0 == 0;
-        child_round(U + prec.u_off, rel, nc, ne, pe0, r, first ? uvc : nullptr);
-        info = RoundInfo{pci, nc, first, rel, uvc};
-        if (pe0 + step < ne) {
-            pe0 += step;
-        } else {
-            ++pci;
-            pe0 = 0;
-            prec = pnext;
-            if (pci + 1 < c1) pnext = child_rec_at(S.child_rec, pci + 1);
+        const int nc = prec.nc;
+        const int64_t uo = prec.u_off, ro = prec.rel_off;
+        const int i0 = kWave * prb, j0 = pjb + kCols * wvu, i = min(i0 + lane, nc - 1);
+        const auto* uc = global(U) + uo + i;
+#pragma unroll
+        for (int u = 0; u < kCols; ++u) {
+            const int j = min(j0 + u, nc - 1);
+            r.rj[u] = uniform_at(S.rel + ro, j);
+            r.v[u] = uc[j * nc];
+        }
+        r.ri = global(S.rel)[ro + i];
+        const bool uv = fw && wvu == 0 && pjb == 0;
+        r.uv = uv ? global(I.uvec)[prec.uv_off + i] : 0.0;
+        info = RoundInfo{pci, nc, i0, j0, uv};
+        pjb += kCols * nw;
+        if (pjb >= min(nc, i0 + kWave)) {   // past the row block's last column
+            pjb = 0;
+            if (kWave * ++prb >= nc) {
+                prb = 0;
+                ++pci;
+                prec = pnext;
+                if (pci + 1 < c1) pnext = child_rec_at(S.child_rec, pci + 1);
+            }
         }
         return true;
     };
@@ -201,7 +177,7 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
     bool hb = issue(rb, ib);
     double rv = 0.0;
     if (fw && tid < w) rv = global(I.rhs)[pk0];
-    const int fsize = (m * (m + 1)) / 2;
+    const int fsize = ((m + 1) * (m + 2)) / 2;
     for (int e = tid; e < fsize; e += nthr) F[e] = 0.0;
     __syncthreads();
     auto place = [&](int pos, double v) {
@@ -215,12 +191,11 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
     for (int u = 0; u < kBatch; ++u)
         if (kt0 + tid + u * nthr < kt1) place(kp[u], kx[u]);
     for (int t = kt0 + tid + kBatch * nthr; t < kt1; t += nthr) place(global(S.k_fpos)[t], global(kv)[t]);
-    // fused forward solve of the Newton step: v over the front's rows starts
-    // from the permuted right-hand side of the supernode's columns (before the
-    // barrier that precedes the children's update vectors)
+    // fused forward solve of the Newton step: the last row starts from the
+    // permuted right-hand side of the supernode's columns (before the barrier
+    // that precedes the children's update vectors)
     if (fw)
-        for (int i = tid; i < m; i += nthr)
-            v[i] = i < w ? (i == tid ? rv : global(I.rhs)[global(I.perm)[f + i]]) : 0.0;
+        for (int i = tid; i < w; i += nthr) F[ix(m, i)] = i == tid ? rv : global(I.rhs)[global(I.perm)[f + i]];
     __syncthreads();
     // extend-add in fixed order; children are separated by barriers (two
     // children can add into the same entry, one child's entries are distinct)
@@ -228,15 +203,18 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
         ChildRound rc;
         RoundInfo ic{};
         const bool hc = issue(rc, ic);
+        const int i = ia.i0 + lane;
+        int at[kCols];
+        double x[kCols];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            if (ra.ri[u] >= 0) F[ix(ra.ri[u], ra.rj[u])] += ra.v[u];
-        if (fw && ia.first) {   // the child's update vector, with its first round
-#pragma unroll
-            for (int u = 0; u < kUvec; ++u)
-                if (ra.ur[u] >= 0) v[ra.ur[u]] += ra.uv[u];
-            for (int i = tid + kUvec * nthr; i < ia.nc; i += nthr) v[ia.rel[i]] += ia.uv[i];
+        for (int u = 0; u < kCols; ++u) {   // entries outside the triangle go to the spare slot
+            const int j = ia.j0 + u;
+            at[u] = (i < ia.nc && j <= i) ? ix.base(ra.rj[u]) + ra.ri : spare;
+            x[u] = F[at[u]];
         }
+#pragma unroll
+        for (int u = 0; u < kCols; ++u) F[at[u]] = x[u] + ra.v[u];
+        if (ia.uv && i < ia.nc) F[ix(m, ra.ri)] += ra.uv;
         if (!hb || ib.child != ia.child) __syncthreads();
         ra = rb;
         ia = ib;
@@ -245,30 +223,55 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
         ib = ic;
         hb = hc;
     }
-    partial_cholesky<P>(F, ix, m, w, fail, fw ? v : nullptr, false);
+    partial_cholesky(F, ix, w, spare, fail);
     // the update block (rows and columns w and on) takes its update before the
     // panel goes out: global stores in flight would hold the update's first
     // shared-memory loads until they complete (their data registers are reused)
-    if (nb > 0) update_block(F, ix, m, w);
-    auto* Ls = global(L + global(S.l_off)[s]);
-    for (int jc = wv; jc < w; jc += nw)
-        for (int i = lane; i < m; i += kWave) Ls[i + jc * m] = i >= jc ? F[ix(i, jc)] : 0.0;
+    if (nb > 0) update_block(F, ix, w, spare);
+    // kStore columns per wave at a time, so that their shared-memory reads are
+    // in flight together
+    constexpr int kStore = 4;
+    auto* Ls = global(L + uniform_at(S.l_off, s));
+    for (int jc = kStore * wvu; jc < w; jc += kStore * nw)
+        for (int i = lane; i < m; i += kWave) {
+            double x[kStore];
+#pragma unroll
+            for (int u = 0; u < kStore; ++u) {
+                const int j = min(jc + u, w - 1);
+                x[u] = F[ix(max(i, j), j)];
+            }
+#pragma unroll
+            for (int u = 0; u < kStore; ++u)
+                if (jc + u < w) Ls[i + (jc + u) * m] = i >= jc + u ? x[u] : 0.0;
+        }
     if (fw) {   // the forward solve's part of the columns and the update vector
-        for (int k = tid; k < w; k += nthr) global(I.xp)[f + k] = v[k];
-        auto* us = global(I.uvec + global(S.uv_off)[s]);
-        for (int i = w + tid; i < m; i += nthr) us[i - w] = v[i];
+        for (int k = tid; k < w; k += nthr) global(I.xp)[f + k] = F[ix(m, k)];
+        auto* us = global(I.uvec + uniform_at(S.uv_off, s));
+        for (int i = w + tid; i < m; i += nthr) us[i - w] = F[ix(m, i)];
     }
     if (nb > 0) {
-        auto* Us = global(U + global(S.u_off)[s]);
-        for (int jj = wv; jj < nb; jj += nw)
-            for (int ii = jj + lane; ii < nb; ii += kWave) Us[ii + jj * nb] = F[ix(w + ii, w + jj)];
+        auto* Us = global(U + uniform_at(S.u_off, s));
+        for (int jj = kStore * wvu; jj < nb; jj += kStore * nw)
+            for (int ii = (jj & ~(kWave - 1)) + lane; ii < nb; ii += kWave) {
+                double x[kStore];
+#pragma unroll
+                for (int u = 0; u < kStore; ++u) {
+                    const int j = min(jj + u, nb - 1);
+                    x[u] = F[ix(w + max(ii, j), w + j)];
+                }
+#pragma unroll
+                for (int u = 0; u < kStore; ++u)
+                    if (jj + u <= ii) Us[ii + (jj + u) * nb] = x[u];
+            }
     }
     __syncthreads();   // the front buffer is reused by the next supernode of the group
 }
 
-// Variants (threads per workgroup, panel width) the autotuner chooses from.
-template <int Threads, int P>
-__global__ void __launch_bounds__(Threads)
+// Variants (threads per workgroup) the autotuner chooses from.
+// (two waves per SIMD at least: at most 256 registers, so that the matrix cores'
+// accumulators stay in the vector registers)
+template <int Threads>
+__global__ void __launch_bounds__(Threads, 2)
 k_factor_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ groups, int pred, double eta_force) {
     extern __shared__ double lds[];
     const Group g = groups[blockIdx.x];
@@ -278,10 +281,8 @@ k_factor_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ group
     const double eta = pred == kPredAll ? eta_force : I.ctl->eta;
     const bool fwd = pred == kPredFactor;   // in a pass: the Newton step's right-hand side is assembled
     for (int i = g.begin; i < g.end; ++i) {
-        const int s = i == g.begin ? s0 : I.S.sched_nodes[i];
-        const int m = (int)(I.S.rows_ptr[s + 1] - I.S.rows_ptr[s]);
-        double* v = lds + (m * (m + 1)) / 2;   // the fused forward solve's vector
-        factor_one<P>(s, I.S, I.kv, eta, I.L, I.U, &I.ctl->fail, lds, v, I, fwd);
+        const int s = i == g.begin ? s0 : uniform_at(I.S.sched_nodes, i);
+        factor_one(s, I.S, I.kv, eta, I.L, I.U, &I.ctl->fail, lds, I, fwd);
     }
 }
 
@@ -334,28 +335,28 @@ __device__ __attribute__((always_inline)) void stage_panel(const double* __restr
 __device__ __attribute__((always_inline)) void fwd_one(int s, const SnView& S, const double* __restrict__ L, double* __restrict__ uvec,
                         const double* __restrict__ rhs, const int32_t* __restrict__ perm, double* __restrict__ xp,
                         double* lds) {
-    const int f = S.sn_ptr[s];
-    const int w = S.sn_ptr[s + 1] - f;
-    const int m = (int)(S.rows_ptr[s + 1] - S.rows_ptr[s]);
+    const int f = uniform_at(S.sn_ptr, s);
+    const int w = uniform_at(S.sn_ptr, s + 1) - f;
+    const int m = (int)(uniform_at(S.rows_ptr, s + 1) - uniform_at(S.rows_ptr, s));
     const int tid = threadIdx.x, nthr = blockDim.x;
     double* P = lds;
     double* rdiag = P + (int64_t)m * w;
     double* v = rdiag + w;
     double* xs = v + m;
-    stage_panel(L + S.l_off[s], m, w, P, rdiag);
+    stage_panel(L + uniform_at(S.l_off, s), m, w, P, rdiag);
     for (int i = tid; i < m; i += nthr) v[i] = i < w ? rhs[perm[f + i]] : 0.0;
     __syncthreads();
-    for (int ci = S.child_ptr[s]; ci < S.child_ptr[s + 1]; ++ci) {
-        const int c = S.child_list[ci];
-        const int nc = (int)(S.uv_off[c + 1] - S.uv_off[c]);
-        const double* uc = uvec + S.uv_off[c];
-        const int32_t* rc = S.rel + S.rel_off[c];
+    for (int ci = uniform_at(S.child_ptr, s); ci < uniform_at(S.child_ptr, s + 1); ++ci) {
+        const ChildRec rec = child_rec_at(S.child_rec, ci);
+        const int nc = rec.nc;
+        const double* uc = uvec + rec.uv_off;
+        const int32_t* rc = S.rel + rec.rel_off;
         for (int i = tid; i < nc; i += nthr) v[rc[i]] += uc[i];
         __syncthreads();
     }
     blocked_forward(P, rdiag, m, w, v, xs);
     for (int k = tid; k < w; k += nthr) xp[f + k] = xs[k];
-    double* us = uvec + S.uv_off[s];
+    double* us = uvec + uniform_at(S.uv_off, s);
     for (int i = w + tid; i < m; i += nthr) us[i - w] = v[i];
     __syncthreads();
 }
@@ -368,7 +369,7 @@ k_fwd_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ groups, 
     const int s0 = first_node(I, g, pred);
     if (s0 < 0) return;
     for (int i = g.begin; i < g.end; ++i)
-        fwd_one(i == g.begin ? s0 : I.S.sched_nodes[i], I.S, I.L, I.uvec, solve_in(I, which), I.perm, I.xp, lds);
+        fwd_one(i == g.begin ? s0 : uniform_at(I.S.sched_nodes, i), I.S, I.L, I.uvec, solve_in(I, which), I.perm, I.xp, lds);
 }
 
 // Value of v in lane k of the wave, in every lane (k wave-uniform).
@@ -409,9 +410,10 @@ __device__ __attribute__((always_inline)) inline void group_sums(double (&acc)[k
 }
 __device__ __attribute__((always_inline)) void bwd_one(int s, const SnView& S, const double* __restrict__ L, double* __restrict__ xp,
                         const int32_t* __restrict__ perm, double* __restrict__ out, double* lds) {
-    const int f = global(S.sn_ptr)[s];
-    const int w = global(S.sn_ptr)[s + 1] - f;
-    const int m = (int)(global(S.rows_ptr)[s + 1] - global(S.rows_ptr)[s]);
+    const int f = uniform_at(S.sn_ptr, s);
+    const int w = uniform_at(S.sn_ptr, s + 1) - f;
+    const int64_t ro = uniform_at(S.rows_ptr, s);
+    const int m = (int)(uniform_at(S.rows_ptr, s + 1) - ro);
     const int nb = m - w;
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave;
@@ -421,8 +423,8 @@ __device__ __attribute__((always_inline)) void bwd_one(int s, const SnView& S, c
     double* xb = rdiag + w;
     double* v = xb + nb;
     double* xs = v + w;
-    const double* Ls = L + global(S.l_off)[s];
-    const int32_t* rows = S.rows + global(S.rows_ptr)[s];
+    const double* Ls = L + uniform_at(S.l_off, s);
+    const int32_t* rows = S.rows + ro;
     const int ri = tid < nb ? global(rows)[w + tid] : 0;
     const double dg = tid < w ? global(Ls)[tid + (int64_t)tid * m] : 1.0;
     const double xv = tid < w ? global(xp)[f + tid] : 0.0;
@@ -574,17 +576,14 @@ k_bwd_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ groups, 
     const int s0 = first_node(I, g, pred);
     if (s0 < 0) return;
     for (int i = g.begin; i < g.end; ++i)
-        bwd_one(i == g.begin ? s0 : I.S.sched_nodes[i], I.S, I.L, I.xp, I.perm, solve_out(I, which), lds);
+        bwd_one(i == g.begin ? s0 : uniform_at(I.S.sched_nodes, i), I.S, I.L, I.xp, I.perm, solve_out(I, which), lds);
 }
 
 }  // namespace
 
 hipError_t linalg_configure(size_t max_lds_bytes) {
-    const void* fns[] = {reinterpret_cast<const void*>(k_factor_groups<256, 8>),
-                         reinterpret_cast<const void*>(k_factor_groups<512, 8>),
-                         reinterpret_cast<const void*>(k_factor_groups<128, 8>),
-                         reinterpret_cast<const void*>(k_factor_groups<256, 4>),
-                         reinterpret_cast<const void*>(k_factor_groups<512, 4>),
+    const void* fns[] = {reinterpret_cast<const void*>(k_factor_groups<256>),
+                         reinterpret_cast<const void*>(k_factor_groups<512>),
                          reinterpret_cast<const void*>(k_fwd_groups), reinterpret_cast<const void*>(k_bwd_groups)};
     for (const void* fn : fns) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds_bytes);
@@ -593,22 +592,13 @@ hipError_t linalg_configure(size_t max_lds_bytes) {
     return hipSuccess;
 }
 
-template <int Threads, int P>
-void launch_variant(int pred, double eta_force, const InstPtrs* I, const Group* g, int groups,
-                    size_t lds_bytes, hipStream_t st) {
-    hipLaunchKernelGGL((k_factor_groups<Threads, P>), dim3(groups), dim3(Threads), lds_bytes, st, I, g, pred, eta_force);
-}
-
-void launch_factor_groups(int variant, int pred, double eta_force, const InstPtrs* I, const Group* g,
-                          int groups, size_t lds_bytes, hipStream_t st) {
+void launch_factor_groups(int variant, int pred, double eta_force, const InstPtrs* I, const Group* g, int groups,
+                          size_t lds_bytes, hipStream_t st) {
     if (groups <= 0) return;
-    switch (variant) {
-        case 1: launch_variant<512, 8>(pred, eta_force, I, g, groups, lds_bytes, st); break;
-        case 2: launch_variant<128, 8>(pred, eta_force, I, g, groups, lds_bytes, st); break;
-        case 3: launch_variant<256, 4>(pred, eta_force, I, g, groups, lds_bytes, st); break;
-        case 4: launch_variant<512, 4>(pred, eta_force, I, g, groups, lds_bytes, st); break;
-        default: launch_variant<256, 8>(pred, eta_force, I, g, groups, lds_bytes, st); break;
-    }
+    if (variant == 1)
+        hipLaunchKernelGGL(k_factor_groups<512>, dim3(groups), dim3(512), lds_bytes, st, I, g, pred, eta_force);
+    else
+        hipLaunchKernelGGL(k_factor_groups<256>, dim3(groups), dim3(256), lds_bytes, st, I, g, pred, eta_force);
 }
 
 void launch_fwd_groups(int pred, int which, const InstPtrs* I, const Group* g, int groups, size_t lds_bytes,

@@ -1,7 +1,8 @@
-"""Large-front kernels at the edges of their tiles: every supernodal panel of a
+"""Front kernels at the edges of their tiles: every supernodal panel of a
 factorization against a dense Cholesky factorization, and a solve with it, on
-plates whose fronts end panels of 64 columns and blocks of 16 columns and rows
-at full, partial and empty remainders."""
+plates whose large fronts end panels of 64 columns and blocks of 16 columns and
+rows at full, partial and empty remainders, and on columns whose one-workgroup
+fronts do the same at 8 and 16 columns, 16 and 48 rows."""
 import sys
 
 import numpy as np
@@ -34,17 +35,14 @@ def _matrix(pat, n, seed):
     return v, K
 
 
-@pytest.mark.parametrize("G,H", [(16, 6), (20, 5), (12, 20), (16, 14)])
-def test_large_front_factor_and_solve(G, H):
-    p = N.Problem(N.plate_structure(G, H, 0.01))
+def _check(p, seed, name):
     p.analyze()
     z = p.export_symbolic()
     sp, rp, rows, perm = z["snode_ptr"], z["snode_rows_ptr"], z["snode_rows"], z["perm"]
     w, m = np.diff(sp), np.diff(rp)
-    large = m >= 200   # such a front's packed triangle exceeds shared memory
-    _note(f"plate {G} x {G} x {H}: {large.sum()} large fronts, up to {m.max()} rows and {w.max()} columns")
-    assert large.any()
-    kv, K = _matrix(p.patterns(), p.n, 7 * G + H)
+    large = m > 200   # such a front's packed triangle exceeds shared memory
+    _note(f"{name}: {large.sum()} of {m.size} fronts large, up to {m.max()} rows and {w.max()} columns")
+    kv, K = _matrix(p.patterns(), p.n, seed)
     ok, lv = p.factor(kv, eta=0.25)
     assert ok
     A = K[np.ix_(perm, perm)] + 0.25 * np.eye(p.n)
@@ -63,8 +61,37 @@ def test_large_front_factor_and_solve(G, H):
         low = np.tril(np.ones((m[s], w[s]), bool))
         d = np.max(np.abs(P[low] - want[low]))
         assert d <= tol, (s, int(w[s]), int(m[s]), d, tol)
-    b = np.random.default_rng(G).normal(size=p.n)
+    b = np.random.default_rng(seed).normal(size=p.n)
     x = p.linear_solve(b)
     M = K + 0.25 * np.eye(p.n)
     back = np.max(np.abs(M @ x - b)) / (np.max(np.sum(np.abs(M), 1)) * np.max(np.abs(x)) + np.max(np.abs(b)))
     assert back <= m.max() * U, back
+    return m, w
+
+
+@pytest.mark.parametrize("G,H", [(16, 6), (20, 5), (12, 20), (16, 14)])
+def test_large_front_factor_and_solve(G, H):
+    m, w = _check(N.Problem(N.plate_structure(G, H, 0.01)), 7 * G + H, f"plate {G} x {G} x {H}")
+    assert np.any(m > 200)
+
+
+@pytest.mark.parametrize("trays,H", [(4, 1), (6, 3), (10, 20), (23, 41), (60, 24)])
+def test_small_front_factor_and_solve(trays, H):
+    m, w = _check(N.Problem(N.distillation_structure(trays, H, 0.05, 2.5)), 100 * trays + H, f"column {trays} x {H}")
+    assert not np.any(m > 200)
+
+
+def test_indefinite_front_is_reported():
+    p = N.Problem(N.distillation_structure(10, 20, 0.05, 2.5))
+    p.analyze()
+    pat = p.patterns()
+    kv, _ = _matrix(pat, p.n, 3)
+    diag = np.flatnonzero(pat["k_rows"] == pat["k_cols"])
+    for at in (diag[0], diag[p.n // 2], diag[-1]):   # one pivot at a time, in different fronts
+        for bad in (-1e6, np.nan, np.inf):
+            v = kv.copy()
+            v[at] = bad
+            ok, _ = p.factor(v, want_l=False)
+            assert not ok
+    ok, _ = p.factor(kv, want_l=False)
+    assert ok
