@@ -817,20 +817,9 @@ nmpc_status device_init(Problem& p, std::string& err) {
     auto big_factor_steps = [&](const std::vector<int32_t>& bigs) {
         std::vector<int4> t;
         for (int32_t sn : bigs)
-            for (int j = 0; j < rows_of(sn); ++j) t.push_back(int4{0, sn, j, 0});
-        push(D.fac, kBigInit, std::move(t));
-        int maxch = 0;
-        for (int32_t sn : bigs) maxch = std::max(maxch, sy.child_ptr[sn + 1] - sy.child_ptr[sn]);
-        for (int r = 0; r < maxch; ++r) {
-            std::vector<int4> e;
-            for (int32_t sn : bigs) {
-                if (sy.child_ptr[sn] + r >= sy.child_ptr[sn + 1]) continue;
-                const int c = sy.child_list[sy.child_ptr[sn] + r];
-                const int nc = (int)(rows_of(c) - width_of(c));
-                for (int jc = 0; jc < nc; ++jc) e.push_back(int4{0, sn, r, jc});
-            }
-            push(D.fac, kBigExtend, std::move(e));
-        }
+            for (int j = 0; j < rows_of(sn); j += kBigAsmCols)
+                for (int64_t q = j / kBigChunk; q * kBigChunk < rows_of(sn); ++q) t.push_back(int4{0, sn, j, (int)q});
+        push(D.fac, kBigAssemble, std::move(t));
         int64_t wmax = 0;
         for (int32_t sn : bigs) wmax = std::max(wmax, width_of(sn));
         for (int64_t kb = 0; kb < wmax; kb += kBigOuter) {
@@ -1039,17 +1028,58 @@ nmpc_status device_init(Problem& p, std::string& err) {
         D.bwd.push_back(gb);
     }
     D.fac_launches = (int)D.fac.size();
-    // front positions of the original entries: the large path keeps r + c (m | 1),
-    // a one-workgroup front is packed (order m + 1), a diagonal entry complemented (it takes + eta)
+    // front positions of the original entries: their row for the large path (its
+    // slots are walked by column), the place in the packed triangle of order m + 1
+    // for a one-workgroup front, a diagonal entry complemented (it takes + eta)
     std::vector<int32_t> k_fpos = sy.k_fpos;
     for (int sn = 0; sn < nsn; ++sn) {
-        if (big_fac[sn]) continue;
         const int64_t mr = rows_of(sn), ld = mr | 1;
         for (int32_t t = sy.k_ptr[sn]; t < sy.k_ptr[sn + 1]; ++t) {
             const int64_t pos = sy.k_fpos[t], r = pos % ld, c = pos / ld;
             const int64_t q = c * (mr + 1) - c * (c + 1) / 2 + r;
-            k_fpos[t] = r == c ? ~(int32_t)q : (int32_t)q;
+            k_fpos[t] = big_fac[sn] ? (int32_t)r : (r == c ? ~(int32_t)q : (int32_t)q);
         }
+    }
+    // the child columns that land in each column of a large front, in child order
+    std::vector<int32_t> big_col(std::max(nsn, 1), 0), big_ptr, chunk_pos;
+    std::vector<BigEntry> big_ent;
+    {
+        int64_t cols = 0;
+        for (int sn = 0; sn < nsn; ++sn)
+            if (big_fac[sn]) {
+                big_col[sn] = (int32_t)cols;
+                cols += rows_of(sn);
+            }
+        big_ptr.assign((size_t)cols + 1, 0);
+        auto each = [&](auto&& fn) {   // fn(column of the front in big_ptr, child, column of the child)
+            for (int sn = 0; sn < nsn; ++sn) {
+                if (!big_fac[sn]) continue;
+                for (int ci = sy.child_ptr[sn]; ci < sy.child_ptr[sn + 1]; ++ci) {
+                    const int c = sy.child_list[ci];
+                    const int nc = (int)(rows_of(c) - width_of(c));
+                    for (int jc = 0; jc < nc; ++jc) fn(big_col[sn] + sy.rel[sy.rel_off[c] + jc], c, jc);
+                }
+            }
+        };
+        each([&](int32_t col, int, int) { ++big_ptr[(size_t)col + 1]; });
+        for (size_t j = 0; j + 1 < big_ptr.size(); ++j) big_ptr[j + 1] += big_ptr[j];
+        std::vector<int32_t> fill(big_ptr.begin(), big_ptr.end() - 1), first(std::max(nsn, 1), -1);
+        for (int sn = 0; sn < nsn; ++sn) {   // where a child's rows pass the chunks of its (large) parent
+            if (!big_fac[sn]) continue;
+            for (int ci = sy.child_ptr[sn]; ci < sy.child_ptr[sn + 1]; ++ci) {
+                const int c = sy.child_list[ci];
+                const auto rb = sy.rel.begin() + sy.rel_off[c], re = rb + (rows_of(c) - width_of(c));
+                first[c] = (int32_t)chunk_pos.size();
+                for (int64_t q = 0; q * kBigChunk < rows_of(sn); ++q)
+                    chunk_pos.push_back((int32_t)(std::lower_bound(rb, re, (int32_t)(q * kBigChunk)) - rb));
+                chunk_pos.push_back((int32_t)(re - rb));
+            }
+        }
+        big_ent.resize((size_t)big_ptr.back());
+        each([&](int32_t col, int c, int jc) {
+            const int nc = (int)(rows_of(c) - width_of(c));
+            big_ent[(size_t)fill[col]++] = BigEntry{u_off[c] + (int64_t)jc * nc, sy.rel_off[c], jc, nc, first[c], 0};
+        });
     }
     // factored diagonal blocks of the large fronts of one level
     size_t max_bigs = 0;
@@ -1099,6 +1129,10 @@ nmpc_status device_init(Problem& p, std::string& err) {
     DTRY(upload_c(A, I.kcol_ptr, sy.kcol_ptr));
     DTRY(upload_c(A, I.S.sched_nodes, nodes));
     DTRY(upload_c(A, I.S.fused, fused));
+    DTRY(upload_c(A, I.S.big_col, big_col));
+    DTRY(upload_c(A, I.S.big_ptr, big_ptr));
+    DTRY(upload_c(A, I.S.big_ent, big_ent));
+    DTRY(upload_c(A, I.S.chunk_pos, chunk_pos));
     DTRY(upload_c(A, I.k_wslot, sy.k_wslot));
     DTRY(upload_c(A, I.k_diag, sy.k_diag));
     DTRY(upload_c(A, I.kc_ptr, sy.kc_ptr));

@@ -66,6 +66,12 @@ struct SnView {
     const int32_t* k_fpos;
     const int32_t* sched_nodes;   // supernodes in launch-schedule order
     const int32_t* fused;         // 1: the Newton step's forward solve runs inside the factor kernel
+    // assembly of the large fronts: entries of column j of a front are [big_ptr
+    // [big_col[s] + j], big_ptr[big_col[s] + j + 1])
+    const int32_t* big_col;
+    const int32_t* big_ptr;
+    const struct BigEntry* big_ent;
+    const int32_t* chunk_pos;
 };
 
 // Phases of one Newton iteration of Algorithm 2 for one instance:
@@ -326,6 +332,16 @@ hipError_t linalg_configure(size_t max_lds_bytes);
 // ---- large supernodes (kernels_big.hip) ---------------------------------------------
 constexpr int kBigPanel = 64;   // pivot columns per panel step of a large front
 constexpr int kBigOuter = 512;  // columns per outer panel (one trailing update each)
+constexpr int kBigChunk = 1024; // rows of a column one wave assembles
+// One column of a child's update block among the columns a large front's column
+// takes up, in child order: where the child's column starts in U, the child's
+// row positions in rel (its update vector starts at the same offset of uvec),
+// the column's index in the child, the child's rows, and the place in
+// chunk_pos of the child's first row at or past every multiple of kBigChunk.
+struct BigEntry {
+    int64_t u_col, rel_off;
+    int32_t jc, nc, chunk, pad;
+};
 constexpr int kBigDiag = kBigPanel * kBigPanel + kBigPanel;   // doubles of a factored diagonal block kept aside
 // One workgroup's share of a step: the front's storage and sizes, then what the
 // kind below names (a, b).  slot: the front's place in the instance's dfac.
@@ -338,8 +354,7 @@ struct BigTask {
 };
 static_assert(sizeof(BigTask) == 64, "one scalar load of 16 words");
 enum BigKind : int {
-    kBigInit = 1,       // a: column
-    kBigExtend = 2,     // a: child position, b: child column
+    kBigAssemble = 1,   // a: first of kBigAsmCols columns, b: chunk of rows
     kBigPanelStep = 3,  // a: kb, b: row block
     kBigUpdate = 5,     // a: kb, b: lower-triangle tile; b < 0: keep the diagonal block of columns a
     kBigFwdTri = 6,     // a: chunk
@@ -353,6 +368,7 @@ enum BigKind : int {
 // which selects the solve vectors).
 void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs* I, const BigTask* tasks, int count,
                 size_t lds_bytes, hipStream_t st);
+constexpr int kBigAsmCols = 4;   // columns per workgroup of the assembly, one per wave
 int big_row_block();
 int big_tile();
 int big_solve_rows();

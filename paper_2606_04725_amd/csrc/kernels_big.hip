@@ -8,12 +8,11 @@
 // task list; every sum is taken in a fixed order, so results do not depend on
 // how tasks are scheduled.
 //
-// Factorization of one level: zero the fronts and scatter the KKT entries
-// (+ eta on the diagonal); add the children's update blocks, one child per
-// launch; then per outer panel of kBigOuter columns, per inner panel of
-// kBigPanel columns: factor the diagonal block (one workgroup per front), solve
-// the rows below it (rows split over workgroups), and update the rest of the
-// outer panel; then one rank-kBigOuter update of the trailing lower triangle.
+// Factorization of one level: assemble the fronts (KKT entries, + eta on the
+// diagonal, and the children's update blocks); then per outer panel of kBigOuter
+// columns, per inner panel of kBigPanel columns: factor the diagonal block and
+// solve the rows below it (rows split over workgroups), and update the rest of
+// the outer panel; then one rank-kBigOuter update of the trailing lower triangle.
 // Updates run on the matrix cores (64 x 64 tiles over workgroups, one
 // v_mfma_f64_16x16x4f64 per 4 columns); the outer panel keeps the update
 // blocks' read-modify-write traffic to one pass per kBigOuter columns.
@@ -40,7 +39,6 @@ constexpr int kSolveCols = 16;   // transposed-GEMV columns per workgroup
 constexpr int kTri = kWave * (kWave + 1);   // a staged 64 x 64 triangle, leading dimension 65
 constexpr int kStage = kWave * kWave / kBlock;   // entries of a 64 x 64 block staged per thread
 constexpr int kUpdateDepth = 8;  // 4-column steps of an update tile whose loads are in flight together
-constexpr int kExtendDepth = 4;  // child rows per thread whose loads are in flight together
 
 struct Front {
     double* L;     // panel, leading dimension m
@@ -71,66 +69,77 @@ __device__ inline double* fwd_entry(const InstPtrs& I, const Front& F, const Big
 }
 
 // ---- factorization ---------------------------------------------------------------
-// task (inst, s, j, -): zero column j of the front, then scatter the KKT slots
-// of column j (j < w), eta added on the diagonal.
-__global__ void __launch_bounds__(kBlock)
-k_big_init(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, double eta_force) {
+// Assembly, task a = first column, b = chunk q of kBigChunk rows: wave v builds
+// the chunk's part of column a + v in shared memory, the KKT slots of the column
+// (a < w; eta added on the diagonal), then the children's columns that land
+// there, in child order, through their relative row positions, and writes it
+// once.  A front is so written once and its children's blocks are read once;
+// zeroing it and adding each child in a launch of its own wrote it once more and
+// read and wrote it again per child (32 x 32 x 50 plate: 1.07 ms per
+// factorization for the two kernels).  One wave per column keeps 20 columns in
+// flight per CU without a barrier; a wave's shared-memory operations complete in
+// the order issued.
+constexpr int kAsmDepth = 8;   // child rows per lane whose loads are in flight together
+template <class T>
+__device__ __attribute__((always_inline)) inline T uniform_at(const T* p, int64_t k) {   // read-only data, a scalar load
+    return ((const __attribute__((address_space(4))) T*)p)[k];
+}
+__global__ void __launch_bounds__(kBigAsmCols * kWave)
+k_big_assemble(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, double eta_force) {
+    __shared__ double cols[kBigAsmCols][kBigChunk];
     const BigTask tk = tasks[blockIdx.x];
     const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
     const double eta = pred == kPredAll ? eta_force : I.ctl->eta;
     const Front F = front_of(tk);
-    const int j = tk.a;
-    if (threadIdx.x == 0 && fwd_fused(tk, pred)) *fwd_entry(I, F, tk, j) = j < F.w ? I.rhs[I.perm[F.f + j]] : 0.0;
-    for (int i = j + threadIdx.x; i < F.m; i += blockDim.x) *at(F, i, j) = 0.0;
-    if (j >= F.w) return;
-    __syncthreads();
-    const int ld = F.m | 1;
-    const int col = F.f + j;
-    for (int t = I.kcol_ptr[col] + threadIdx.x; t < I.kcol_ptr[col + 1]; t += blockDim.x) {
-        const int r = I.S.k_fpos[t] % ld;
-        double v = I.kv[t];
-        if (r == j) v += eta;
-        F.L[r + (int64_t)j * F.m] = v;
-    }
-}
-
-// task (inst, s, child position, child column jc): add column jc of the child's
-// update block into the front through the child's relative row positions.
-__global__ void __launch_bounds__(kBlock)
-k_big_extend(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
-    const BigTask tk = tasks[blockIdx.x];
-    const InstPtrs& I = Ia[tk.inst];
-    if (!ctl_active(I.ctl, pred)) return;
-    const Front F = front_of(tk);
-    const int c = I.S.child_list[I.S.child_ptr[tk.sn] + tk.a];
-    const int wc = I.S.sn_ptr[c + 1] - I.S.sn_ptr[c];
-    const int nc = (int)(I.S.rows_ptr[c + 1] - I.S.rows_ptr[c]) - wc;
-    const double* Uc = I.U + I.S.u_off[c];
-    const int32_t* rel = I.S.rel + I.S.rel_off[c];
-    const int jc = tk.b;
-    const int rj = rel[jc];
-    if (threadIdx.x == 0 && fwd_fused(tk, pred)) *fwd_entry(I, F, tk, rj) += I.uvec[I.S.uv_off[c] + jc];
-    const auto* uc = global(Uc) + (int64_t)jc * nc;
-    const auto* rg = global(rel);
-    // kExtendDepth rows per thread at a time: their loads are issued together
-    // (distinct rows of the child land on distinct entries of the front)
-    for (int ic0 = jc + threadIdx.x; ic0 < nc; ic0 += kExtendDepth * kBlock) {
-        int rr[kExtendDepth];
-        double uv[kExtendDepth], tv[kExtendDepth];
-#pragma unroll
-        for (int u = 0; u < kExtendDepth; ++u) {
-            const int ic = ic0 + u * kBlock;
-            rr[u] = ic < nc ? rg[ic] : 0;
-            uv[u] = ic < nc ? uc[ic] : 0.0;
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int j = tk.a + wv;
+    if (j >= F.m) return;
+    const int base = tk.b * kBigChunk, r0 = max(base, j), r1 = min(F.m, base + kBigChunk);   // the chunk's rows
+    if (r0 >= r1) return;
+    double* col = cols[wv];   // row r at col[r - base]
+    const int ce = uniform_at(I.S.big_col, tk.sn) + j;
+    const int e0 = uniform_at(I.S.big_ptr, ce), e1 = uniform_at(I.S.big_ptr, ce + 1);
+    const bool fw = fwd_fused(tk, pred) && j >= base;   // the chunk that holds the column's own row
+    double fv = fw && j < F.w ? global(I.rhs)[uniform_at(I.perm, F.f + j)] : 0.0;
+    for (int r = r0 + lane; r < r1; r += kWave) col[r - base] = 0.0;
+    if (j < F.w) {
+        const int t1 = uniform_at(I.kcol_ptr, F.f + j + 1);
+        for (int t = uniform_at(I.kcol_ptr, F.f + j) + lane; t < t1; t += kWave) {
+            const int r = global(I.S.k_fpos)[t];
+            double v = global(I.kv)[t];
+            if (r == j) v += eta;
+            if (r >= r0 && r < r1) col[r - base] = v;
         }
-#pragma unroll
-        for (int u = 0; u < kExtendDepth; ++u)
-            tv[u] = ic0 + u * kBlock < nc ? *global(at(F, rr[u], rj)) : 0.0;
-#pragma unroll
-        for (int u = 0; u < kExtendDepth; ++u)
-            if (ic0 + u * kBlock < nc) *global(at(F, rr[u], rj)) = tv[u] + uv[u];
     }
+    for (int e = e0; e < e1; ++e) {
+        const int64_t u_col = uniform_at(&I.S.big_ent->u_col, (int64_t)e * (sizeof(BigEntry) / sizeof(int64_t)));
+        const int64_t rel_off = uniform_at(&I.S.big_ent->rel_off, (int64_t)e * (sizeof(BigEntry) / sizeof(int64_t)));
+        const int jc = uniform_at(&I.S.big_ent->jc, (int64_t)e * (sizeof(BigEntry) / sizeof(int32_t)));
+        const int nc = uniform_at(&I.S.big_ent->nc, (int64_t)e * (sizeof(BigEntry) / sizeof(int32_t)));
+        const int ck = uniform_at(&I.S.big_ent->chunk, (int64_t)e * (sizeof(BigEntry) / sizeof(int32_t)));
+        if (fw) fv += global(I.uvec)[rel_off + jc];
+        const int i0 = max(jc, base > 0 ? uniform_at(I.S.chunk_pos, ck + tk.b) : 0);
+        const int i1 = F.m > base + kBigChunk ? uniform_at(I.S.chunk_pos, ck + tk.b + 1) : nc;
+        const auto* rg = global(I.S.rel) + rel_off;
+        const auto* uc = global(I.U) + u_col;
+        for (int ib = i0 + lane; ib < i1; ib += kAsmDepth * kWave) {
+            int rr[kAsmDepth];
+            double uv[kAsmDepth];
+#pragma unroll
+            for (int u = 0; u < kAsmDepth; ++u) {
+                const int i = min(ib + u * kWave, i1 - 1);
+                rr[u] = rg[i];
+                uv[u] = uc[i];
+            }
+#pragma unroll
+            for (int u = 0; u < kAsmDepth; ++u)
+                if (ib + u * kWave < i1) col[rr[u] - base] += uv[u];
+        }
+    }
+    gdouble* dst = global(at(F, j, j)) - j;   // entry (r, j) at dst[r]
+    for (int r = r0 + lane; r < r1; r += kWave) dst[r] = col[r - base];
+    if (fw && lane == 0) *fwd_entry(I, F, tk, j) = fv;
 }
 
 // One panel of a front: task a = kb, b = row block.  Every workgroup factors the
@@ -666,11 +675,8 @@ void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs*
                 size_t lds_bytes, hipStream_t st) {
     if (count <= 0) return;
     switch (kind) {
-        case kBigInit:
-            hipLaunchKernelGGL(k_big_init, dim3(count), dim3(kBlock), 0, st, I, tasks, pred, eta_force);
-            break;
-        case kBigExtend:
-            hipLaunchKernelGGL(k_big_extend, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);
+        case kBigAssemble:
+            hipLaunchKernelGGL(k_big_assemble, dim3(count), dim3(kBigAsmCols * kWave), 0, st, I, tasks, pred, eta_force);
             break;
         case kBigPanelStep:
             hipLaunchKernelGGL(k_big_panel, dim3(count), dim3(kPanelThreads), 0, st, I, tasks, pred);
