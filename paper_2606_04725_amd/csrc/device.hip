@@ -946,6 +946,16 @@ nmpc_status device_init(Problem& p, std::string& err) {
         big_factor_steps(bigs);
         if (!gs.groups.empty()) D.fwd.push_back(gs);
         if (!gr.groups.empty()) D.fwd_rest.push_back(gr);
+        {
+            std::vector<int4> ga, ga_rest;
+            for (int32_t sn : bsol)
+                for (int rb = 0; rb < ceil_div(rows_of(sn), big_gather_rows()); ++rb) {
+                    ga.push_back(int4{0, sn, rb, 0});
+                    if (!fused[sn]) ga_rest.push_back(ga.back());
+                }
+            push(D.fwd_rest, kBigFwdGather, std::move(ga_rest));
+            push(D.fwd, kBigFwdGather, std::move(ga));
+        }
         int64_t nch = 0;
         for (int32_t sn : bsol) nch = std::max<int64_t>(nch, ceil_div(width_of(sn), CH));
         for (int c = 0; c < nch; ++c) {
@@ -1040,20 +1050,21 @@ nmpc_status device_init(Problem& p, std::string& err) {
             k_fpos[t] = big_fac[sn] ? (int32_t)r : (r == c ? ~(int32_t)q : (int32_t)q);
         }
     }
-    // the child columns that land in each column of a large front, in child order
+    // the child columns that land in each column of a large front (or a
+    // supernode whose solves are large), in child order
     std::vector<int32_t> big_col(std::max(nsn, 1), 0), big_ptr, chunk_pos;
     std::vector<BigEntry> big_ent;
     {
         int64_t cols = 0;
         for (int sn = 0; sn < nsn; ++sn)
-            if (big_fac[sn]) {
+            if (big_fac[sn] || big_sol[sn]) {
                 big_col[sn] = (int32_t)cols;
                 cols += rows_of(sn);
             }
         big_ptr.assign((size_t)cols + 1, 0);
         auto each = [&](auto&& fn) {   // fn(column of the front in big_ptr, child, column of the child)
             for (int sn = 0; sn < nsn; ++sn) {
-                if (!big_fac[sn]) continue;
+                if (!big_fac[sn] && !big_sol[sn]) continue;
                 for (int ci = sy.child_ptr[sn]; ci < sy.child_ptr[sn + 1]; ++ci) {
                     const int c = sy.child_list[ci];
                     const int nc = (int)(rows_of(c) - width_of(c));
@@ -1065,7 +1076,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
         for (size_t j = 0; j + 1 < big_ptr.size(); ++j) big_ptr[j + 1] += big_ptr[j];
         std::vector<int32_t> fill(big_ptr.begin(), big_ptr.end() - 1), first(std::max(nsn, 1), -1);
         for (int sn = 0; sn < nsn; ++sn) {   // where a child's rows pass the chunks of its (large) parent
-            if (!big_fac[sn]) continue;
+            if (!big_fac[sn] && !big_sol[sn]) continue;
             for (int ci = sy.child_ptr[sn]; ci < sy.child_ptr[sn + 1]; ++ci) {
                 const int c = sy.child_list[ci];
                 const auto rb = sy.rel.begin() + sy.rel_off[c], re = rb + (rows_of(c) - width_of(c));

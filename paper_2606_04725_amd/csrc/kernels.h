@@ -66,8 +66,8 @@ struct SnView {
     const int32_t* k_fpos;
     const int32_t* sched_nodes;   // supernodes in launch-schedule order
     const int32_t* fused;         // 1: the Newton step's forward solve runs inside the factor kernel
-    // assembly of the large fronts: entries of column j of a front are [big_ptr
-    // [big_col[s] + j], big_ptr[big_col[s] + j + 1])
+    // children of the large supernodes (factorization or solves): entries of row
+    // and column j are [big_ptr[big_col[s] + j], big_ptr[big_col[s] + j + 1])
     const int32_t* big_col;
     const int32_t* big_ptr;
     const struct BigEntry* big_ent;
@@ -357,6 +357,7 @@ enum BigKind : int {
     kBigAssemble = 1,   // a: first of kBigAsmCols columns, b: chunk of rows
     kBigPanelStep = 3,  // a: kb, b: row block
     kBigUpdate = 5,     // a: kb, b: lower-triangle tile; b < 0: keep the diagonal block of columns a
+    kBigFwdGather = 2,  // a: row block
     kBigFwdTri = 6,     // a: chunk
     kBigFwdGemv = 7,    // a: chunk, b: row block
     kBigBwdBelow = 8,   // a: column block
@@ -370,6 +371,7 @@ void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs*
                 size_t lds_bytes, hipStream_t st);
 constexpr int kBigAsmCols = 4;   // columns per workgroup of the assembly, one per wave
 int big_row_block();
+int big_gather_rows();   // rows per workgroup of the forward gather
 int big_tile();
 int big_solve_rows();
 int big_solve_cols();

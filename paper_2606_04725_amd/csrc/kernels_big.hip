@@ -34,7 +34,7 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kRowBlock = kBlock / 4;   // TRSM rows per workgroup (four lanes per row)
 constexpr int kTile = 64;        // trailing-update tile
-constexpr int kSolveRows = 256;  // GEMV rows per workgroup
+constexpr int kSolveRows = 64;   // GEMV rows per workgroup
 constexpr int kSolveCols = 16;   // transposed-GEMV columns per workgroup
 constexpr int kTri = kWave * (kWave + 1);   // a staged 64 x 64 triangle, leading dimension 65
 constexpr int kStage = kWave * kWave / kBlock;   // entries of a 64 x 64 block staged per thread
@@ -429,48 +429,103 @@ k_big_update(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks,
 }
 
 // ---- solves ------------------------------------------------------------------------
-// The columns of a large supernode are solved kChunk at a time.  Forward: one
-// workgroup solves the chunk's triangle (the first chunk also gathers the
-// right-hand side over the supernode's columns into xp and the rows below into
-// its update vector, adding the children's update vectors), then the rows after
-// the chunk (the rest of the diagonal part and the rows below) take the chunk's
-// GEMV, split over workgroups.  Backward, from the last chunk: the rows below
-// contribute L[w:m, k]^T x(rows below) to bsum (transposed GEMV), each chunk's
-// triangle is solved by one workgroup, then the columns before the chunk take
-// its transposed GEMV into bsum.  Sums over chunks run in a fixed order.
+// The columns of a large supernode are solved kChunk at a time.  Forward: the
+// right-hand side over the supernode's columns goes into xp and the rows below
+// into its update vector, each with the children's update vectors, a row per
+// thread over many workgroups; then per chunk one workgroup solves its triangle
+// and the rows after it (the rest of the diagonal part and the rows below) take
+// the chunk's GEMV, split over workgroups.  Backward, from the last chunk: the
+// rows below contribute L[w:m, k]^T x(rows below) to bsum (transposed GEMV),
+// each chunk's triangle is solved by one workgroup, then the columns before the
+// chunk take its transposed GEMV into bsum.  Sums run in a fixed order.
 constexpr int kChunk = 256;
 
-// Stage the lower triangle of the diagonal block [b0, b0 + bw)^2 of L in T
-// (leading dimension kWave + 1) and the reciprocals of its diagonal in rd (1
-// past bw); every load of a thread is issued before the first store.  The
-// caller synchronizes.
-__device__ inline void stage_triangle(const Front& F, int b0, int bw, double* T, double* rd) {
-    double t[kStage];
+// Lower triangle of the diagonal block [b0, b0 + bw)^2 of L into registers (16
+// entries per thread, loads only, from clamped addresses) ...
+__device__ __attribute__((always_inline)) inline void load_triangle(const Front& F, int b0, int bw, double (&t)[kStage]) {
 #pragma unroll
     for (int s = 0; s < kStage; ++s) {
-        const int e = threadIdx.x + s * kBlock, i = e % kWave, j = e / kWave;
-        t[s] = (i < bw && j <= i) ? global(F.L)[(b0 + i) + (int64_t)(b0 + j) * F.m] : 0.0;
-    }
-#pragma unroll
-    for (int s = 0; s < kStage; ++s) {
-        const int e = threadIdx.x + s * kBlock, i = e % kWave, j = e / kWave;
-        if (j <= i) T[i + j * (kWave + 1)] = t[s];
-        if (i == j) rd[i] = i < bw ? 1.0 / t[s] : 1.0;
+        const int e = threadIdx.x + s * kBlock, i = min(e % kWave, bw - 1), j = min(e / kWave, i);
+        t[s] = global(F.L)[(b0 + i) + (int64_t)(b0 + j) * F.m];
     }
 }
 
-// Value of v in lane k of the wave, in every lane (k wave-uniform).
-__device__ inline double lane_value(double v, int k) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), k);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), k);
-    return __hiloint2double(hi, lo);
+// ... and from there to T (leading dimension kWave + 1), zero on and above the
+// diagonal and past bw, with the reciprocals of the diagonal in rd (1 past bw):
+// a wave holds every fourth column, so each lane finds its diagonal entry in one
+// of the four waves and a wave divides once.  The caller synchronizes.
+__device__ __attribute__((always_inline)) inline void store_triangle(const double (&t)[kStage], int bw, double* T, double* rd) {
+    const int i = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    static_assert(kBlock == 4 * kWave, "four columns per step");
+    double d = 1.0;
+#pragma unroll
+    for (int s = 0; s < kStage; ++s) {
+        const int j = wv + 4 * s;
+        T[i + j * (kWave + 1)] = j < i && i < bw ? t[s] : 0.0;
+        d = j == i ? t[s] : d;
+    }
+    if ((i & 3) == wv) rd[i] = i < bw ? 1.0 / d : 1.0;
 }
 
-// forward, task (inst, s, chunk c): x[c0, c1) = L[c0:c1, c0:c1]^{-1} v[c0, c1)
-// in xp, by blocks of 64 columns (the block's triangle staged in shared memory,
-// wave 0 solves it, then the chunk's later rows take the block's update).
+// Solve with the staged triangle (or, Back, its transpose) on one wave: lane j
+// holds v_j and its reciprocal, x_k leaves lane k through the scalar unit.  The
+// coefficients of 16 steps are read from shared memory before the steps, and
+// are zero for the lanes a step does not touch, so a step is a product, two
+// lane reads and one multiply-add (about 30 cycles; with the coefficients read
+// and selected in each step it was 100).
+template <bool Back>
+__device__ __attribute__((always_inline)) inline double solve_triangle(double vj, const double* T, const double* rd, int bw) {
+    const int j = threadIdx.x & (kWave - 1);
+    const double r = rd[j];
+    for (int g = 0; g < kWave; g += 16) {
+        const int k0 = Back ? kWave - 16 - g : g;   // the group's first column
+        if (k0 >= bw) continue;
+        double c[16];
+        const double* col = T + (Back ? k0 + j * (kWave + 1) : j + k0 * (kWave + 1));
+#pragma unroll
+        for (int u = 0; u < 16; ++u) c[u] = col[Back ? u : u * (kWave + 1)];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int q = Back ? 15 - u : u;
+            const double y = vj * r;
+            const int lo = __builtin_amdgcn_readlane(__double2loint(y), k0 + q);
+            const int hi = __builtin_amdgcn_readlane(__double2hiint(y), k0 + q);
+            vj = fma(-c[q], __hiloint2double(hi, lo), vj);
+        }
+    }
+    return vj * r;
+}
+
+// forward, task a = row block: a row i of the front per thread, its right-hand
+// side (i < w) and the children's update vectors in child order, into xp (i < w)
+// or the update vector.
 __global__ void __launch_bounds__(kBlock)
-k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, int which) {
+k_bigfwd_gather(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, int which) {
+    const BigTask tk = tasks[blockIdx.x];
+    const InstPtrs& I = Ia[tk.inst];
+    if (!ctl_active(I.ctl, pred)) return;
+    const Front F = front_of(tk);
+    const int i = tk.a * kBlock + threadIdx.x;
+    if (i >= F.m) return;
+    const int ce = uniform_at(I.S.big_col, tk.sn) + i;
+    const int e0 = global(I.S.big_ptr)[ce], e1 = global(I.S.big_ptr)[ce + 1];
+    double v = i < F.w ? global(solve_in(I, which))[global(I.perm)[F.f + i]] : 0.0;
+    for (int e = e0; e < e1; ++e) {
+        const auto* en = global(I.S.big_ent) + e;
+        v += global(I.uvec)[en->rel_off + en->jc];
+    }
+    *fwd_entry(I, F, tk, i) = v;
+}
+
+// forward, task a = chunk: x[c0, c1) = L[c0:c1, c0:c1]^{-1} v[c0, c1) in xp, by
+// blocks of 64 columns: the block's triangle staged in shared memory, wave 0
+// solves it while the other waves load the entries of the chunk's later rows,
+// one per thread, which then take the block's update.  The next block's triangle
+// is loaded ahead (Cholesky of the 28 x 37 plate: 48 us per launch with the loads
+// after the solve and a division per column).
+__global__ void __launch_bounds__(kBlock)
+k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
+    static_assert(kChunk == kBlock, "a row per thread past the first wave");
     __shared__ double T[kTri];
     __shared__ double rd[kWave];
     __shared__ double v[kChunk];
@@ -478,167 +533,204 @@ k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks,
     const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
     const Front F = front_of(tk);
-    const int s = tk.sn, tid = threadIdx.x, nthr = blockDim.x;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     double* xs = I.xp + F.f;
-    if (tk.a == 0) {
-        const double* rhs = solve_in(I, which);
-        double* us = I.uvec + tk.uv;
-        for (int k = tid; k < F.w; k += nthr) xs[k] = rhs[I.perm[F.f + k]];
-        for (int i = tid; i < F.m - F.w; i += nthr) us[i] = 0.0;
-        __syncthreads();
-        for (int ci = I.S.child_ptr[s]; ci < I.S.child_ptr[s + 1]; ++ci) {
-            const int c = I.S.child_list[ci];
-            const int nc = (int)(I.S.uv_off[c + 1] - I.S.uv_off[c]);
-            const double* uc = I.uvec + I.S.uv_off[c];
-            const int32_t* rc = I.S.rel + I.S.rel_off[c];
-            for (int i = tid; i < nc; i += nthr) {
-                const int p = rc[i];
-                if (p < F.w) xs[p] += uc[i];
-                else us[p - F.w] += uc[i];
-            }
-            __syncthreads();
-        }
-    }
     const int c0 = tk.a * kChunk, cw = min(kChunk, F.w - c0);
-    for (int k = tid; k < cw; k += nthr) v[k] = xs[c0 + k];
+    double t[kStage];
+    load_triangle(F, c0, min(kWave, cw), t);
+    if (tid < cw) v[tid] = global(xs)[c0 + tid];
     for (int b0 = 0; b0 < cw; b0 += kWave) {
         const int bw = min(kWave, cw - b0), b1 = b0 + bw;
-        stage_triangle(F, c0 + b0, bw, T, rd);
+        store_triangle(t, bw, T, rd);
         __syncthreads();
-        if (tid < kWave) {
-            // lane j holds v_j; x_k leaves lane k through the scalar unit.  Lanes
-            // j >= bw carry zeros (rd = 1 there, their entries of T are unused).
-            const int j = tid;
-            double vj = j < bw ? v[b0 + j] : 0.0;
+        if (b1 < cw) load_triangle(F, c0 + b1, min(kWave, cw - b1), t);
+        if (wv == 0) {
+            const double x = solve_triangle<false>(tid < bw ? v[b0 + tid] : 0.0, T, rd, bw);
+            if (tid < bw) v[b0 + tid] = x;
+            __syncthreads();
+        } else {
+            const int i = b0 + tid;   // the thread's row; past cw there is none
+            double l[kWave];
+            if (b1 < cw) {   // then bw == kWave
+                const gdouble* li = global(F.L) + (c0 + min(i, cw - 1)) + (int64_t)(c0 + b0) * F.m;
 #pragma unroll
-            for (int k = 0; k < kWave; ++k) {
-                const double xk = lane_value(vj, k) * rd[k];
-                const double upd = fma(-T[j + k * (kWave + 1)], xk, vj);
-                vj = j == k ? xk : (j > k && j < bw ? upd : vj);
+                for (int k = 0; k < kWave; ++k) l[k] = li[(int64_t)k * F.m];
             }
-            if (j < bw) v[b0 + j] = vj;
-        }
-        __syncthreads();
-        for (int i = b1 + tid; i < cw; i += nthr) {
-            const gdouble* li = global(F.L) + (c0 + i) + (int64_t)(c0 + b0) * F.m;
-            double acc = v[i];
-            if (bw == kWave) {
-#pragma unroll 32
-                for (int k = 0; k < kWave; ++k) acc = fma(-li[(int64_t)k * F.m], v[b0 + k], acc);
-            } else {
-                for (int k = 0; k < bw; ++k) acc = fma(-li[(int64_t)k * F.m], v[b0 + k], acc);
+            __syncthreads();
+            if (i < cw && b1 < cw) {
+                double acc = v[i];
+#pragma unroll
+                for (int k = 0; k < kWave; ++k) acc = fma(-l[k], v[b0 + k], acc);
+                v[i] = acc;
             }
-            v[i] = acc;
         }
         __syncthreads();
     }
-    for (int k = tid; k < cw; k += nthr) xs[c0 + k] = v[k];
+    if (tid < cw) xs[c0 + tid] = v[tid];
 }
 
-// forward, task (inst, s, chunk c, row block): rows i >= c1 of the block (one
-// per thread): v[i] -= L[i, c0:c1) x[c0, c1), in xp (i < w) or in the update
-// vector (i >= w).
+// forward, task a = chunk, b = row block: 64 rows i >= c1, v[i] -= L[i, c0:c1)
+// x[c0, c1), in xp (i < w) or in the update vector (i >= w); a row per lane, a
+// quarter of the chunk's columns per wave, the quarters added in order (a row
+// per thread over the whole chunk left most of the chip idle: 10.5 us per launch).
 __global__ void __launch_bounds__(kBlock)
 k_bigfwd_gemv(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
+    static_assert(kSolveRows == kWave && kChunk % (kBlock / kWave) == 0, "a row per lane, equal shares of the columns");
+    constexpr int kPart = kChunk / (kBlock / kWave);
     __shared__ double x[kChunk];
+    __shared__ double sum[kBlock / kWave][kWave];
     const BigTask tk = tasks[blockIdx.x];
     const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
     const Front F = front_of(tk);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int c0 = tk.a * kChunk, cw = min(kChunk, F.w - c0), c1 = c0 + cw;
-    for (int k = threadIdx.x; k < cw; k += blockDim.x) x[k] = I.xp[F.f + c0 + k];
+    const int i = c1 + tk.b * kSolveRows + lane;
+    const gdouble* Li = global(F.L) + min(i, F.m - 1) + (int64_t)c0 * F.m;
+    double* out = fwd_entry(I, F, tk, min(i, F.m - 1));
+    const double xv = tid < cw ? global(I.xp)[F.f + c0 + tid] : 0.0;
+    const double old = wv == 0 ? *global(out) : 0.0;
+    double l[kPart];
+#pragma unroll
+    for (int k = 0; k < kPart; ++k) l[k] = Li[(int64_t)min(kPart * wv + k, cw - 1) * F.m];
+    x[tid] = xv;
     __syncthreads();
-    const int i = c1 + tk.b * kSolveRows + threadIdx.x;
-    if (i >= F.m) return;
-    const gdouble* Li = global(F.L) + i + (int64_t)c0 * F.m;
     double acc = 0.0;
-#pragma unroll 16
-    for (int k = 0; k < cw; ++k) acc = fma(Li[(int64_t)k * F.m], x[k], acc);
-    if (i < F.w) I.xp[F.f + i] -= acc;
-    else I.uvec[tk.uv + (i - F.w)] -= acc;
+#pragma unroll
+    for (int k = 0; k < kPart; ++k) acc = fma(l[k], x[kPart * wv + k], acc);
+    sum[wv][lane] = acc;
+    __syncthreads();
+    if (wv == 0 && i < F.m) *global(out) = old - (((sum[0][lane] + sum[1][lane]) + sum[2][lane]) + sum[3][lane]);
 }
 
-// backward, task (inst, s, column block): bsum[f + k] = L[w:m, k]^T x(rows below)
-// for the block's columns; wave v takes columns k0 + v, k0 + v + 4, ..., lanes
-// walk the rows (a butterfly sums the lanes).
+// backward, task a = column block: bsum[f + k] = L[w:m, k]^T x(rows below) for the
+// block's kSolveCols columns: the rows' solution is gathered into shared memory
+// once (kBelow rows at a time), then wave v takes columns k0 + v, k0 + v + 4,
+// ..., all at once, lanes over the rows (a butterfly sums the lanes).  Gathered
+// per column it took 18 us per launch (32 x 32 x 50 plate).
+constexpr int kBelow = 2048;
 __global__ void __launch_bounds__(kBlock)
 k_bigbwd_below(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
+    constexpr int kPer = kSolveCols / (kBlock / kWave);   // columns per wave
+    __shared__ double x[kBelow];
     const BigTask tk = tasks[blockIdx.x];
     const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
     const Front F = front_of(tk);
-    const int32_t* rows = I.S.rows + I.S.rows_ptr[tk.sn];
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    const int32_t* rows = I.S.rows + uniform_at(I.S.rows_ptr, tk.sn);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, nw = kBlock / kWave;
     const int k0 = tk.a * kSolveCols;
-    for (int k = k0 + wv; k < min(F.w, k0 + kSolveCols); k += nw) {
-        double acc = 0.0;
-#pragma unroll 4
-        for (int i = F.w + lane; i < F.m; i += kWave) acc = fma(global(F.L)[i + (int64_t)k * F.m], global(I.xp)[rows[i]], acc);
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-        if (lane == 0) I.bsum[F.f + k] = acc;
+    const gdouble* col[kPer];
+    double acc[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        col[q] = global(F.L) + (int64_t)min(k0 + wv + q * nw, F.w - 1) * F.m;
+        acc[q] = 0.0;
     }
+    for (int base = F.w; base < F.m; base += kBelow) {
+        const int len = min(kBelow, F.m - base);
+        if (base > F.w) __syncthreads();
+        {
+            int at[kBelow / kBlock];
+            double g[kBelow / kBlock];
+#pragma unroll
+            for (int u = 0; u < kBelow / kBlock; ++u) at[u] = global(rows)[base + min(tid + u * kBlock, len - 1)];
+#pragma unroll
+            for (int u = 0; u < kBelow / kBlock; ++u) g[u] = global(I.xp)[at[u]];
+#pragma unroll
+            for (int u = 0; u < kBelow / kBlock; ++u) x[tid + u * kBlock] = g[u];
+        }
+        __syncthreads();
+        constexpr int kDepth = 4;   // rows per lane whose loads are in flight together
+        for (int i0 = lane; i0 < len; i0 += kDepth * kWave) {
+            double l[kDepth][kPer];
+#pragma unroll
+            for (int u = 0; u < kDepth; ++u)
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) l[u][q] = col[q][base + min(i0 + u * kWave, len - 1)];
+#pragma unroll
+            for (int u = 0; u < kDepth; ++u)
+                if (i0 + u * kWave < len) {
+                    const double xv = x[i0 + u * kWave];
+#pragma unroll
+                    for (int q = 0; q < kPer; ++q) acc[q] = fma(l[u][q], xv, acc[q]);
+                }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) acc[q] += __shfl_xor(acc[q], off, kWave);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (lane == 0 && k0 + wv + q * nw < F.w) I.bsum[F.f + k0 + wv + q * nw] = acc[q];
 }
 
 // Whether bsum of a chunk's columns holds contributions: rows below the
 // supernode, or a later chunk.
 __device__ inline bool bsum_live(const Front& F, int c) { return F.m > F.w || (c + 1) * kChunk < F.w; }
 
-// backward, task (inst, s, chunk c): v = xp[c0, c1) - bsum; solve
-// L[c0:c1, c0:c1]^T x = v by blocks of 64 from the last (the block's triangle
-// staged in shared memory, wave 0 solves it, then the chunk's earlier columns
-// take the block's rows of L); writes xp and the unpermuted solution.
+// backward, task a = chunk: v = xp[c0, c1) - bsum; solve L[c0:c1, c0:c1]^T x = v
+// by blocks of 64 from the last: wave 0 solves the block's staged triangle while
+// the other waves bring its rows of the chunk's earlier columns into shared
+// memory (coalesced), from where a thread per column takes the update.  With each
+// thread reading its own column, 64 cache lines per load, a launch took 26 us
+// (32 x 32 x 50 plate).  Writes xp and the unpermuted solution.
 __global__ void __launch_bounds__(kBlock)
 k_bigbwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, int which) {
+    constexpr int kWaves = kBlock / kWave - 1;   // that load
     __shared__ double T[kTri];
+    __shared__ double O[(kChunk - kWave) * (kWave + 1)];   // O[i + j (kWave + 1)] = L[b0 + i, j]
     __shared__ double rd[kWave];
     __shared__ double v[kChunk];
     const BigTask tk = tasks[blockIdx.x];
     const InstPtrs& I = Ia[tk.inst];
     if (!ctl_active(I.ctl, pred)) return;
     const Front F = front_of(tk);
-    const int tid = threadIdx.x, nthr = blockDim.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int c0 = tk.a * kChunk, cw = min(kChunk, F.w - c0);
     const bool live = bsum_live(F, tk.a);
-    for (int k = tid; k < cw; k += nthr) v[k] = I.xp[F.f + c0 + k] - (live ? I.bsum[F.f + c0 + k] : 0.0);
     const int nblk = (cw + kWave - 1) / kWave;
+    double t[kStage];
+    load_triangle(F, c0 + (nblk - 1) * kWave, cw - (nblk - 1) * kWave, t);
+    const int pk = tid < cw ? global(I.perm)[F.f + c0 + tid] : 0;
+    if (tid < cw) v[tid] = global(I.xp)[F.f + c0 + tid] - (live ? global(I.bsum)[F.f + c0 + tid] : 0.0);
     for (int bi = nblk - 1; bi >= 0; --bi) {
         const int b0 = bi * kWave, bw = min(kWave, cw - b0);
-        stage_triangle(F, c0 + b0, bw, T, rd);
+        store_triangle(t, bw, T, rd);
         __syncthreads();
-        if (tid < kWave) {
-            // lane j holds v_j; rows k >= bw are skipped (x_k of a zero lane is 0)
-            const int j = tid;
-            double vj = j < bw ? v[b0 + j] : 0.0;
+        if (bi > 0) load_triangle(F, c0 + b0 - kWave, kWave, t);
+        if (wv == 0) {
+            const double x = solve_triangle<true>(tid < bw ? v[b0 + tid] : 0.0, T, rd, bw);
+            v[b0 + tid] = tid < bw ? x : 0.0;
+        } else if (bi > 0) {
+            // columns wv - 1, wv - 1 + 3, ... < b0, 32 loads in flight
+            const gdouble* li = global(F.L) + (c0 + b0 + min(lane, bw - 1)) + (int64_t)c0 * F.m;
+            for (int j0 = wv - 1; j0 < b0; j0 += 32 * kWaves) {
+                double l[32];
 #pragma unroll
-            for (int k = kWave - 1; k >= 0; --k) {
-                const double xk = lane_value(vj, k) * rd[k];
-                const double upd = fma(-T[k + j * (kWave + 1)], xk, vj);
-                vj = j == k ? xk : (j < k && k < bw ? upd : vj);
+                for (int u = 0; u < 32; ++u) l[u] = li[(int64_t)min(j0 + u * kWaves, b0 - 1) * F.m];
+#pragma unroll
+                for (int u = 0; u < 32; ++u) O[lane + min(j0 + u * kWaves, b0 - 1) * (kWave + 1)] = lane < bw ? l[u] : 0.0;
             }
-            if (j < bw) v[b0 + j] = vj;
         }
         __syncthreads();
-        for (int c = tid; c < b0; c += nthr) {
-            double acc = v[c];
-            const gdouble* lc = global(F.L) + (int64_t)(c0 + c) * F.m + c0 + b0;
-            if (bw == kWave) {
-#pragma unroll 32
-                for (int i = 0; i < kWave; ++i) acc = fma(-lc[i], v[b0 + i], acc);
-            } else {
-                for (int i = 0; i < bw; ++i) acc = fma(-lc[i], v[b0 + i], acc);
-            }
-            v[c] = acc;
+        if (tid < b0) {
+            double acc = v[tid];
+            const double* o = O + tid * (kWave + 1);
+#pragma unroll
+            for (int i = 0; i < kWave; ++i) acc = fma(-o[i], v[b0 + i], acc);
+            v[tid] = acc;
         }
         __syncthreads();
     }
-    double* out = solve_out(I, which);
-    for (int k = tid; k < cw; k += nthr) {
-        I.xp[F.f + c0 + k] = v[k];
-        out[I.perm[F.f + c0 + k]] = v[k];
+    if (tid < cw) {
+        global(I.xp)[F.f + c0 + tid] = v[tid];
+        global(solve_out(I, which))[pk] = v[tid];
     }
 }
 
-// backward, task (inst, s, chunk c, column block): for the block's columns
+// backward, task a = chunk, b = column block: for the block's columns
 // k < c0, bsum[f + k] (+)= L[c0:c1, k]^T x[c0, c1) (the first contribution of a
 // supernode without rows below sets it); wave per column, lanes over the rows.
 __global__ void __launch_bounds__(kBlock)
@@ -666,6 +758,7 @@ k_bigbwd_gemvt(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ task
 }  // namespace
 
 int big_row_block() { return kRowBlock; }
+int big_gather_rows() { return kBlock; }
 int big_tile() { return kTile; }
 int big_solve_rows() { return kSolveRows; }
 int big_solve_cols() { return kSolveCols; }
@@ -687,8 +780,11 @@ void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs*
         case kBigUpdateInner:
             hipLaunchKernelGGL(k_big_update<true>, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);
             break;
+        case kBigFwdGather:
+            hipLaunchKernelGGL(k_bigfwd_gather, dim3(count), dim3(kBlock), 0, st, I, tasks, pred, which);
+            break;
         case kBigFwdTri:
-            hipLaunchKernelGGL(k_bigfwd_tri, dim3(count), dim3(kBlock), 0, st, I, tasks, pred, which);
+            hipLaunchKernelGGL(k_bigfwd_tri, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);
             break;
         case kBigFwdGemv:
             hipLaunchKernelGGL(k_bigfwd_gemv, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);
