@@ -44,7 +44,7 @@ static_assert(kFilterCapMax == kFilterCapacity, "filter capacity of the options 
     } while (0)
 
 // Launch schedule of one instance: a list of steps.  A group step is a list of
-// groups (supernodes walked in order by one workgroup, in sched_nodes order);
+// groups (supernodes of Device::nodes walked in order by one workgroup);
 // a large-supernode step is a task list for one of the kernels of the
 // multi-workgroup path (BigKind).
 enum StepKind : int { kStepGroupFactor = 100, kStepGroupFwd = 101, kStepGroupBwd = 102 };
@@ -66,6 +66,8 @@ struct Device {
     InstPtrs hI{};                 // host copy of the instance descriptor
     std::vector<Step> fac, fwd, bwd;
     std::vector<int64_t> u_off;    // update blocks' places in the pool
+    std::vector<int32_t> nodes;    // supernodes of the groups, each group's in order
+    std::vector<ChildRec> child_rec;
     std::vector<int32_t> fused;    // supernodes whose Newton-step forward solve runs with their factorization
     std::vector<Step> fwd_rest;   // forward steps of the supernodes whose Newton-step forward solve is not fused
     int fac_launches = 0;          // kernel launches of one factorization
@@ -117,7 +119,8 @@ struct Batch {
     InstPtrs* dI = nullptr;
     Ctl* ctl = nullptr;
     IpmSpaces spaces{};
-    Group* groups = nullptr;
+    FactorTask* ftasks = nullptr;   // one-workgroup launches
+    SolveTask* stasks = nullptr;
     BigTask* tasks = nullptr;
     std::vector<BLaunch> fac, fwd, bwd, fwd_rest;
     bool has_distill = false, has_plate = false, has_reflux = false;
@@ -306,7 +309,8 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
     // forward lists aligned at the leaves, the backward lists at the roots), one
     // launch per kind
     const size_t lim = lds_limit_bytes();
-    std::vector<Group> gl;
+    std::vector<FactorTask> fl;
+    std::vector<SolveTask> sl;
     std::vector<BigTask> tl;
     auto record = [](const Device& D, int inst, const int4& t) {
         const Symbolic& sy = D.owner->sym;
@@ -326,11 +330,69 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
         r.slot = t.x;
         return r;
     };
+    auto factor_task = [&hI](const Device& D, int inst, int sn) {
+        const Symbolic& sy = D.owner->sym;
+        const InstPtrs& I = hI[inst];
+        FactorTask r{};
+        const int f = sy.sn_ptr[sn], c0 = sy.child_ptr[sn];
+        r.ctl = I.ctl;
+        r.L = I.L + sy.l_off[sn];
+        r.U = I.U + D.u_off[sn];
+        r.xp = I.xp + f;
+        r.perm = I.perm + f;
+        r.kv = I.kv + sy.k_ptr[sn];
+        r.fpos = I.S.k_fpos + sy.k_ptr[sn];
+        r.rhs = I.rhs;
+        r.Uall = I.U;
+        r.uvec = I.uvec;
+        r.rel = I.S.rel;
+        r.recs = I.S.child_rec + c0;
+        r.uv = D.fused[sn] ? sy.uv_off[sn] : -1;
+        r.w = sy.sn_ptr[sn + 1] - f;
+        r.m = (int32_t)(sy.sn_rows_ptr[sn + 1] - sy.sn_rows_ptr[sn]);
+        r.nk = (int32_t)(sy.k_ptr[sn + 1] - sy.k_ptr[sn]);
+        r.nchild = sy.child_ptr[sn + 1] - c0;
+        if (r.nchild > 0) r.rec0 = D.child_rec[c0];
+        if (r.nchild > 1) r.rec1 = D.child_rec[c0 + 1];
+        return r;
+    };
+    auto solve_task = [&hI](const Device& D, int inst, int sn) {
+        const Symbolic& sy = D.owner->sym;
+        const InstPtrs& I = hI[inst];
+        SolveTask r{};
+        r.f = sy.sn_ptr[sn];
+        r.ctl = I.ctl;
+        r.L = I.L + sy.l_off[sn];
+        r.rows = I.S.rows + sy.sn_rows_ptr[sn];
+        r.perm = I.perm + r.f;
+        r.w = sy.sn_ptr[sn + 1] - r.f;
+        r.m = (int32_t)(sy.sn_rows_ptr[sn + 1] - sy.sn_rows_ptr[sn]);
+        r.inst = inst;
+        r.sn = sn;
+        return r;
+    };
+    // a launch's records: the groups' first supernodes, then the rest of each
+    struct Walk {
+        int inst, begin, end;   // of the instance's Device::nodes
+    };
+    auto emit_walks = [&](auto& all, const std::vector<Walk>& g, const auto& task) {
+        const size_t at = all.size();
+        for (const Walk& x : g) all.push_back(task(*members[x.inst], x.inst, members[x.inst]->nodes[x.begin]));
+        for (size_t q = 0; q < g.size(); ++q) {
+            size_t last = at + q;
+            for (int i = g[q].begin + 1; i < g[q].end; ++i) {
+                all[last].next = (int32_t)(all.size() - at);
+                last = all.size();
+                all.push_back(task(*members[g[q].inst], g[q].inst, members[g[q].inst]->nodes[i]));
+            }
+        }
+        return (int)at;
+    };
     auto merge = [&](std::vector<BLaunch>& dst, std::vector<Step> Device::*list) {
         size_t len = 0;
         for (auto* D : members) len = std::max(len, (D->*list).size());
         for (size_t j = 0; j < len; ++j) {
-            std::vector<Group> g_fac, g_sol;
+            std::vector<Walk> g_fac, g_sol;
             size_t b_fac = 0, b_sol = 0;
             int gkind = 0, variant = 0, vfront = -1;
             std::vector<std::vector<BigTask>> by_kind(32);
@@ -351,10 +413,10 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
                     }
                     for (const auto& g : st.groups) {
                         if (st.kind == kStepGroupFactor) {
-                            g_fac.push_back(Group{i, g.begin, g.end});
+                            g_fac.push_back(Walk{i, g.begin, g.end});
                             b_fac = std::max(b_fac, g.lds_factor);
                         } else {
-                            g_sol.push_back(Group{i, g.begin, g.end});
+                            g_sol.push_back(Walk{i, g.begin, g.end});
                             b_sol = std::max(b_sol, g.lds_solve);
                         }
                     }
@@ -363,13 +425,11 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
                     kind_lds[st.kind] = std::max(kind_lds[st.kind], st.lds);
                 }
             }
-            auto emit_groups = [&](const std::vector<Group>& g, int kind, size_t bytes) {
-                if (g.empty()) return;
-                dst.push_back(BLaunch{kind, (int)gl.size(), (int)g.size(), bytes, variant, (int)j});
-                gl.insert(gl.end(), g.begin(), g.end());
-            };
-            emit_groups(g_fac, kStepGroupFactor, b_fac);
-            emit_groups(g_sol, gkind, b_sol);
+            if (!g_fac.empty())
+                dst.push_back(BLaunch{kStepGroupFactor, emit_walks(fl, g_fac, factor_task), (int)g_fac.size(), b_fac,
+                                      variant, (int)j});
+            if (!g_sol.empty())
+                dst.push_back(BLaunch{gkind, emit_walks(sl, g_sol, solve_task), (int)g_sol.size(), b_sol, 0, (int)j});
             for (int k = 0; k < 32; ++k) {
                 if (by_kind[k].empty()) continue;
                 dst.push_back(BLaunch{k, (int)tl.size(), (int)by_kind[k].size(), kind_lds[k], 0, (int)j});
@@ -381,7 +441,8 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
     merge(B->fwd, &Device::fwd);
     merge(B->fwd_rest, &Device::fwd_rest);
     merge(B->bwd, &Device::bwd);
-    BTRY(upload(B->allocs, B->groups, gl));
+    BTRY(upload(B->allocs, B->ftasks, fl));
+    BTRY(upload(B->allocs, B->stasks, sl));
     BTRY(upload(B->allocs, B->tasks, tl));
     BTRY(linalg_configure(lim));   // the device maximum, so every batch's launches fit
     BTRY(dalloc(B->allocs, B->running, 3));
@@ -428,14 +489,13 @@ void cold_guess(Batch& B) {
 void run_launch(Batch& B, const BLaunch& L, int pred, double eta_force, int which) {
     switch (L.kind) {
         case kStepGroupFactor:
-            launch_factor_groups(L.variant, pred, eta_force, B.dI, B.groups + L.off, L.count, L.bytes,
-                                 B.stream);
+            launch_factor_groups(L.variant, pred, eta_force, B.ftasks + L.off, L.count, L.bytes, B.stream);
             break;
         case kStepGroupFwd:
-            launch_fwd_groups(pred, which, B.dI, B.groups + L.off, L.count, L.bytes, B.stream);
+            launch_fwd_groups(pred, which, B.dI, B.stasks + L.off, L.count, L.bytes, B.stream);
             break;
         case kStepGroupBwd:
-            launch_bwd_groups(pred, which, B.dI, B.groups + L.off, L.count, L.bytes, B.stream);
+            launch_bwd_groups(pred, which, B.dI, B.stasks + L.off, L.count, L.bytes, B.stream);
             break;
         default:
             launch_big(L.kind, pred, eta_force, which, B.dI, B.tasks + L.off, L.count, L.bytes, B.stream);
@@ -1101,6 +1161,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
     }
     D.u_off = u_off;
     D.fused = fused;
+    D.nodes = nodes;
     std::vector<void*>& A = D.allocs;
     DTRY(upload_c(A, I.jptr, st.jptr));
     DTRY(upload_c(A, I.jcol, st.jcol));
@@ -1124,11 +1185,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
                               (int32_t)(sy.sn_rows_ptr[c + 1] - sy.sn_rows_ptr[c]) - wc, c};
         }
         DTRY(upload_c(A, I.S.child_rec, rec));
-        std::vector<ChildRec> first((size_t)2 * std::max(sy.nsn, 1), ChildRec{0, 0, 0, 0, 0});
-        for (int sn = 0; sn < sy.nsn; ++sn)
-            for (int k = 0; k < 2 && sy.child_ptr[sn] + k < sy.child_ptr[sn + 1]; ++k)
-                first[(size_t)2 * sn + k] = rec[(size_t)sy.child_ptr[sn] + k];
-        DTRY(upload_c(A, I.S.first_recs, first));
+        D.child_rec = std::move(rec);
     }
     DTRY(upload_c(A, I.S.l_off, sy.l_off));
     DTRY(upload_c(A, I.S.u_off, u_off));
@@ -1138,7 +1195,6 @@ nmpc_status device_init(Problem& p, std::string& err) {
     DTRY(upload_c(A, I.S.k_ptr, sy.k_ptr));
     DTRY(upload_c(A, I.S.k_fpos, k_fpos));
     DTRY(upload_c(A, I.kcol_ptr, sy.kcol_ptr));
-    DTRY(upload_c(A, I.S.sched_nodes, nodes));
     DTRY(upload_c(A, I.S.fused, fused));
     DTRY(upload_c(A, I.S.big_col, big_col));
     DTRY(upload_c(A, I.S.big_ptr, big_ptr));
@@ -1879,6 +1935,8 @@ nmpc_status seeds_build(Problem& p, std::string& err) {
         c->bwd = D.bwd;
         c->fwd_rest = D.fwd_rest;
         c->u_off = D.u_off;
+        c->nodes = D.nodes;
+        c->child_rec = D.child_rec;
         c->fused = D.fused;
         D.seed_devs.push_back(c);
     }

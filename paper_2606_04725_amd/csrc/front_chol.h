@@ -61,6 +61,27 @@ __device__ __attribute__((always_inline)) inline double wave_lane(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// kSolveSteps columns, k0 .. k0 + kSolveSteps - 1, of a triangular solve on one
+// wave: lane j holds v_j and the reciprocal r of its diagonal entry, c[u] is its
+// entry of column k0 + u, zero where a step does not touch the lane.  The
+// columns go upwards or, Back, downwards; x_k = v_k r_k leaves lane k through
+// the scalar unit.  With the coefficients ready a step is a product, two lane
+// reads and one multiply-add, about 30 cycles; read and selected in each step
+// they made it 100.
+constexpr int kSolveSteps = 16;
+template <bool Back>
+__device__ __attribute__((always_inline)) inline double solve_steps(double v, double r, const double (&c)[kSolveSteps], int k0) {
+#pragma unroll
+    for (int u = 0; u < kSolveSteps; ++u) {
+        const int q = Back ? kSolveSteps - 1 - u : u;
+        const double y = v * r;
+        const int lo = __builtin_amdgcn_readlane(__double2loint(y), k0 + q);
+        const int hi = __builtin_amdgcn_readlane(__double2hiint(y), k0 + q);
+        v = fma(-c[q], __hiloint2double(hi, lo), v);
+    }
+    return v;
+}
+
 // 1 / sqrt(pivot), the hardware estimate and one third-order step; a pivot that
 // is not positive and finite counts as 1 and, when it is a pivot of the panel
 // (live), sets bad.

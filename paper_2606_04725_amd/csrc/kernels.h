@@ -56,7 +56,6 @@ struct SnView {
     const int32_t* child_ptr;
     const int32_t* child_list;
     const ChildRec* child_rec;    // per child_list position
-    const ChildRec* first_recs;   // per supernode: the records of its first two children (zero past the last)
     const int64_t* l_off;
     const int64_t* u_off;
     const int64_t* uv_off;
@@ -64,7 +63,6 @@ struct SnView {
     const int32_t* rel;
     const int32_t* k_ptr;
     const int32_t* k_fpos;
-    const int32_t* sched_nodes;   // supernodes in launch-schedule order
     const int32_t* fused;         // 1: the Newton step's forward solve runs inside the factor kernel
     // children of the large supernodes (factorization or solves): entries of row
     // and column j are [big_ptr[big_col[s] + j], big_ptr[big_col[s] + j + 1])
@@ -242,10 +240,34 @@ struct DevOpts {
     int cg_max;
 };
 
-// One group of supernodes of one instance: sched_nodes[begin .. end), walked in
-// order by one workgroup.
-struct Group {
-    int inst, begin, end;
+// One supernode of a one-workgroup launch, its sizes and operands by absolute
+// address, so that a workgroup reads its record and then its data.  A launch's
+// array holds the first supernode of every workgroup, then the others, each
+// pointed to by its predecessor (next, 0 at the end).
+struct alignas(64) FactorTask {
+    Ctl* ctl;
+    double* L;             // its panel
+    double* U;             // its update block
+    double* xp;            // at its first column
+    const int32_t* perm;   // at its first column
+    const double* kv;      // its slots of the condensed matrix (nk) and their places
+    const int32_t* fpos;
+    const double* rhs;
+    const double* Uall;    // the update blocks, update vectors and relative rows of all
+    double* uvec;
+    const int32_t* rel;
+    const ChildRec* recs;  // its children (nchild)
+    int64_t uv;            // its update vector; < 0: its forward solve is not fused
+    int32_t w, m, nk, nchild, next, pad;
+    ChildRec rec0, rec1;   // its first two children
+};
+// The solves run over other work vectors too (InstPtrs inst of the launch).
+struct alignas(64) SolveTask {
+    const Ctl* ctl;
+    const double* L;
+    const int32_t* rows;
+    const int32_t* perm;   // at its first column
+    int32_t f, w, m, inst, sn, next;
 };
 
 // ---- model evaluation (kernels_model.hip) -------------------------------------------
@@ -318,13 +340,11 @@ void launch_adj_refine(int step, const InstPtrs* I, const IpmSpaces& S, double e
 // variant: threads per workgroup, 0: 256, 1: 512 (the same arithmetic).  Fewer
 // would leave rows of the largest front without a lane.
 constexpr int kFactorVariants = 2;
-void launch_factor_groups(int variant, int pred, double eta_force, const InstPtrs* I, const Group* g,
-                          int groups, size_t lds_bytes, hipStream_t st);
-// Forward (eq. 23, rhs permutation fused) and back (eqs. 24-25, inverse
-// permutation fused) substitution over groups, vectors chosen by which.
-void launch_fwd_groups(int pred, int which, const InstPtrs* I, const Group* g, int groups, size_t lds_bytes,
+void launch_factor_groups(int variant, int pred, double eta_force, const FactorTask* t, int groups, size_t lds_bytes,
+                          hipStream_t st);
+void launch_fwd_groups(int pred, int which, const InstPtrs* I, const SolveTask* t, int groups, size_t lds_bytes,
                        hipStream_t st);
-void launch_bwd_groups(int pred, int which, const InstPtrs* I, const Group* g, int groups, size_t lds_bytes,
+void launch_bwd_groups(int pred, int which, const InstPtrs* I, const SolveTask* t, int groups, size_t lds_bytes,
                        hipStream_t st);
 // Raise the dynamic shared-memory limit of the front kernels (once per process).
 hipError_t linalg_configure(size_t max_lds_bytes);

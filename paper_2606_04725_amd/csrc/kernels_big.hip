@@ -467,31 +467,19 @@ __device__ __attribute__((always_inline)) inline void store_triangle(const doubl
     if ((i & 3) == wv) rd[i] = i < bw ? 1.0 / d : 1.0;
 }
 
-// Solve with the staged triangle (or, Back, its transpose) on one wave: lane j
-// holds v_j and its reciprocal, x_k leaves lane k through the scalar unit.  The
-// coefficients of 16 steps are read from shared memory before the steps, and
-// are zero for the lanes a step does not touch, so a step is a product, two
-// lane reads and one multiply-add (about 30 cycles; with the coefficients read
-// and selected in each step it was 100).
+// Solve with the staged triangle (or, Back, its transpose) on one wave.
 template <bool Back>
 __device__ __attribute__((always_inline)) inline double solve_triangle(double vj, const double* T, const double* rd, int bw) {
     const int j = threadIdx.x & (kWave - 1);
     const double r = rd[j];
-    for (int g = 0; g < kWave; g += 16) {
-        const int k0 = Back ? kWave - 16 - g : g;   // the group's first column
+    for (int g = 0; g < kWave; g += kSolveSteps) {
+        const int k0 = Back ? kWave - kSolveSteps - g : g;   // the group's first column
         if (k0 >= bw) continue;
-        double c[16];
+        double c[kSolveSteps];
         const double* col = T + (Back ? k0 + j * (kWave + 1) : j + k0 * (kWave + 1));
 #pragma unroll
-        for (int u = 0; u < 16; ++u) c[u] = col[Back ? u : u * (kWave + 1)];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int q = Back ? 15 - u : u;
-            const double y = vj * r;
-            const int lo = __builtin_amdgcn_readlane(__double2loint(y), k0 + q);
-            const int hi = __builtin_amdgcn_readlane(__double2hiint(y), k0 + q);
-            vj = fma(-c[q], __hiloint2double(hi, lo), vj);
-        }
+        for (int u = 0; u < kSolveSteps; ++u) c[u] = col[Back ? u : u * (kWave + 1)];
+        vj = solve_steps<Back>(vj, r, c, k0);
     }
     return vj * r;
 }

@@ -70,10 +70,15 @@ struct ChildRound {
     double uv;
 };
 
+// A record by scalar loads.
+template <class T>
+__device__ __attribute__((always_inline)) inline const __attribute__((address_space(4))) T* record_at(const T* p, int k) {
+    return (const __attribute__((address_space(4))) T*)p + k;
+}
+
 // A child record by scalar loads (field by field: a structure copy does not
 // cross address spaces).
-__device__ __attribute__((always_inline)) inline ChildRec child_rec_at(const ChildRec* recs, int k) {
-    const auto* g = (const __attribute__((address_space(4))) ChildRec*)recs + k;
+__device__ __attribute__((always_inline)) inline ChildRec child_rec_at(const __attribute__((address_space(4))) ChildRec* g) {
     ChildRec r;
     r.u_off = g->u_off;
     r.rel_off = g->rel_off;
@@ -83,49 +88,43 @@ __device__ __attribute__((always_inline)) inline ChildRec child_rec_at(const Chi
     return r;
 }
 
-// The group's first supernode, or -1 when the instance is not in the launch's
-// phase.  Both reads are issued before either is waited for (groups are never
-// empty, so the schedule entry exists whatever the phase).
-__device__ __attribute__((always_inline)) inline int first_node(const InstPtrs& I, const Group& g, int pred) {
-    const Ctl* c = I.ctl;   // every instance has its control block
-    const int s0 = uniform_at(I.S.sched_nodes, g.begin);
-    const int ph = __builtin_amdgcn_readfirstlane(global(c)->phase);   // written by earlier kernels: a vector load
-    const bool active = pred == kPredAll || (pred == kPredFactor ? (ph == kPhB || ph == kPhF) : ph == pred);
-    return active ? s0 : -1;
+// Whether an instance in phase ph takes part in a launch for pred.
+__device__ __attribute__((always_inline)) inline bool in_phase(const Ctl* ctl, int pred) {
+    if (pred == kPredAll) return true;
+    const int ph = __builtin_amdgcn_readfirstlane(global(ctl)->phase);   // written by earlier kernels: a vector load
+    return pred == kPredFactor ? (ph == kPhB || ph == kPhF) : ph == pred;
 }
 
 // One supernode: assemble the front, factor it, store the L panel and update.
 // The front is a packed lower triangle in shared memory, of order m + 1: its last
 // row holds the fused forward solve's right-hand side (zeros without it), which
 // so takes every step as one more row, and its last entry is the spare slot.
-__device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S, const double* __restrict__ kv, double eta, double* __restrict__ L,
-                           double* __restrict__ U, int* __restrict__ fail, double* F, const InstPtrs& I,
-                           bool fwd) {
-    // the first two children's records hang off the supernode itself, so they
-    // are read with its sizes (one level of dependent loads less for the rounds)
-    const ChildRec rec0 = child_rec_at(S.first_recs, 2 * s), rec1 = child_rec_at(S.first_recs, 2 * s + 1);
-    const int f = uniform_at(S.sn_ptr, s);
-    const int w = uniform_at(S.sn_ptr, s + 1) - f;
-    const int m = (int)(uniform_at(S.rows_ptr, s + 1) - uniform_at(S.rows_ptr, s));
+__device__ __attribute__((always_inline)) void factor_one(const __attribute__((address_space(4))) FactorTask* T, double eta,
+                           double* F, bool fwd) {
+    const int w = T->w, m = T->m;
     const PackedIdx ix{m + 1};
     const int nb = m - w;
     const int spare = ((m + 1) * (m + 2)) / 2 - 1;
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int lane = tid & (kWave - 1), wv = tid / kWave, nw = nthr / kWave;
-    const bool fw = fwd && uniform_at(S.fused, s);
+    const bool fw = fwd && T->uv >= 0;
     // original entries of the condensed matrix in this supernode's columns, the
     // first kBatch per thread loaded before the children's rounds (so that
     // waiting for them does not wait for the rounds); a diagonal entry's
     // position is stored complemented and takes + eta
-    const int kt0 = uniform_at(S.k_ptr, s), kt1 = uniform_at(S.k_ptr, s + 1);
-    const int c0 = uniform_at(S.child_ptr, s), c1 = uniform_at(S.child_ptr, s + 1);
+    const int nk = T->nk, nchild = T->nchild;
+    const auto* fpos = global(T->fpos);
+    const auto* kv = global(T->kv);
+    const auto* perm = global(T->perm);
+    const auto* rhs = global(T->rhs);
+    const int32_t* rel = T->rel;
     int kp[kBatch];
     double kx[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-        const int t = kt0 + tid + u * nthr;
-        kp[u] = t < kt1 ? global(S.k_fpos)[t] : 0;
-        kx[u] = t < kt1 ? global(kv)[t] : 0.0;
+        const int t = tid + u * nthr;
+        kp[u] = t < nk ? fpos[t] : 0;
+        kx[u] = t < nk ? kv[t] : 0.0;
     }
     // The children's update blocks go in rounds, child after child, row block
     // after row block; the loads of two rounds are in flight ahead of the one
@@ -136,28 +135,28 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
         int child, nc, i0, j0;
         bool uv;
     };
-    int pci = c0, prb = 0, pjb = 0;   // the next round to issue
-    ChildRec prec = rec0, pnext = rec1;
+    int pci = 0, prb = 0, pjb = 0;   // the next round to issue
+    ChildRec prec = child_rec_at(&T->rec0), pnext = child_rec_at(&T->rec1);
     // the fused forward solve's right-hand side of the supernode's columns:
     // the permutation is read before the rounds, thread i's entry of the
     // right-hand side after them (loads complete in the order issued; the
     // right-hand side is waited for where the rounds are about to be added)
-    const int pk0 = fw && tid < w ? global(I.perm)[f + tid] : 0;
+    const int pk0 = fw && tid < w ? perm[tid] : 0;
     auto issue = [&](ChildRound& r, RoundInfo& info) -> bool {
-        if (pci >= c1) return false;
+        if (pci >= nchild) return false;
         const int nc = prec.nc;
         const int64_t uo = prec.u_off, ro = prec.rel_off;
         const int i0 = kWave * prb, j0 = pjb + kCols * wvu, i = min(i0 + lane, nc - 1);
-        const auto* uc = global(U) + uo + i;
+        const auto* uc = global(T->Uall) + uo + i;
 #pragma unroll
         for (int u = 0; u < kCols; ++u) {
             const int j = min(j0 + u, nc - 1);
-            r.rj[u] = uniform_at(S.rel + ro, j);
+            r.rj[u] = uniform_at(rel + ro, j);
             r.v[u] = uc[j * nc];
         }
-        r.ri = global(S.rel)[ro + i];
+        r.ri = global(rel)[ro + i];
         const bool uv = fw && wvu == 0 && pjb == 0;
-        r.uv = uv ? global(I.uvec)[prec.uv_off + i] : 0.0;
+        r.uv = uv ? global(T->uvec)[prec.uv_off + i] : 0.0;
         info = RoundInfo{pci, nc, i0, j0, uv};
         pjb += kCols * nw;
         if (pjb >= min(nc, i0 + kWave)) {   // past the row block's last column
@@ -166,7 +165,7 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
                 prb = 0;
                 ++pci;
                 prec = pnext;
-                if (pci + 1 < c1) pnext = child_rec_at(S.child_rec, pci + 1);
+                if (pci + 1 < nchild) pnext = child_rec_at(record_at(T->recs, pci + 1));
             }
         }
         return true;
@@ -176,7 +175,7 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
     bool ha = issue(ra, ia);
     bool hb = issue(rb, ib);
     double rv = 0.0;
-    if (fw && tid < w) rv = global(I.rhs)[pk0];
+    if (fw && tid < w) rv = rhs[pk0];
     const int fsize = ((m + 1) * (m + 2)) / 2;
     for (int e = tid; e < fsize; e += nthr) F[e] = 0.0;
     __syncthreads();
@@ -189,13 +188,13 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
     };
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
-        if (kt0 + tid + u * nthr < kt1) place(kp[u], kx[u]);
-    for (int t = kt0 + tid + kBatch * nthr; t < kt1; t += nthr) place(global(S.k_fpos)[t], global(kv)[t]);
+        if (tid + u * nthr < nk) place(kp[u], kx[u]);
+    for (int t = tid + kBatch * nthr; t < nk; t += nthr) place(fpos[t], kv[t]);
     // fused forward solve of the Newton step: the last row starts from the
     // permuted right-hand side of the supernode's columns (before the barrier
     // that precedes the children's update vectors)
     if (fw)
-        for (int i = tid; i < w; i += nthr) F[ix(m, i)] = i == tid ? rv : global(I.rhs)[global(I.perm)[f + i]];
+        for (int i = tid; i < w; i += nthr) F[ix(m, i)] = i == tid ? rv : rhs[perm[i]];
     __syncthreads();
     // extend-add in fixed order; children are separated by barriers (two
     // children can add into the same entry, one child's entries are distinct)
@@ -223,7 +222,7 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
         ib = ic;
         hb = hc;
     }
-    partial_cholesky(F, ix, w, spare, fail);
+    partial_cholesky(F, ix, w, spare, &T->ctl->fail);
     // the update block (rows and columns w and on) takes its update before the
     // panel goes out: global stores in flight would hold the update's first
     // shared-memory loads until they complete (their data registers are reused)
@@ -231,7 +230,7 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
     // kStore columns per wave at a time, so that their shared-memory reads are
     // in flight together
     constexpr int kStore = 4;
-    auto* Ls = global(L + uniform_at(S.l_off, s));
+    auto* Ls = global(T->L);
     for (int jc = kStore * wvu; jc < w; jc += kStore * nw)
         for (int i = lane; i < m; i += kWave) {
             double x[kStore];
@@ -245,12 +244,12 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
                 if (jc + u < w) Ls[i + (jc + u) * m] = i >= jc + u ? x[u] : 0.0;
         }
     if (fw) {   // the forward solve's part of the columns and the update vector
-        for (int k = tid; k < w; k += nthr) global(I.xp)[f + k] = F[ix(m, k)];
-        auto* us = global(I.uvec + uniform_at(S.uv_off, s));
+        for (int k = tid; k < w; k += nthr) global(T->xp)[k] = F[ix(m, k)];
+        auto* us = global(T->uvec + T->uv);
         for (int i = w + tid; i < m; i += nthr) us[i - w] = F[ix(m, i)];
     }
     if (nb > 0) {
-        auto* Us = global(U + uniform_at(S.u_off, s));
+        auto* Us = global(T->U);
         for (int jj = kStore * wvu; jj < nb; jj += kStore * nw)
             for (int ii = (jj & ~(kWave - 1)) + lane; ii < nb; ii += kWave) {
                 double x[kStore];
@@ -272,17 +271,17 @@ __device__ __attribute__((always_inline)) void factor_one(int s, const SnView& S
 // accumulators stay in the vector registers)
 template <int Threads>
 __global__ void __launch_bounds__(Threads, 2)
-k_factor_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ groups, int pred, double eta_force) {
+k_factor_groups(const FactorTask* __restrict__ tasks, int pred, double eta_force) {
     extern __shared__ double lds[];
-    const Group g = groups[blockIdx.x];
-    const InstPtrs& I = Ia[g.inst];
-    const int s0 = first_node(I, g, pred);
-    if (s0 < 0) return;
-    const double eta = pred == kPredAll ? eta_force : I.ctl->eta;
+    const auto* T = record_at(tasks, blockIdx.x);
+    if (!in_phase(T->ctl, pred)) return;
+    const double eta = pred == kPredAll ? eta_force : global(T->ctl)->eta;
     const bool fwd = pred == kPredFactor;   // in a pass: the Newton step's right-hand side is assembled
-    for (int i = g.begin; i < g.end; ++i) {
-        const int s = i == g.begin ? s0 : uniform_at(I.S.sched_nodes, i);
-        factor_one(s, I.S, I.kv, eta, I.L, I.U, &I.ctl->fail, lds, I, fwd);
+    while (true) {
+        factor_one(T, eta, lds, fwd);
+        const int next = T->next;
+        if (next == 0) break;
+        T = record_at(tasks, next);
     }
 }
 
@@ -332,22 +331,20 @@ __device__ __attribute__((always_inline)) void stage_panel(const double* __restr
 // its columns, add the children's update vectors, solve with the diagonal
 // block, then form the update vector of its rows below.
 // Shared memory: panel (m w) + rdiag (w) + v (m) + xs (w).
-__device__ __attribute__((always_inline)) void fwd_one(int s, const SnView& S, const double* __restrict__ L, double* __restrict__ uvec,
-                        const double* __restrict__ rhs, const int32_t* __restrict__ perm, double* __restrict__ xp,
-                        double* lds) {
-    const int f = uniform_at(S.sn_ptr, s);
-    const int w = uniform_at(S.sn_ptr, s + 1) - f;
-    const int m = (int)(uniform_at(S.rows_ptr, s + 1) - uniform_at(S.rows_ptr, s));
+__device__ __attribute__((always_inline)) void fwd_one(const __attribute__((address_space(4))) SolveTask* T, const SnView& S, double* __restrict__ uvec,
+                        const double* __restrict__ rhs, double* __restrict__ xp, double* lds) {
+    const int s = T->sn, f = T->f, w = T->w, m = T->m;
+    const int32_t* perm = T->perm;
     const int tid = threadIdx.x, nthr = blockDim.x;
     double* P = lds;
     double* rdiag = P + (int64_t)m * w;
     double* v = rdiag + w;
     double* xs = v + m;
-    stage_panel(L + uniform_at(S.l_off, s), m, w, P, rdiag);
-    for (int i = tid; i < m; i += nthr) v[i] = i < w ? rhs[perm[f + i]] : 0.0;
+    stage_panel(T->L, m, w, P, rdiag);
+    for (int i = tid; i < m; i += nthr) v[i] = i < w ? rhs[perm[i]] : 0.0;
     __syncthreads();
     for (int ci = uniform_at(S.child_ptr, s); ci < uniform_at(S.child_ptr, s + 1); ++ci) {
-        const ChildRec rec = child_rec_at(S.child_rec, ci);
+        const ChildRec rec = child_rec_at(record_at(S.child_rec, ci));
         const int nc = rec.nc;
         const double* uc = uvec + rec.uv_off;
         const int32_t* rc = S.rel + rec.rel_off;
@@ -362,35 +359,33 @@ __device__ __attribute__((always_inline)) void fwd_one(int s, const SnView& S, c
 }
 
 __global__ void __launch_bounds__(kFactorBlock)
-k_fwd_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ groups, int pred, int which) {
+k_fwd_groups(const InstPtrs* __restrict__ Ia, const SolveTask* __restrict__ tasks, int pred, int which) {
     extern __shared__ double lds[];
-    const Group g = groups[blockIdx.x];
-    const InstPtrs& I = Ia[g.inst];
-    const int s0 = first_node(I, g, pred);
-    if (s0 < 0) return;
-    for (int i = g.begin; i < g.end; ++i)
-        fwd_one(i == g.begin ? s0 : uniform_at(I.S.sched_nodes, i), I.S, I.L, I.uvec, solve_in(I, which), I.perm, I.xp, lds);
-}
-
-// Value of v in lane k of the wave, in every lane (k wave-uniform).
-__device__ __attribute__((always_inline)) inline double lane_value(double v, int k) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), k);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), k);
-    return __hiloint2double(hi, lo);
+    const auto* T = record_at(tasks, blockIdx.x);
+    const InstPtrs& I = Ia[T->inst];
+    if (!in_phase(T->ctl, pred)) return;
+    while (true) {
+        fwd_one(T, I.S, I.uvec, solve_in(I, which), I.xp, lds);
+        const int next = T->next;
+        if (next == 0) break;
+        T = record_at(tasks, next);
+    }
 }
 
 // Back substitution L^T x = v for one supernode, after all its ancestors:
 // subtract the contribution of the rows below (already final), then solve
 // with the transposed diagonal block; writes x unpermuted.  Every global load
-// is issued before the first shared-memory store: the diagonal block (staged
-// transposed, leading dimension w | 1, kBatch entries per thread per round),
-// its diagonal, the supernode's entries of xp, the solution of the rows below
-// (gathered through the row list) and the output permutation.  The rows below
-// are then read straight from the panel, 16 lanes per column and kBwdCols
-// columns per lane group at once (a butterfly sums the lanes).  The diagonal
-// block is solved by wave 0, 64 columns at a time from the last: lane j holds
-// v_j, x_k leaves lane k through the scalar unit, and the earlier columns take
-// the block's contribution before the next block.
+// is issued before the first shared-memory store: the diagonal block (a column
+// per wave at a time, the lanes over its rows; staged with leading dimension
+// w | 1 and zeros on and above the diagonal), its diagonal, the supernode's
+// entries of xp, the solution of the rows below (gathered through the row list)
+// and the output permutation.  The rows below are read straight from the panel,
+// 16 lanes per column and kBwdCols columns per lane group at once (a butterfly
+// sums the lanes).  The diagonal block is solved by wave 0, 64 columns at a time
+// from the last, and the earlier columns take the block's contribution before
+// the next block.  A lone chain of dependent loads and lane reads bounds it (the
+// matrix is small): 40 x 100 column, 7.9 us per launch with the solve's
+// coefficients read in each step and sizes read through the schedule.
 // Shared memory: diagonal block (w (w | 1)) + rdiag (w) + xb (m - w) + v (w) + xs (w).
 constexpr int kBwdCols = 4;    // columns per 16-lane group in the rows-below product
 constexpr int kBwdDepth = 8;   // rows per lane whose loads are in flight together
@@ -408,27 +403,45 @@ __device__ __attribute__((always_inline)) inline void group_sums(double (&acc)[k
         for (int u = 0; u < kBwdCols; ++u) acc[u] += x[u];
     }
 }
-__device__ __attribute__((always_inline)) void bwd_one(int s, const SnView& S, const double* __restrict__ L, double* __restrict__ xp,
-                        const int32_t* __restrict__ perm, double* __restrict__ out, double* lds) {
-    const int f = uniform_at(S.sn_ptr, s);
-    const int w = uniform_at(S.sn_ptr, s + 1) - f;
-    const int64_t ro = uniform_at(S.rows_ptr, s);
-    const int m = (int)(uniform_at(S.rows_ptr, s + 1) - ro);
+__device__ __attribute__((always_inline)) void bwd_one(const __attribute__((address_space(4))) SolveTask* T, double* __restrict__ xp,
+                        double* __restrict__ out, double* lds) {
+    const int f = T->f, w = T->w, m = T->m;
     const int nb = m - w;
     const int tid = threadIdx.x, nthr = blockDim.x;
-    const int lane = tid & (kWave - 1), wv = tid / kWave;
+    const int lane = tid & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(tid / kWave), nw = nthr / kWave;
     const int ld = w | 1;
-    double* PT = lds;
-    double* rdiag = PT + (int64_t)w * ld;
+    double* D = lds;
+    double* rdiag = D + w * ld;
     double* xb = rdiag + w;
     double* v = xb + nb;
     double* xs = v + w;
-    const double* Ls = L + uniform_at(S.l_off, s);
-    const int32_t* rows = S.rows + ro;
-    const int ri = tid < nb ? global(rows)[w + tid] : 0;
-    const double dg = tid < w ? global(Ls)[tid + (int64_t)tid * m] : 1.0;
-    const double xv = tid < w ? global(xp)[f + tid] : 0.0;
-    const int pk = tid < w ? global(perm)[f + tid] : 0;
+    const auto* Ls = global(T->L);
+    const auto* rows = global(T->rows) + w;
+    const int ri = rows[min(tid, max(nb, 1) - 1) - (nb == 0)];   // without rows below: the last column's own
+    // the panel fits in shared memory, so w < nthr
+    const int tc = min(tid, w - 1);
+    const int pk = global(T->perm)[tc];
+    const double dg = Ls[tc + tc * m];
+    // a round of the diagonal block: 64 rows from r0 of kDiag columns per wave from c0 + wv
+    constexpr int kDiag = 16;
+    double t[kDiag];
+    auto load_diag = [&](int r0, int c0) {
+        const auto* col = Ls + min(r0 + lane, w - 1);
+#pragma unroll
+        for (int u = 0; u < kDiag; ++u) t[u] = col[min(c0 + wv + u * nw, w - 1) * m];
+    };
+    auto store_diag = [&](int r0, int c0) {
+        const int r = r0 + lane;
+        if (r < w) {
+#pragma unroll
+            for (int u = 0; u < kDiag; ++u) {
+                const int c = c0 + wv + u * nw;
+                if (c < w) D[r + c * ld] = r > c ? t[u] : 0.0;
+            }
+        }
+    };
+    load_diag(0, 0);
+    const double xv = global(xp)[f + tc];
     // rows-below product: 16 lanes per column, kBwdCols columns per lane group;
     // when it takes one pass (w <= kBwdCols * groups, nb <= kSub * kBwdDepth)
     // the panel's values are loaded here, with everything else
@@ -440,43 +453,27 @@ __device__ __attribute__((always_inline)) void bwd_one(int s, const SnView& S, c
 #pragma unroll
         for (int u = 0; u < kBwdCols; ++u) {
             const int jc = grp + u * ngrp;
-            const double* col = Ls + (int64_t)(jc < w ? jc : 0) * m + w;
+            const auto* col = Ls + (jc < w ? jc : 0) * m + w;
 #pragma unroll
-            for (int t = 0; t < kBwdDepth; ++t) lp[t][u] = global(col)[min(sub + kSub * t, nb - 1)];
+            for (int q = 0; q < kBwdDepth; ++q) lp[q][u] = col[min(sub + kSub * q, nb - 1)];
         }
     }
-    const int ww = w * w;
-    // entry e of the block is (r, c) = (e % w, e / w); the quotient through a
-    // single-precision reciprocal is exact here (e < w^2 <= 2^15, and (e + 1/2)
-    // / w stays at least 1 / (2 w) away from an integer)
-    const float rw = 1.0f / (float)w;
-    for (int e0 = 0; e0 < ww; e0 += nthr * kBatch) {
-        double t[kBatch];
-        int cc[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int e = e0 + tid + u * nthr, c = (int)(((float)e + 0.5f) * rw), r = e - c * w;
-            cc[u] = c;
-            t[u] = (e < ww && r >= c) ? global(Ls)[r + (int64_t)c * m] : 0.0;
+    const double xr = global(xp)[ri];
+    store_diag(0, 0);
+    const int span = kDiag * nw;   // columns per round
+    for (int c0 = 0; c0 < w; c0 += span)
+        for (int r0 = (c0 / kWave) * kWave; r0 < w; r0 += kWave) {
+            if (r0 == 0 && c0 == 0) continue;
+            load_diag(r0, c0);
+            store_diag(r0, c0);
         }
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int e = e0 + tid + u * nthr, c = cc[u], r = e - c * w;
-            if (e < ww && r >= c) PT[c + r * ld] = t[u];
-        }
-    }
-    if (tid < nb) xb[tid] = global(xp)[ri];
+    if (tid < nb) xb[tid] = xr;
     if (tid < w) {
         rdiag[tid] = 1.0 / dg;
         v[tid] = xv;
     }
-    // the panel fits in shared memory, so w < nthr; a narrow supernode can have
-    // more rows below than threads
-    for (int i = tid + nthr; i < nb; i += nthr) xb[i] = global(xp)[global(rows)[w + i]];
-    for (int k = tid + nthr; k < w; k += nthr) {
-        rdiag[k] = 1.0 / global(Ls)[k + (int64_t)k * m];
-        v[k] = global(xp)[f + k];
-    }
+    // a narrow supernode can have more rows below than threads
+    for (int i = tid + nthr; i < nb; i += nthr) xb[i] = global(xp)[rows[i]];
     __syncthreads();
     if (one_pass) {
         if (grp < w) {   // uniform over each 16-lane group
@@ -484,11 +481,11 @@ __device__ __attribute__((always_inline)) void bwd_one(int s, const SnView& S, c
 #pragma unroll
             for (int u = 0; u < kBwdCols; ++u) acc[u] = 0.0;
 #pragma unroll
-            for (int t = 0; t < kBwdDepth; ++t) {
-                const int i = sub + kSub * t;
-                const double xv = i < nb ? xb[min(i, nb - 1)] : 0.0;
+            for (int q = 0; q < kBwdDepth; ++q) {
+                const int i = sub + kSub * q;
+                const double x = i < nb ? xb[min(i, nb - 1)] : 0.0;
 #pragma unroll
-                for (int u = 0; u < kBwdCols; ++u) acc[u] = fma(lp[t][u], xv, acc[u]);
+                for (int u = 0; u < kBwdCols; ++u) acc[u] = fma(lp[q][u], x, acc[u]);
             }
             group_sums(acc);
 #pragma unroll
@@ -500,12 +497,12 @@ __device__ __attribute__((always_inline)) void bwd_one(int s, const SnView& S, c
     } else
     for (int jc0 = grp; jc0 < w; jc0 += kBwdCols * ngrp) {
         double acc[kBwdCols];
-        const double* col[kBwdCols];
+        const gdouble* col[kBwdCols];
 #pragma unroll
         for (int u = 0; u < kBwdCols; ++u) {
             const int jc = jc0 + u * ngrp;
             acc[u] = 0.0;
-            col[u] = Ls + (int64_t)(jc < w ? jc : 0) * m + w;
+            col[u] = Ls + (jc < w ? jc : 0) * m + w;
         }
         // kBwdDepth rows per lane at a time, all their loads issued together
         // (rows past nb load row nb - 1 and add zero; a column past w reads
@@ -517,7 +514,7 @@ __device__ __attribute__((always_inline)) void bwd_one(int s, const SnView& S, c
                 const int i = i0 + kSub * t, ic = min(i, nb - 1);
                 xv[t] = i < nb ? xb[ic] : 0.0;
 #pragma unroll
-                for (int u = 0; u < kBwdCols; ++u) lv[t][u] = global(col[u])[ic];
+                for (int u = 0; u < kBwdCols; ++u) lv[t][u] = col[u][ic];
             }
 #pragma unroll
             for (int t = 0; t < kBwdDepth; ++t)
@@ -535,48 +532,62 @@ __device__ __attribute__((always_inline)) void bwd_one(int s, const SnView& S, c
     for (int b0 = ((w - 1) / kWave) * kWave; b0 >= 0; b0 -= kWave) {
         const int bw = min(kWave, w - b0);
         if (wv == 0) {
-            const int j = lane;
-            double vj = j < bw ? v[b0 + j] : 0.0;
+            const int j = min(lane, bw - 1);
+            const double r = rdiag[b0 + j];
+            double vj = lane < bw ? v[b0 + j] : 0.0;
+            const double* col = D + b0 + (b0 + j) * ld;
+            for (int k0 = ((bw - 1) / kSolveSteps) * kSolveSteps; k0 >= 0; k0 -= kSolveSteps) {
+                double c[kSolveSteps];
+                if (k0 + kSolveSteps <= bw) {
 #pragma unroll
-            for (int k = kWave - 1; k >= 0; --k) {
-                if (k < bw) {   // wave-uniform
-                    const double xk = lane_value(vj, k) * rdiag[b0 + k];
-                    const double upd = fma(-PT[(b0 + j) + (b0 + k) * ld], xk, vj);
-                    vj = j == k ? xk : (j < k ? upd : vj);
+                    for (int u = 0; u < kSolveSteps; ++u) c[u] = col[k0 + u];
+                } else {   // steps past the block take nothing
+#pragma unroll
+                    for (int u = 0; u < kSolveSteps; ++u) {
+                        const double x = col[min(k0 + u, bw - 1)];
+                        c[u] = k0 + u < bw ? x : 0.0;
+                    }
+                }
+                vj = solve_steps<true>(vj, r, c, k0);
+            }
+            vj *= r;
+            if (lane < bw) {
+                xs[b0 + lane] = vj;
+                if (b0 == 0) {   // the other blocks' entries go out below
+                    global(xp)[f + lane] = vj;
+                    global(out)[pk] = vj;
                 }
             }
-            if (j < bw) xs[b0 + j] = vj;
         }
-        __syncthreads();
         if (b0 > 0) {   // columns before the block: v[c] -= L(block, c)^T x(block)
+            __syncthreads();
             for (int c = tid; c < b0; c += nthr) {
                 double acc = v[c];
-                for (int q = 0; q < bw; ++q) acc = fma(-PT[c + (b0 + q) * ld], xs[b0 + q], acc);
+                for (int q = 0; q < bw; ++q) acc = fma(-D[b0 + q + c * ld], xs[b0 + q], acc);
                 v[c] = acc;
             }
             __syncthreads();
         }
     }
-    if (tid < w) {
+    if (tid >= kWave && tid < w) {
         global(xp)[f + tid] = xs[tid];
         global(out)[pk] = xs[tid];
     }
-    for (int k = tid + nthr; k < w; k += nthr) {
-        global(xp)[f + k] = xs[k];
-        global(out)[global(perm)[f + k]] = xs[k];
-    }
-    __syncthreads();
 }
 
 __global__ void __launch_bounds__(kFactorBlock)
-k_bwd_groups(const InstPtrs* __restrict__ Ia, const Group* __restrict__ groups, int pred, int which) {
+k_bwd_groups(const InstPtrs* __restrict__ Ia, const SolveTask* __restrict__ tasks, int pred, int which) {
     extern __shared__ double lds[];
-    const Group g = groups[blockIdx.x];
-    const InstPtrs& I = Ia[g.inst];
-    const int s0 = first_node(I, g, pred);
-    if (s0 < 0) return;
-    for (int i = g.begin; i < g.end; ++i)
-        bwd_one(i == g.begin ? s0 : uniform_at(I.S.sched_nodes, i), I.S, I.L, I.xp, I.perm, solve_out(I, which), lds);
+    const auto* T = record_at(tasks, blockIdx.x);
+    const InstPtrs& I = Ia[T->inst];
+    if (!in_phase(T->ctl, pred)) return;
+    while (true) {
+        bwd_one(T, I.xp, solve_out(I, which), lds);
+        const int next = T->next;
+        if (next == 0) break;
+        __syncthreads();   // the next supernode reads this one's solution and reuses its shared memory
+        T = record_at(tasks, next);
+    }
 }
 
 }  // namespace
@@ -592,25 +603,25 @@ hipError_t linalg_configure(size_t max_lds_bytes) {
     return hipSuccess;
 }
 
-void launch_factor_groups(int variant, int pred, double eta_force, const InstPtrs* I, const Group* g, int groups,
-                          size_t lds_bytes, hipStream_t st) {
+void launch_factor_groups(int variant, int pred, double eta_force, const FactorTask* t, int groups, size_t lds_bytes,
+                          hipStream_t st) {
     if (groups <= 0) return;
     if (variant == 1)
-        hipLaunchKernelGGL(k_factor_groups<512>, dim3(groups), dim3(512), lds_bytes, st, I, g, pred, eta_force);
+        hipLaunchKernelGGL(k_factor_groups<512>, dim3(groups), dim3(512), lds_bytes, st, t, pred, eta_force);
     else
-        hipLaunchKernelGGL(k_factor_groups<256>, dim3(groups), dim3(256), lds_bytes, st, I, g, pred, eta_force);
+        hipLaunchKernelGGL(k_factor_groups<256>, dim3(groups), dim3(256), lds_bytes, st, t, pred, eta_force);
 }
 
-void launch_fwd_groups(int pred, int which, const InstPtrs* I, const Group* g, int groups, size_t lds_bytes,
+void launch_fwd_groups(int pred, int which, const InstPtrs* I, const SolveTask* t, int groups, size_t lds_bytes,
                        hipStream_t st) {
     if (groups <= 0) return;
-    hipLaunchKernelGGL(k_fwd_groups, dim3(groups), dim3(kFactorBlock), lds_bytes, st, I, g, pred, which);
+    hipLaunchKernelGGL(k_fwd_groups, dim3(groups), dim3(kFactorBlock), lds_bytes, st, I, t, pred, which);
 }
 
-void launch_bwd_groups(int pred, int which, const InstPtrs* I, const Group* g, int groups, size_t lds_bytes,
+void launch_bwd_groups(int pred, int which, const InstPtrs* I, const SolveTask* t, int groups, size_t lds_bytes,
                        hipStream_t st) {
     if (groups <= 0) return;
-    hipLaunchKernelGGL(k_bwd_groups, dim3(groups), dim3(kFactorBlock), lds_bytes, st, I, g, pred, which);
+    hipLaunchKernelGGL(k_bwd_groups, dim3(groups), dim3(kFactorBlock), lds_bytes, st, I, t, pred, which);
 }
 
 }  // namespace nmpc
