@@ -11,15 +11,18 @@
 // in one pass every running instance moves through one Newton iteration (or
 // one more factorization attempt, or one more trial point, when its last one
 // failed), so instances of a batch never wait for each other.  A pass needs no
-// host decision, so it is captured once as a HIP graph and replayed; after
-// each pass the host reads one integer, the number of instances still running.
+// host decision, so it is captured once as a HIP graph and replayed; a pass
+// ends with the evaluation of the next iterate, whose decision kernel stores
+// the number of instances still running in a pinned word that the host polls.
 //
 // A problem's own solve is a batch of one; a user batch groups the device state
 // of several analyzed problems and runs the same passes over all of them, so
 // an instance's arithmetic is the same alone or batched.
 #include <hip/hip_runtime.h>
+#include <sched.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -128,11 +131,10 @@ struct Batch {
     // distinct code object; each launch covers the batch, its kernels skip
     // instances with another tag)
     std::vector<GenFns> gen;
-    int* running = nullptr;        // device: instances running, instances waiting for corrections,
-                                   // instances whose HyKKT conjugate gradients run
-    int* hrunning = nullptr;       // pinned copy
+    Report rep{};                  // device counters, pinned words and control blocks (hctl)
+    uint16_t seq = 0, seq_cg = 0;  // reports enqueued
     Ctl* hctl = nullptr;           // pinned
-    hipEvent_t ev[8] = {};
+    hipEvent_t ev[9] = {};
     // captured graphs, index timed + 2 * part: part 0 the pass, part 1 the
     // second-order corrections (replayed only when an instance waits for them)
     hipGraph_t graph[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -242,7 +244,7 @@ void batch_release(Batch* B) {
     if (B->loop_exec) (void)hipGraphExecDestroy(B->loop_exec);
     if (B->loop_graph) (void)hipGraphDestroy(B->loop_graph);
     for (void* a : B->allocs) (void)hipFree(a);
-    if (B->hrunning) (void)hipHostFree(B->hrunning);
+    if (B->rep.host) (void)hipHostFree(B->rep.host);
     if (B->hctl) (void)hipHostFree(B->hctl);
     if (B->loop_ctl) (void)hipHostFree(B->loop_ctl);
     for (auto e : B->ev)
@@ -445,9 +447,11 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
     BTRY(upload(B->allocs, B->stasks, sl));
     BTRY(upload(B->allocs, B->tasks, tl));
     BTRY(linalg_configure(lim));   // the device maximum, so every batch's launches fit
-    BTRY(dalloc(B->allocs, B->running, 3));
-    BTRY(hipHostMalloc((void**)&B->hrunning, 3 * sizeof(int), hipHostMallocDefault));
-    BTRY(hipHostMalloc((void**)&B->hctl, sizeof(Ctl) * ni, hipHostMallocDefault));
+    BTRY(upload(B->allocs, B->rep.cnt, std::vector<unsigned>(kRepCounters, 0u)));
+    BTRY(hipHostMalloc((void**)&B->rep.host, 2 * sizeof(unsigned long long), hipHostMallocCoherent | hipHostMallocMapped));
+    B->rep.host[0] = B->rep.host[1] = 0;
+    BTRY(hipHostMalloc((void**)&B->hctl, sizeof(Ctl) * ni, hipHostMallocCoherent | hipHostMallocMapped));
+    B->rep.ctl = B->hctl;
     for (auto& e : B->ev) BTRY(hipEventCreate(&e));
 #undef BTRY
     out = B;
@@ -513,46 +517,31 @@ void solve_launches(Batch& B, int pred, int which, bool fused_done = false) {
     for (const auto& L : B.bwd) run_launch(B, L, pred, 0.0, which);
 }
 
-// One pass of Algorithm 2 over every running instance.  An instance whose first
-// trial point asks for second-order corrections waits in phase C; the
-// corrections run in their own part, enqueued before the next pass only when
-// some instance waits (most passes need none).
-void enqueue_pass(Batch& B, const DevOpts& o, bool timed) {
-    hipStream_t st = B.stream;
-    auto mark = [&](int k) {
-        if (timed) (void)hipEventRecord(B.ev[k], st);
-    };
-    mark(0);
-    eval(B, true, kSrcIter, kPhA);
-    launch_phaseA(B.dI, B.spaces, B.ninst, kPhA, o, true, st);
-    mark(1);
-    launch_assemble(B.dI, B.spaces, kPhB, st);
-    mark(2);
-    factor_launches(B, kPredFactor, 0.0);
-    launch_decideF(B.dI, B.ninst, o, st);
-    mark(3);
-    solve_launches(B, kPhS, 0, true);
-    launch_phaseE(B.dI, B.spaces, B.ninst, o, st);
-    mark(4);
-    launch_trial(B.dI, B.spaces, st);
-    eval(B, false, kSrcTrial, kPhT);
-    launch_phaseT(B.dI, B.spaces, B.ninst, o, st);
-    launch_update(B.dI, B.spaces, B.ninst, o, B.running, st);
-    mark(5);
+// Evaluation and optimality of the instances at a new iterate (phase A), with
+// the report of the instances still running.  It opens a solve and closes every
+// pass, so that the host learns of convergence before it enqueues a pass that
+// would find nothing to do.
+void enqueue_eval(Batch& B, const DevOpts& o) {
+    eval(B, true, kSrcIter, kPredEval);
+    launch_phaseA(B.dI, B.spaces, B.ninst, kPredEval, o, true, B.rep, B.stream);
 }
 
-// One pass of the HyKKT variant: as enqueue_pass up to the solve of the
-// right-hand side, then conjugate gradients on the Schur complement (one
-// iteration per host round trip, until no instance's CG runs; the device ends
-// each at cg_max), the final solve, and the rest of the pass.
-hipError_t enqueue_pass_hykkt(Batch& B, const DevOpts& o, bool timed) {
+hipError_t wait_report(Batch& B, int which, uint16_t& seq, unsigned long long& word);
+
+// One pass of Algorithm 2 over every running instance, from the condensed
+// system to the evaluation of the next iterate.  An instance whose first trial
+// point asks for second-order corrections waits in phase C; the corrections run
+// in their own part, enqueued before the next pass only when some instance
+// waits (most passes need none).  Events (timed): 1 to 5 before the assembly,
+// the factorization, the solves, the line search and the evaluation, 0 after it.
+// The HyKKT variant adds conjugate gradients on the Schur complement to the
+// solve (one iteration per host round trip, until no instance's CG runs; the
+// device ends each at cg_max) and a final solve.
+hipError_t enqueue_pass(Batch& B, const DevOpts& o, bool timed, bool hyk = false) {
     hipStream_t st = B.stream;
     auto mark = [&](int k) {
         if (timed) (void)hipEventRecord(B.ev[k], st);
     };
-    mark(0);
-    eval(B, true, kSrcIter, kPhA);
-    launch_phaseA(B.dI, B.spaces, B.ninst, kPhA, o, true, st);
     mark(1);
     launch_assemble(B.dI, B.spaces, kPhB, st);
     mark(2);
@@ -560,28 +549,34 @@ hipError_t enqueue_pass_hykkt(Batch& B, const DevOpts& o, bool timed) {
     launch_decideF(B.dI, B.ninst, o, st);
     mark(3);
     solve_launches(B, kPhS, 0, true);
-    launch_hk_cg_start(B.dI, B.spaces, B.ninst, o, B.running + 2, st);
-    for (int k = 0; k <= o.cg_max + 1; ++k) {
-        hipError_t e = hipMemcpyAsync(B.hrunning + 2, B.running + 2, sizeof(int), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return e;
-        if (B.hrunning[2] == 0) break;
-        launch_hk_cg_pre(B.dI, B.spaces, st);
-        solve_launches(B, kPhS, 5);
-        launch_hk_cg_post(B.dI, B.spaces, B.ninst, o, B.running + 2, st);
+    if (hyk) {
+        launch_hk_cg_start(B.dI, B.spaces, B.ninst, o, B.rep, st);
+        for (int k = 0; k <= o.cg_max + 1; ++k) {
+            unsigned long long running = 0;
+            ++B.seq_cg;
+            const hipError_t e = wait_report(B, 1, B.seq_cg, running);
+            if (e != hipSuccess) return e;
+            if (running == 0) break;
+            launch_hk_cg_pre(B.dI, B.spaces, st);
+            solve_launches(B, kPhS, 5);
+            launch_hk_cg_post(B.dI, B.spaces, B.ninst, o, B.rep, st);
+        }
+        launch_hk_finish(B.dI, B.spaces, st);
+        solve_launches(B, kPhS, 0, false);
     }
-    launch_hk_finish(B.dI, B.spaces, st);
-    solve_launches(B, kPhS, 0, false);
     launch_phaseE(B.dI, B.spaces, B.ninst, o, st);
     mark(4);
     launch_trial(B.dI, B.spaces, st);
     eval(B, false, kSrcTrial, kPhT);
     launch_phaseT(B.dI, B.spaces, B.ninst, o, st);
-    launch_update(B.dI, B.spaces, B.ninst, o, B.running, st);
+    launch_update(B.dI, B.spaces, o, st);
     mark(5);
+    enqueue_eval(B, o);
+    mark(0);
     return hipGetLastError();
 }
 
+// Events: 6, 7 around the corrections, 8 after the evaluation.
 void enqueue_corrections(Batch& B, const DevOpts& o, bool timed) {
     hipStream_t st = B.stream;
     if (timed) (void)hipEventRecord(B.ev[6], st);
@@ -590,9 +585,43 @@ void enqueue_corrections(Batch& B, const DevOpts& o, bool timed) {
     launch_soc_step(B.dI, B.spaces, B.ninst, st);
     eval(B, false, kSrcTrial, kPhC);
     launch_soc_decide(B.dI, B.spaces, B.ninst, o, st);
-    launch_update(B.dI, B.spaces, B.ninst, o, B.running, st);
+    launch_update(B.dI, B.spaces, o, st);
     if (timed) (void)hipEventRecord(B.ev[7], st);
+    enqueue_eval(B, o);
+    if (timed) (void)hipEventRecord(B.ev[8], st);
 }
+
+// Wait for the report seq (0: the passes', 1: the conjugate gradients') and
+// return its counts.  The word is polled; every few milliseconds the stream is
+// asked whether it has drained or failed, and what a drained stream left is
+// taken as the report and its number.
+hipError_t wait_report(Batch& B, int which, uint16_t& seq, unsigned long long& word) {
+    const unsigned long long* w = B.rep.host + which;
+    auto next_query = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    for (unsigned spin = 1;; ++spin) {
+        word = __atomic_load_n(w, __ATOMIC_ACQUIRE);
+        if ((uint16_t)(word >> kRepSeq) == seq) break;
+        __builtin_ia32_pause();
+        if (spin % 256) continue;
+        sched_yield();
+        if (std::chrono::steady_clock::now() < next_query) continue;
+        const hipError_t e = hipStreamQuery(B.stream);
+        if (e == hipSuccess) {
+            word = __atomic_load_n(w, __ATOMIC_ACQUIRE);
+            seq = (uint16_t)(word >> kRepSeq);
+            break;
+        }
+        if (e != hipErrorNotReady) return e;
+        (void)hipGetLastError();
+        next_query = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    }
+    word &= (1ull << kRepSeq) - 1;
+    return hipSuccess;
+}
+
+int report_running(unsigned long long w) { return (int)(w & ((1u << kRepWaiting) - 1)); }
+int report_waiting(unsigned long long w) { return (int)((w >> kRepWaiting) & ((1u << (kRepEnded - kRepWaiting)) - 1)); }
+bool report_ended(unsigned long long w) { return (w >> kRepEnded) & 1; }
 
 // Capture one part (0: the pass, 1: the corrections) as a graph, once per
 // batch, timing mode and options.
@@ -600,6 +629,8 @@ hipError_t ensure_graph(Batch& B, const DevOpts& o, bool timed, int part) {
     const int k = (timed ? 1 : 0) + 2 * part;
     if (B.exec[k] && std::memcmp(&B.graph_opts[k], &o, sizeof(DevOpts)) == 0) return hipSuccess;
     if (B.exec[k]) {   // options changed: the kernels' arguments are part of the graph
+        const hipError_t es = hipStreamSynchronize(B.stream);   // its last replay's end may still run
+        if (es != hipSuccess) return es;
         (void)hipGraphExecDestroy(B.exec[k]);
         (void)hipGraphDestroy(B.graph[k]);
         B.exec[k] = nullptr;
@@ -607,7 +638,7 @@ hipError_t ensure_graph(Batch& B, const DevOpts& o, bool timed, int part) {
     }
     hipError_t e = hipStreamBeginCapture(B.stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
-    if (part == 0) enqueue_pass(B, o, timed);
+    if (part == 0) (void)enqueue_pass(B, o, timed);
     else enqueue_corrections(B, o, timed);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(B.stream, &g);
@@ -1349,51 +1380,67 @@ nmpc_status batch_solve(Batch& B, int warm, const nmpc_options& o, nmpc_result* 
     long passes = 0;
     int timing_lost = 0;
     bool corrections = false;   // an instance waits for second-order corrections
-    while (true) {
-        if (corrections) {
-            if (use_graph) HIP_TRY(hipGraphLaunch(B.exec[k + 2], st));
-            else enqueue_corrections(B, dop, timed);
-        }
-        if (use_graph) {
-            HIP_TRY(hipGraphLaunch(B.exec[k], st));
-        } else if (hyk) {
-            HIP_TRY(enqueue_pass_hykkt(B, dop, timed));
+    // wait for the last evaluation's report; timed phases also need their events' end
+    unsigned long long word = 0;
+    bool lost = false;
+    auto add_time = [&](int slot, int from, int to) {
+        float t = 0.0f;
+        if (hipEventElapsedTime(&t, B.ev[from], B.ev[to]) == hipSuccess) {
+            ms[slot] += t;
         } else {
-            enqueue_pass(B, dop, timed);
-            HIP_TRY(hipGetLastError());
+            (void)hipGetLastError();
+            lost = true;
         }
-        HIP_TRY(hipMemcpyAsync(B.hrunning, B.running, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
+    };
+    if (timed) (void)hipEventRecord(B.ev[6], st);
+    enqueue_eval(B, dop);
+    if (timed) (void)hipEventRecord(B.ev[7], st);
+    HIP_TRY(hipGetLastError());
+    ++B.seq;
+    HIP_TRY(wait_report(B, 0, B.seq, word));
+    if (timed) {
         HIP_TRY(hipStreamSynchronize(st));
+        add_time(0, 6, 7);
+        lost = false;
+    }
+    while (report_running(word) > 0) {
+        if (passes >= max_passes) {
+            err = "solve: pass limit reached with instances still running";
+            return NMPC_ERR_HIP;
+        }
+        corrections = report_waiting(word) > 0;
+        if (corrections) {
+            if (use_graph) {
+                HIP_TRY(hipGraphLaunch(B.exec[k + 2], st));
+            } else {
+                enqueue_corrections(B, dop, timed);
+                HIP_TRY(hipGetLastError());
+            }
+            ++B.seq;
+        }
+        if (use_graph) HIP_TRY(hipGraphLaunch(B.exec[k], st));
+        else HIP_TRY(enqueue_pass(B, dop, timed, hyk));
+        ++B.seq;
+        HIP_TRY(wait_report(B, 0, B.seq, word));
         ++passes;
         if (timed) {
-            bool lost = false;
-            for (int ph = 0; ph < 6; ++ph) {
-                if (ph == 5 && !corrections) break;
-                float t = 0.0f;
-                const hipError_t te = ph < 5 ? hipEventElapsedTime(&t, B.ev[ph], B.ev[ph + 1])
-                                             : hipEventElapsedTime(&t, B.ev[6], B.ev[7]);
-                if (te == hipSuccess) {
-                    ms[ph < 5 ? ph : 4] += t;   // corrections count as line search
-                } else {
-                    (void)hipGetLastError();
-                    lost = true;
-                }
+            HIP_TRY(hipStreamSynchronize(st));
+            for (int ph = 1; ph < 5; ++ph) add_time(ph, ph, ph + 1);
+            add_time(0, 5, 0);
+            if (corrections) {   // corrections count as line search
+                add_time(4, 6, 7);
+                add_time(0, 7, 8);
             }
             if (lost && use_graph) {   // events inside the graph did not time: launch eagerly from now on
                 B.graph_failed[k] = true;
                 use_graph = false;
                 ++timing_lost;
             }
-        }
-        corrections = B.hrunning[1] > 0;
-        if (B.hrunning[0] == 0) break;
-        if (passes >= max_passes) {
-            err = "solve: pass limit reached with instances still running";
-            return NMPC_ERR_HIP;
+            lost = false;
         }
     }
-    HIP_TRY(hipMemcpyAsync(B.hctl, B.ctl, sizeof(Ctl) * ni, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    // an instance that ended in the last evaluation opened one more iteration
+    if (report_ended(word)) ++passes;
     int worst = NMPC_OK;
     for (int i = 0; i < ni; ++i) {
         const Ctl& c = B.hctl[i];
@@ -1488,6 +1535,9 @@ nmpc_status device_closed_loop(Problem& p, int steps, const double* traj, const 
         c.phase = kPhA;
         *B.loop_ctl = c;
     }
+    // the evaluation that opens a solve and the passes after it: a solve that
+    // needs up to passes evaluations ends within the graph
+    const int bodies = std::max(passes - 1, 1);
     Batch::LoopKey key;
     std::memset(&key, 0, sizeof(key));
     key.o = dop;
@@ -1497,15 +1547,16 @@ nmpc_status device_closed_loop(Problem& p, int steps, const double* traj, const 
     key.x_out = x_out;
     key.passes = passes;
     if (!B.loop_exec || std::memcmp(&B.loop_key, &key, sizeof(key)) != 0) {
+        HIP_TRY(hipStreamSynchronize(st));
         if (B.loop_exec) (void)hipGraphExecDestroy(B.loop_exec);
         if (B.loop_graph) (void)hipGraphDestroy(B.loop_graph);
         B.loop_exec = nullptr;
         B.loop_graph = nullptr;
-        HIP_TRY(hipStreamSynchronize(st));
         HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
         hipLaunchKernelGGL(k_loop_update, dim3(1), dim3(kBlock), 0, st, B.dI, B.loop_ctr, traj, noise, u_out, x_out);
         (void)hipMemcpyAsync(B.ctl, B.loop_ctl, sizeof(Ctl), hipMemcpyHostToDevice, st);
-        for (int k = 0; k < passes; ++k) enqueue_pass(B, dop, false);
+        enqueue_eval(B, dop);
+        for (int k = 0; k < bodies; ++k) (void)enqueue_pass(B, dop, false);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(st, &g);
         if (e == hipSuccess) e = hipGraphInstantiate(&B.loop_exec, g, nullptr, nullptr, 0);
@@ -1531,21 +1582,24 @@ nmpc_status device_closed_loop(Problem& p, int steps, const double* traj, const 
     int status = NMPC_OK;
     for (int k = 0; k < steps; ++k) {
         HIP_TRY(hipGraphLaunch(B.loop_exec, st));
-        long npass = passes;
-        while (true) {
-            HIP_TRY(hipMemcpyAsync(B.hrunning, B.running, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
-            HIP_TRY(hipStreamSynchronize(st));
-            if (B.hrunning[0] == 0) break;
+        B.seq = (uint16_t)(B.seq + 1 + bodies);
+        unsigned long long word = 0;
+        HIP_TRY(wait_report(B, 0, B.seq, word));
+        long npass = bodies;
+        while (report_running(word) > 0) {
             if (npass >= max_passes) {
                 err = "closed loop: pass limit reached";
                 return NMPC_ERR_HIP;
             }
-            if (B.hrunning[1] > 0) HIP_TRY(hipGraphLaunch(B.exec[2], st));
+            if (report_waiting(word) > 0) {
+                HIP_TRY(hipGraphLaunch(B.exec[2], st));
+                ++B.seq;
+            }
             HIP_TRY(hipGraphLaunch(B.exec[0], st));
+            ++B.seq;
+            HIP_TRY(wait_report(B, 0, B.seq, word));
             ++npass;
         }
-        HIP_TRY(hipMemcpyAsync(B.hctl, B.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
         *iters_total += B.hctl[0].it;
         status = B.hctl[0].status;
         *steps_done = k + 1;
@@ -1698,7 +1752,7 @@ hipError_t assemble_here(Device& D, double mu) {
     if (e != hipSuccess) return e;
     eval(B, true, kSrcIter, kPredAll);
     DevOpts unused{};
-    launch_phaseA(B.dI, B.spaces, 1, kPredAll, unused, false, B.stream);
+    launch_phaseA(B.dI, B.spaces, 1, kPredAll, unused, false, B.rep, B.stream);
     launch_assemble(B.dI, B.spaces, kPredAll, B.stream);
     return hipGetLastError();
 }
@@ -2153,6 +2207,7 @@ void apply_variants(Device& D, const std::vector<int>& v) {
     Batch& B = *D.self;
     for (auto& L : B.fac)
         if (L.kind == kStepGroupFactor && L.step < (int)v.size()) L.variant = v[L.step];
+    (void)hipStreamSynchronize(B.stream);   // a replay's end may still run
     for (int k = 0; k < 4; ++k) {   // the kernels' variants are part of the captured graphs
         if (B.exec[k]) (void)hipGraphExecDestroy(B.exec[k]);
         if (B.graph[k]) (void)hipGraphDestroy(B.graph[k]);

@@ -79,11 +79,12 @@ struct SnView {
 //   S  solves (eqs. 22-25), remaining directions, fraction to the boundary (eq. 26)
 //   T  one trial point of the backtracking line search
 //   C  one second-order correction of the first trial point
-//   U  accepted step: update, next iteration
+//   U  accepted step: update, then as A for the next iteration
 enum Phase : int { kPhA = 0, kPhB = 1, kPhF = 2, kPhS = 3, kPhT = 4, kPhC = 5, kPhU = 6, kPhDone = 7 };
 // predicate values of the launch wrappers: a phase, or one of these
 constexpr int kPredAll = -1;       // every instance, whatever its phase
 constexpr int kPredFactor = 100;   // phases B and F
+constexpr int kPredEval = 101;     // phases A and U: evaluation follows the update of the accepted instances
 
 constexpr int kStatusRunning = -1;
 
@@ -116,12 +117,28 @@ struct Ctl {
     int hyk;
     int cg_it, cg_done, cg_total;
     double hk_gamma, cg_rr, cg_stop, cg_alpha, cg_beta;
+    int exported, pad;   // the finished block is in pinned memory
 };
+
+// Where the device reports to the host without a copy or a wait for the stream:
+// pinned words that a kernel's last workgroup stores and the host polls.  A
+// word's top 16 bits count the reports (a stale one is told from the awaited
+// one), counts are below.  cnt: device counters, zero before the first report.
+constexpr int kRepCounters = 6;   // ticket, running, waiting, ended; reports of the passes, of the CG
+struct Report {
+    unsigned* cnt;
+    unsigned long long* host;   // [0] passes, [1] conjugate gradients
+    Ctl* ctl;                   // control blocks of finished instances, per instance
+};
+// pass word: instances running (24 bits), waiting for corrections (22 bits), 1 if
+// an instance ended in this evaluation
+constexpr int kRepWaiting = 24, kRepEnded = 46, kRepSeq = 48;
 
 __host__ __device__ inline bool ctl_active(const Ctl* c, int pred) {
     if (pred == kPredAll) return true;
     const int ph = c->phase;
     if (pred == kPredFactor) return ph == kPhB || ph == kPhF;
+    if (pred == kPredEval) return ph == kPhA || ph == kPhU;
     return ph == pred;
 }
 
@@ -285,7 +302,7 @@ struct IpmSpaces {
     Space sp[kNumSpaces];
 };
 void launch_phaseA(const InstPtrs* I, const IpmSpaces& S, int ninst, int pred, const DevOpts& o, bool decide,
-                   hipStream_t st);
+                   const Report& rep, hipStream_t st);
 void launch_assemble(const InstPtrs* I, const IpmSpaces& S, int pred, hipStream_t st);
 void launch_decideF(const InstPtrs* I, int ninst, const DevOpts& o, hipStream_t st);
 void launch_phaseE(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, hipStream_t st);
@@ -296,9 +313,8 @@ void launch_phaseT(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOp
 void launch_soc_prepare(const InstPtrs* I, const IpmSpaces& S, hipStream_t st);
 void launch_soc_step(const InstPtrs* I, const IpmSpaces& S, int ninst, hipStream_t st);
 void launch_soc_decide(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, hipStream_t st);
-// update of the accepted instances, then close the pass: running count -> *running
-void launch_update(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, int* running,
-                   hipStream_t st);
+// update of the accepted instances (the evaluation after it starts their next iteration)
+void launch_update(const InstPtrs* I, const IpmSpaces& S, const DevOpts& o, hipStream_t st);
 void launch_cold_start(const InstPtrs* I, const IpmSpaces& S, double bound_push, double slack_push, double mu0,
                        bool after_eval, hipStream_t st);
 // HyKKT step (instances in phase S with the HyKKT flag): CG start after the
@@ -307,10 +323,10 @@ void launch_cold_start(const InstPtrs* I, const IpmSpaces& S, double bound_push,
 // both write the number of instances whose CG still runs to *count.  finish:
 // the right-hand side of the final solve.  from_lifted: convert the held
 // Lifted-KKT iterate.
-void launch_hk_cg_start(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, int* count,
+void launch_hk_cg_start(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, const Report& rep,
                         hipStream_t st);
 void launch_hk_cg_pre(const InstPtrs* I, const IpmSpaces& S, hipStream_t st);
-void launch_hk_cg_post(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, int* count,
+void launch_hk_cg_post(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, const Report& rep,
                        hipStream_t st);
 void launch_hk_finish(const InstPtrs* I, const IpmSpaces& S, hipStream_t st);
 void launch_hk_from_lifted(const InstPtrs* I, const IpmSpaces& S, hipStream_t st);

@@ -206,15 +206,8 @@ __global__ void __launch_bounds__(kBlock) k_phaseA(const InstPtrs* __restrict__ 
 }
 
 // Optimality errors (eqs. 27-28), termination and the barrier update.
-__global__ void __launch_bounds__(kBlock) k_decideA(const InstPtrs* __restrict__ Ia, Space sp, DevOpts o) {
-    __shared__ double sh[kMaxQ * kWaves];
-    __shared__ double A[kMaxQ];
-    const int inst = blockIdx.x;
-    const InstPtrs& I = Ia[inst];
-    Ctl* c = I.ctl;
-    if (c->phase != kPhA) return;
-    finalize_partials(I.part, nblocks_of(sp, inst), kOpsA, sh, A);
-    if (threadIdx.x != 0) return;
+__device__ inline void decide_eval(Ctl* c, const double* A, const DevOpts& o) {
+    if (c->phase == kPhU) c->it += 1;   // the accepted step starts the next iteration
     const double f = A[0];
     c->f = f;
     const double dual = A[1], sinf = A[2], prim = A[3], sbmax = A[4], sbmin = A[5];
@@ -254,6 +247,55 @@ __global__ void __launch_bounds__(kBlock) k_decideA(const InstPtrs* __restrict__
     c->eta = 0.0;
     c->fail = 0;
     c->phase = kPhB;
+}
+
+// The decision after the evaluation, then the report: the control block of an
+// instance that has finished goes to pinned memory (once), and the launch's last
+// workgroup stores the counts of the instances still running and waiting for
+// corrections.  A copy of the counts and a wait for the stream put 40 us between
+// a pass's last kernel and the next pass's first (10 x 20 column).
+__global__ void __launch_bounds__(kBlock) k_decideA(const InstPtrs* __restrict__ Ia, Space sp, DevOpts o, Report rep) {
+    __shared__ double sh[kMaxQ * kWaves];
+    __shared__ double A[kMaxQ];
+    __shared__ int fin, ended;
+    const int inst = blockIdx.x;
+    const InstPtrs& I = Ia[inst];
+    Ctl* c = I.ctl;
+    const bool act = ctl_active(c, kPredEval);
+    if (act) finalize_partials(I.part, nblocks_of(sp, inst), kOpsA, sh, A);
+    if (threadIdx.x == 0) {
+        if (act) decide_eval(c, A, o);
+        const bool done = c->phase == kPhDone;
+        fin = done && !c->exported;
+        ended = act && done;
+        if (fin) c->exported = 1;
+    }
+    __syncthreads();
+    if (fin) {
+        const int* src = reinterpret_cast<const int*>(c);
+        int* dst = reinterpret_cast<int*>(rep.ctl + inst);
+        for (int i = threadIdx.x; i < (int)(sizeof(Ctl) / sizeof(int)); i += kBlock) dst[i] = src[i];
+        __threadfence_system();
+        __syncthreads();
+    }
+    if (threadIdx.x != 0) return;
+    unsigned run = c->phase != kPhDone, wait = c->phase == kPhC, end = ended;
+    if (gridDim.x > 1) {
+        if (run) atomicAdd(rep.cnt + 1, 1u);
+        if (wait) atomicAdd(rep.cnt + 2, 1u);
+        if (end) atomicAdd(rep.cnt + 3, 1u);
+        __threadfence();
+        if (atomicAdd(rep.cnt, 1u) + 1 != gridDim.x) return;
+        __threadfence();
+        run = atomicExch(rep.cnt + 1, 0u);
+        wait = atomicExch(rep.cnt + 2, 0u);
+        end = atomicExch(rep.cnt + 3, 0u);
+        atomicExch(rep.cnt, 0u);
+    }
+    const unsigned long long seq = ++rep.cnt[4] & 0xffffu;
+    const unsigned long long word = (seq << kRepSeq) | ((unsigned long long)(end != 0) << kRepEnded) |
+                                    ((unsigned long long)wait << kRepWaiting) | run;
+    __hip_atomic_store(rep.host, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- phase B: condensed system ingredients --------------------------------------
@@ -880,31 +922,6 @@ __global__ void __launch_bounds__(kBlock) k_update(const InstPtrs* __restrict__ 
     }
 }
 
-// End of a pass: accepted instances start their next iteration; count the
-// instances still running.
-__global__ void __launch_bounds__(kBlock) k_pass_end(const InstPtrs* __restrict__ Ia, int ninst, int* running) {
-    __shared__ int cnt, csoc;
-    if (threadIdx.x == 0) cnt = csoc = 0;
-    __syncthreads();
-    int mine = 0, soc = 0;
-    for (int i = threadIdx.x; i < ninst; i += kBlock) {
-        Ctl* c = Ia[i].ctl;
-        if (c->phase == kPhU) {
-            c->it += 1;
-            c->phase = kPhA;
-        }
-        if (c->phase != kPhDone) ++mine;
-        if (c->phase == kPhC) ++soc;
-    }
-    if (mine) atomicAdd(&cnt, mine);
-    if (soc) atomicAdd(&csoc, soc);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        running[0] = cnt;
-        running[1] = csoc;
-    }
-}
-
 // cold start: push y into the bounds' interior (bound_push of magnitude and range)
 __global__ void __launch_bounds__(kBlock) k_push_bounds(const InstPtrs* __restrict__ Ia, Space sp, double bp) {
     int lb;
@@ -1350,8 +1367,8 @@ __global__ void __launch_bounds__(kBlock) k_hk_pupd(const InstPtrs* __restrict__
     if (r < I.mc) I.hk_p[r] = I.hk_r[r] + I.ctl->cg_beta * I.hk_p[r];
 }
 
-// instances whose CG still runs -> *count
-__global__ void __launch_bounds__(kBlock) k_hk_count(const InstPtrs* __restrict__ Ia, int ninst, int* count) {
+// instances whose CG still runs, to the host
+__global__ void __launch_bounds__(kBlock) k_hk_count(const InstPtrs* __restrict__ Ia, int ninst, Report rep) {
     __shared__ int cnt;
     if (threadIdx.x == 0) cnt = 0;
     __syncthreads();
@@ -1359,7 +1376,9 @@ __global__ void __launch_bounds__(kBlock) k_hk_count(const InstPtrs* __restrict_
     for (int i = threadIdx.x; i < ninst; i += kBlock) mine += hk_cg_running(Ia[i].ctl) ? 1 : 0;
     if (mine) atomicAdd(&cnt, mine);
     __syncthreads();
-    if (threadIdx.x == 0) *count = cnt;
+    if (threadIdx.x != 0) return;
+    const unsigned long long seq = ++rep.cnt[5] & 0xffffu;
+    __hip_atomic_store(rep.host + 1, (seq << kRepSeq) | (unsigned long long)cnt, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // right-hand side of the final solve: b1 + gamma_h J_c^T b2 - J_c^T x
@@ -1390,10 +1409,10 @@ __global__ void __launch_bounds__(kBlock) k_hk_from_lifted(const InstPtrs* __res
 }  // namespace
 
 void launch_phaseA(const InstPtrs* I, const IpmSpaces& S, int ninst, int pred, const DevOpts& o, bool decide,
-                   hipStream_t st) {
+                   const Report& rep, hipStream_t st) {
     const Space& sp = S.sp[kSpNML];
     hipLaunchKernelGGL(k_phaseA, dim3(sp.blocks), dim3(kBlock), 0, st, I, sp, pred);
-    if (decide) hipLaunchKernelGGL(k_decideA, dim3(ninst), dim3(kBlock), 0, st, I, sp, o);
+    if (decide) hipLaunchKernelGGL(k_decideA, dim3(ninst), dim3(kBlock), 0, st, I, sp, o, rep);
 }
 
 void launch_assemble(const InstPtrs* I, const IpmSpaces& S, int pred, hipStream_t st) {
@@ -1440,10 +1459,8 @@ void launch_soc_decide(const InstPtrs* I, const IpmSpaces& S, int ninst, const D
     hipLaunchKernelGGL(k_decideC, dim3(ninst), dim3(kBlock), 0, st, I, sp, o);
 }
 
-void launch_update(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, int* running,
-                   hipStream_t st) {
+void launch_update(const InstPtrs* I, const IpmSpaces& S, const DevOpts& o, hipStream_t st) {
     hipLaunchKernelGGL(k_update, dim3(S.sp[kSpMax].blocks), dim3(kBlock), 0, st, I, S.sp[kSpMax], o.kappa_sigma);
-    hipLaunchKernelGGL(k_pass_end, dim3(1), dim3(kBlock), 0, st, I, ninst, running);
 }
 
 void launch_cold_start(const InstPtrs* I, const IpmSpaces& S, double bound_push, double slack_push, double mu0,
@@ -1492,19 +1509,19 @@ void launch_adj_refine(int step, const InstPtrs* I, const IpmSpaces& S, double e
     }
 }
 
-void launch_hk_cg_start(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, int* count,
+void launch_hk_cg_start(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, const Report& rep,
                         hipStream_t st) {
     const Space& sp = S.sp[kSpM];
     hipLaunchKernelGGL(k_hk_cg_init, dim3(sp.blocks), dim3(kBlock), 0, st, I, sp);
     hipLaunchKernelGGL(k_hk_cg_begin, dim3(ninst), dim3(kBlock), 0, st, I, sp, o);
-    hipLaunchKernelGGL(k_hk_count, dim3(1), dim3(kBlock), 0, st, I, ninst, count);
+    hipLaunchKernelGGL(k_hk_count, dim3(1), dim3(kBlock), 0, st, I, ninst, rep);
 }
 
 void launch_hk_cg_pre(const InstPtrs* I, const IpmSpaces& S, hipStream_t st) {
     hipLaunchKernelGGL(k_hk_jt, dim3(S.sp[kSpN].blocks), dim3(kBlock), 0, st, I, S.sp[kSpN]);
 }
 
-void launch_hk_cg_post(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, int* count,
+void launch_hk_cg_post(const InstPtrs* I, const IpmSpaces& S, int ninst, const DevOpts& o, const Report& rep,
                        hipStream_t st) {
     const Space& sp = S.sp[kSpM];
     hipLaunchKernelGGL(k_hk_sp, dim3(sp.blocks), dim3(kBlock), 0, st, I, sp);
@@ -1512,7 +1529,7 @@ void launch_hk_cg_post(const InstPtrs* I, const IpmSpaces& S, int ninst, const D
     hipLaunchKernelGGL(k_hk_axpy, dim3(sp.blocks), dim3(kBlock), 0, st, I, sp);
     hipLaunchKernelGGL(k_hk_cg_beta, dim3(ninst), dim3(kBlock), 0, st, I, sp, o);
     hipLaunchKernelGGL(k_hk_pupd, dim3(sp.blocks), dim3(kBlock), 0, st, I, sp);
-    hipLaunchKernelGGL(k_hk_count, dim3(1), dim3(kBlock), 0, st, I, ninst, count);
+    hipLaunchKernelGGL(k_hk_count, dim3(1), dim3(kBlock), 0, st, I, ninst, rep);
 }
 
 void launch_hk_finish(const InstPtrs* I, const IpmSpaces& S, hipStream_t st) {
