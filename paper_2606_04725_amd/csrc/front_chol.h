@@ -82,13 +82,9 @@ __device__ __attribute__((always_inline)) inline double solve_steps(double v, do
     return v;
 }
 
-// 1 / sqrt(pivot), the hardware estimate and one third-order step; a pivot that
-// is not positive and finite counts as 1 and, when it is a pivot of the panel
-// (live), sets bad.
-__device__ __attribute__((always_inline)) inline double pivot_rsqrt(double piv, bool live, bool& bad) {
-    const bool ok = piv > 0.0 && piv < INFINITY;
-    bad |= live && !ok;
-    piv = ok ? piv : 1.0;
+// 1 / sqrt(pivot), the hardware estimate and one third-order step; not finite
+// for a pivot that is not positive and finite.
+__device__ __attribute__((always_inline)) inline double pivot_rsqrt(double piv) {
     const double y = __builtin_amdgcn_rsq(piv);
     const double e = fma(-piv, y * y, 1.0);
     return fma(fma(e, 0.375, 0.5), y * e, y);
@@ -103,11 +99,13 @@ __device__ __attribute__((always_inline)) inline double pivot_rsqrt(double piv, 
 // and used in turn, each pair waits for the scalar unit: 5400 cycles for P = 16
 // against 3000).  A lone wave issues about one instruction in 4 to 5 cycles,
 // which bounds this.  The next pivot's reciprocal root is formed while the other
-// columns take their updates.
+// columns take their updates.  A pivot that is not positive and finite makes its
+// reciprocal root, and through the updates every later one, not finite: only the
+// last of the kw is tested (tested and replaced one by one they cost 7
+// instructions of a pivot's 27).
 template <int P>
 __device__ __attribute__((always_inline)) inline bool factor_rows(double (&a)[16], int kw) {
-    bool bad = false;
-    double inv = pivot_rsqrt(wave_lane<0>(a[0]), true, bad);
+    double inv = pivot_rsqrt(wave_lane<0>(a[0])), last = inv;
     static_for<P>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
         a[k] *= inv;
@@ -119,11 +117,14 @@ __device__ __attribute__((always_inline)) inline bool factor_rows(double (&a)[16
         static_for<P - 1 - k>([&](auto jc) {
             constexpr int j = k + 1 + decltype(jc)::value;
             a[j] = fma(-a[k], b[j], a[j]);
-            if constexpr (j == k + 1) inv = pivot_rsqrt(wave_lane<j>(a[j]), j < kw, bad);
+            if constexpr (j == k + 1) {
+                inv = pivot_rsqrt(wave_lane<j>(a[j]));
+                last = j < kw ? inv : last;
+            }
         });
         __builtin_amdgcn_sched_barrier(0);   // one pivot at a time: the next ones' lane reads would fill the registers
     });
-    return bad;
+    return !(fabs(last) < INFINITY);
 }
 
 // Steps 1 and 2 of pivot columns [kb, kb + kw), kw <= 16: wave 0 holds rows kb

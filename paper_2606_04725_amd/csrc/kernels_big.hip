@@ -170,14 +170,39 @@ __device__ __attribute__((always_inline)) inline bool factor_16(double* D, doubl
 #pragma unroll
     for (int c = 0; c < 16; ++c) a[c] = D[row + (c0 + c) * kLdd];
     const bool bad = factor_rows<16>(a, 16);
-    double dg = 1.0;
+    if (c0 + lane < kBigPanel) {
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-        if (c0 + lane < kBigPanel) D[row + (c0 + c) * kLdd] = a[c];   // above the diagonal: never read again
-        dg = lane == c ? a[c] : dg;
+        for (int c = 0; c < 16; ++c) D[row + (c0 + c) * kLdd] = a[c];   // above the diagonal: never read again
     }
-    if (lane < 16) rd[c0 + lane] = 1.0 / dg;
+    __builtin_amdgcn_wave_barrier();   // the same wave reads them: program order suffices
+    if (lane < 16) rd[c0 + lane] = 1.0 / D[(c0 + lane) * (kLdd + 1)];
     return bad;
+}
+
+// The 16 columns after the first 16 (P + 1) factored ones take their update, by
+// one wave: the tiles below the diagonal at once, so that their products are
+// independent and the operands are read ahead (tile by tile, 8.5 of the panel's
+// 40 thousand cycles went here).
+template <int P>
+__device__ __attribute__((always_inline)) inline void update_next_16(double* D) {
+    constexpr int n0 = 16 * (P + 1), nt = kBigPanel / 16 - 1 - P;
+    const int lane = threadIdx.x & (kWave - 1), li = lane & 15, lk = lane >> 4;
+    f64x4 u[nt];
+#pragma unroll
+    for (int t = 0; t < nt; ++t) u[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < n0; i += 4) {
+        const double* col = D + n0 + li + (i + lk) * kLdd;
+        const double bv = col[0];
+#pragma unroll
+        for (int t = 0; t < nt; ++t) u[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(col[16 * t], bv, u[t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < nt; ++t) {
+        double* d = D + n0 + 16 * t + lk + (n0 + li) * kLdd;   // entries above the diagonal are never used
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d[4 * r] -= u[t][r];
+    }
 }
 
 // Solve the 16 columns c0 of a 16-row tile in the matrix-core layout (lane (li,
@@ -220,7 +245,7 @@ k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, 
     const bool row_wave = wv >= 1 && !rhs_wave && rw < F.m;
     const bool works = row_wave || (rhs_wave && fw);
     double* X = Xs[wv >= 1 ? wv - 1 : 0];
-    const gdouble* Lg = global(F.L);
+    gdouble* Lp = global(F.L) + (int64_t)kb * F.m;   // the panel's columns: 32-bit offsets from here
     {
         // every load of the thread (D and its wave's rows) before the first
         // store, from clamped addresses (no branch around a load)
@@ -229,10 +254,10 @@ k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, 
 #pragma unroll
         for (int s = 0; s < kDiagStage; ++s) {
             const int e = tid + s * kPanelThreads, i = min(e % kBigPanel, pw - 1), j = min(e / kBigPanel, i);
-            t[s] = Lg[(kb + i) + (int64_t)(kb + j) * F.m];
+            t[s] = Lp[kb + i + j * F.m];
         }
-        const gdouble* src = rhs_wave ? global(I.xp) + F.f + kb : Lg + (int64_t)kb * F.m + min(rw + li, F.m - 1);
-        const int64_t stride = rhs_wave ? 1 : F.m;
+        const gdouble* src = rhs_wave ? global(I.xp) + F.f + kb : Lp + min(rw + li, F.m - 1);
+        const int stride = rhs_wave ? 1 : F.m;
         const bool in = rhs_wave ? fw && li == 0 : rw + li < F.m;
 #pragma unroll
         for (int u = 0; u < 16; ++u) x[u] = src[min(4 * u + lk, pw - 1) * stride];
@@ -265,21 +290,10 @@ k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, 
         }
         __syncthreads();
         if (wv == 0) {
-            if (p + 1 < np) {   // the next 16 columns take the factored ones' update
-                const int n0 = c0 + 16;
-                for (int ti = p + 1; ti < np; ++ti) {
-                    f64x4 u = {0.0, 0.0, 0.0, 0.0};
-                    for (int i = 0; i < n0; i += 4) {
-                        const double av = D[(16 * ti + li) + (i + lk) * kLdd];
-                        const double bv = D[(n0 + li) + (i + lk) * kLdd];
-                        u = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, u, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int i = 16 * ti + 4 * r + lk, j = n0 + li;
-                        if (j <= i) D[i + j * kLdd] -= u[r];
-                    }
-                }
+            if (p + 1 < np) {
+                if (p == 0) update_next_16<0>(D);
+                else if (p == 1) update_next_16<1>(D);
+                else update_next_16<2>(D);
                 __builtin_amdgcn_wave_barrier();   // the same wave reads them next: program order suffices
             }
         } else if (works) {
@@ -295,7 +309,7 @@ k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, 
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int col = 4 * u + lk, r = rw + li;
-            if (r < F.m && col < pw) global(F.L)[r + (int64_t)(kb + col) * F.m] = X[li + col * kLdx];
+            if (r < F.m && col < pw) Lp[r + col * F.m] = X[li + col * kLdx];
         }
         if (fw) {   // each row takes the panel's product with its solution: lane (li, lk) sums 16 columns
             const double* y = Xs[kPanelRowWaves];
@@ -315,7 +329,7 @@ k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, 
             for (int j = 0; j < pw; ++j)
                 if (lane >= j && lane < pw) {
                     if (aside) scr[lane + j * kBigPanel] = D[lane + j * kLdd];
-                    else global(F.L)[(kb + lane) + (int64_t)(kb + j) * F.m] = D[lane + j * kLdd];
+                    else Lp[kb + lane + j * F.m] = D[lane + j * kLdd];
                 }
         } else if (fw && lane < pw) {
             const double v = X[lane * kLdx];

@@ -56,17 +56,17 @@ __device__ void g2s(T* dst, const T* __restrict__ src, int64_t n) {
 }
 
 // Loads of one round of a child's update block (nc x nc, lower triangle):
-// row block rb (a row per lane), columns jb + kCols wave, ..., kCols per wave.
-// A column is contiguous over the lanes, the columns' positions in the front
-// are the same for the whole wave (scalar loads), and the entries' places are
-// formed only when they are added, so the round's loads stay in flight until
+// row block rb (a row per lane), columns jb + Cols wave, ..., Cols per wave.
+// A column is contiguous over the lanes; lane u < Cols also loads the front
+// column of the wave's u-th, whose place leaves that lane through the scalar
+// unit when the entries are added, so the round's loads stay in flight until
 // then.  The first round of a row block also carries the block's entries of the
 // child's update vector (fused forward solve), on wave 0.
-constexpr int kCols = 8;
+template <int Cols>
 struct ChildRound {
-    double v[kCols];
-    int rj[kCols];   // front columns, wave-uniform
-    int ri;          // front row of the lane
+    double v[Cols];
+    int cj;   // front column of the wave's column lane % Cols
+    int ri;   // front row of the lane
     double uv;
 };
 
@@ -99,6 +99,7 @@ __device__ __attribute__((always_inline)) inline bool in_phase(const Ctl* ctl, i
 // The front is a packed lower triangle in shared memory, of order m + 1: its last
 // row holds the fused forward solve's right-hand side (zeros without it), which
 // so takes every step as one more row, and its last entry is the spare slot.
+template <int Cols>
 __device__ __attribute__((always_inline)) void factor_one(const __attribute__((address_space(4))) FactorTask* T, double eta,
                            double* F, bool fwd) {
     const int w = T->w, m = T->m;
@@ -142,23 +143,20 @@ __device__ __attribute__((always_inline)) void factor_one(const __attribute__((a
     // right-hand side after them (loads complete in the order issued; the
     // right-hand side is waited for where the rounds are about to be added)
     const int pk0 = fw && tid < w ? perm[tid] : 0;
-    auto issue = [&](ChildRound& r, RoundInfo& info) -> bool {
+    auto issue = [&](ChildRound<Cols>& r, RoundInfo& info) -> bool {
         if (pci >= nchild) return false;
         const int nc = prec.nc;
         const int64_t uo = prec.u_off, ro = prec.rel_off;
-        const int i0 = kWave * prb, j0 = pjb + kCols * wvu, i = min(i0 + lane, nc - 1);
+        const int i0 = kWave * prb, j0 = pjb + Cols * wvu, i = min(i0 + lane, nc - 1);
         const auto* uc = global(T->Uall) + uo + i;
 #pragma unroll
-        for (int u = 0; u < kCols; ++u) {
-            const int j = min(j0 + u, nc - 1);
-            r.rj[u] = uniform_at(rel + ro, j);
-            r.v[u] = uc[j * nc];
-        }
+        for (int u = 0; u < Cols; ++u) r.v[u] = uc[min(j0 + u, nc - 1) * nc];
+        r.cj = global(rel)[ro + min(j0 + lane % Cols, nc - 1)];
         r.ri = global(rel)[ro + i];
         const bool uv = fw && wvu == 0 && pjb == 0;
         r.uv = uv ? global(T->uvec)[prec.uv_off + i] : 0.0;
         info = RoundInfo{pci, nc, i0, j0, uv};
-        pjb += kCols * nw;
+        pjb += Cols * nw;
         if (pjb >= min(nc, i0 + kWave)) {   // past the row block's last column
             pjb = 0;
             if (kWave * ++prb >= nc) {
@@ -170,7 +168,7 @@ __device__ __attribute__((always_inline)) void factor_one(const __attribute__((a
         }
         return true;
     };
-    ChildRound ra, rb;
+    ChildRound<Cols> ra, rb;
     RoundInfo ia{}, ib{};
     bool ha = issue(ra, ia);
     bool hb = issue(rb, ib);
@@ -199,20 +197,21 @@ __device__ __attribute__((always_inline)) void factor_one(const __attribute__((a
     // extend-add in fixed order; children are separated by barriers (two
     // children can add into the same entry, one child's entries are distinct)
     while (ha) {
-        ChildRound rc;
+        ChildRound<Cols> rc;
         RoundInfo ic{};
         const bool hc = issue(rc, ic);
         const int i = ia.i0 + lane;
-        int at[kCols];
-        double x[kCols];
+        const int bj = ix.base(ra.cj);
+        int at[Cols];
+        double x[Cols];
 #pragma unroll
-        for (int u = 0; u < kCols; ++u) {   // entries outside the triangle go to the spare slot
+        for (int u = 0; u < Cols; ++u) {   // entries outside the triangle go to the spare slot
             const int j = ia.j0 + u;
-            at[u] = (i < ia.nc && j <= i) ? ix.base(ra.rj[u]) + ra.ri : spare;
+            at[u] = (i < ia.nc && j <= i) ? __builtin_amdgcn_readlane(bj, u) + ra.ri : spare;
             x[u] = F[at[u]];
         }
 #pragma unroll
-        for (int u = 0; u < kCols; ++u) F[at[u]] = x[u] + ra.v[u];
+        for (int u = 0; u < Cols; ++u) F[at[u]] = x[u] + ra.v[u];
         if (ia.uv && i < ia.nc) F[ix(m, ra.ri)] += ra.uv;
         if (!hb || ib.child != ia.child) __syncthreads();
         ra = rb;
@@ -278,7 +277,7 @@ k_factor_groups(const FactorTask* __restrict__ tasks, int pred, double eta_force
     const double eta = pred == kPredAll ? eta_force : global(T->ctl)->eta;
     const bool fwd = pred == kPredFactor;   // in a pass: the Newton step's right-hand side is assembled
     while (true) {
-        factor_one(T, eta, lds, fwd);
+        factor_one<8>(T, eta, lds, fwd);
         const int next = T->next;
         if (next == 0) break;
         T = record_at(tasks, next);
