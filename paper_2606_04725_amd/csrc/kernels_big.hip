@@ -38,7 +38,7 @@ constexpr int kSolveRows = 64;   // GEMV rows per workgroup
 constexpr int kSolveCols = 16;   // transposed-GEMV columns per workgroup
 constexpr int kTri = kWave * (kWave + 1);   // a staged 64 x 64 triangle, leading dimension 65
 constexpr int kStage = kWave * kWave / kBlock;   // entries of a 64 x 64 block staged per thread
-constexpr int kUpdateDepth = 8;  // 4-column steps of an update tile whose loads are in flight together
+constexpr int kUpdateDepth = 4;  // 4-column steps of an update tile whose loads are in flight while as many are multiplied
 
 struct Front {
     double* L;     // panel, leading dimension m
@@ -366,8 +366,15 @@ __device__ inline int xcd_tile(int b, int n) {
 // w - kb).  Inner, task (inst, s, ki, tile): the rest of ki's outer panel,
 // rows from ki + kw to m, columns [ki + kw, outer panel end), kw =
 // min(kBigPanel, w - ki).  Wave v computes the 32 x 32 quarter (v / 2, v % 2).
+// Two waves per SIMD at least, so that the accumulators stay in the vector
+// registers: copied to the accumulation registers and back in every round, the
+// round's loads behind branches and not ahead of the products, and the tile's
+// own entries read last, the outer launches of a 32 x 32 x 50 plate took 72.9 us
+// and the inner ones 14.2; now 57.8 and 11.2 (the outer ones at 0.3 of the rate
+// of a large matrix product: tiles of neighbouring launches' ends leave compute
+// units idle, and the panel's rows come from beyond the XCD's L2).
 template <bool Inner>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock, 2)
 k_big_update(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
     const BigTask tk = tasks[xcd_tile(blockIdx.x, gridDim.x)];
     const InstPtrs& I = Ia[tk.inst];
@@ -393,53 +400,126 @@ k_big_update(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks,
         tj = tk.b - ti * (ti + 1) / 2;
     }
     const int cmax = Inner ? min(F.w, k0 - k0 % kBigOuter + kBigOuter) : F.m;
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int li = lane & 15, lk = lane >> 4;
     const int i0 = t0 + kTile * ti + 32 * (wv >> 1);
     const int j0 = t0 + kTile * tj + 32 * (wv & 1);
     if (j0 >= cmax || i0 >= F.m || j0 > i0 + 31) return;
-    f64x4 acc[2][2];
+    // Every load is from a clamped address: entries past the front or above the
+    // diagonal compute something that is not stored (above the diagonal there is
+    // no storage where a tile crosses from the panel into the update block, so
+    // those read their column's diagonal entry).  The tile's own entries are
+    // loaded before the products.
+    const int m = F.m;
+    gdouble* cp[2];
+    int jb[2];
+    f64x4 acc[2][2], c[2][2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        jb[b] = min(j0 + 16 * b + li, cmax - 1);
+        cp[b] = global(at(F, jb[b], jb[b])) - jb[b];   // entry (i, j), i >= j, at cp[i]
+    }
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-    // kUpdateDepth steps of 4 columns are loaded before their products, so the
-    // loads of a step overlap one another instead of each waiting in turn
-    // (columns past kw load zeros and add nothing)
-    const gdouble* Lg = global(F.L);
-    bool rok[2], cok[2];
+        for (int b = 0; b < 2; ++b) {
+            acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int a = 0; a < 2; ++a) rok[a] = i0 + 16 * a + li < F.m;
+            for (int r = 0; r < 4; ++r) c[a][b][r] = cp[b][max(min(i0 + 16 * a + 4 * r + lk, m - 1), jb[b])];
+        }
+    // kUpdateDepth steps of 4 columns are in flight while the ones before them
+    // are multiplied; a lane's place in a step is a 32-bit offset from the step's
+    // first column, which is the same for the wave
+    int ao[2], bo[2];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) cok[b] = j0 + 16 * b + li < cmax;
-    for (int k4 = 0; k4 < kw; k4 += 4 * kUpdateDepth) {
-        double av[kUpdateDepth][2], bv[kUpdateDepth][2];
+    for (int a = 0; a < 2; ++a) ao[a] = lk * m + min(i0 + 16 * a + li, m - 1);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) bo[b] = lk * m + min(j0 + 16 * b + li, cmax - 1);
+    const gdouble* Lk = global(F.L) + (int64_t)k0 * m;
+    struct Steps {
+        double a[kUpdateDepth][2], b[kUpdateDepth][2];
+    };
+    auto load = [&](Steps& s, int k4) {   // k4 + 4 kUpdateDepth <= kw
+        const gdouble* col = Lk + (int64_t)k4 * m;
+#pragma unroll
+        for (int u = 0; u < kUpdateDepth; ++u, col += 4 * m) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a) s.a[u][a] = col[ao[a]];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) s.b[u][b] = col[bo[b]];
+        }
+    };
+    auto load_tail = [&](Steps& s, int k4) {   // columns past kw count as zero
 #pragma unroll
         for (int u = 0; u < kUpdateDepth; ++u) {
-            const int kk = k4 + 4 * u + lk;
-            const gdouble* col = Lg + (int64_t)(k0 + kk) * F.m;
+            const int k = k4 + 4 * u + lk;
+            const gdouble* col = Lk + (int64_t)min(k, kw - 1) * m;
 #pragma unroll
-            for (int a = 0; a < 2; ++a) av[u][a] = (kk < kw && rok[a]) ? col[i0 + 16 * a + li] : 0.0;
+            for (int a = 0; a < 2; ++a) {
+                const double x = col[ao[a] - lk * m];
+                s.a[u][a] = k < kw ? x : 0.0;
+            }
 #pragma unroll
-            for (int b = 0; b < 2; ++b) bv[u][b] = (kk < kw && cok[b]) ? col[j0 + 16 * b + li] : 0.0;
+            for (int b = 0; b < 2; ++b) {
+                const double x = col[bo[b] - lk * m];
+                s.b[u][b] = k < kw ? x : 0.0;
+            }
         }
+    };
+    auto multiply = [&](const Steps& s) {
 #pragma unroll
         for (int u = 0; u < kUpdateDepth; ++u)
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][a], bv[u][b], acc[a][b], 0, 0, 0);
+                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(s.a[u][a], s.b[u][b], acc[a][b], 0, 0, 0);
+    };
+    constexpr int kStep = 4 * kUpdateDepth;
+    const int full = kw / kStep, rest = kw % kStep;   // kw >= 1
+    Steps s0, s1;
+    if (full == 0) {
+        load_tail(s0, 0);
+        multiply(s0);
+    } else {
+        load(s0, 0);
+        int q = 1;
+        for (; q + 1 < full; q += 2) {
+            load(s1, q * kStep);
+            multiply(s0);
+            load(s0, (q + 1) * kStep);
+            multiply(s1);
+        }
+        if (q < full) {
+            load(s1, q * kStep);
+            multiply(s0);
+            if (rest) load_tail(s0, full * kStep);
+            multiply(s1);
+            if (rest) multiply(s0);
+        } else {
+            if (rest) load_tail(s1, full * kStep);
+            multiply(s0);
+            if (rest) multiply(s1);
+        }
     }
+    if (i0 + 32 <= m && j0 + 32 <= cmax && j0 + 31 <= i0) {   // the whole tile is stored
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = i0 + 16 * a + 4 * r + lk, j = j0 + 16 * b + li;
-                if (i < F.m && j <= i && j < cmax) *global(at(F, i, j)) -= acc[a][b][r];
-            }
+                for (int r = 0; r < 4; ++r) cp[b][i0 + 16 * a + 4 * r + lk] = c[a][b][r] - acc[a][b][r];
+    } else {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = i0 + 16 * a + 4 * r + lk, j = j0 + 16 * b + li;
+                    if (i < m && j <= i && j < cmax) cp[b][i] = c[a][b][r] - acc[a][b][r];
+                }
+    }
 }
 
 // ---- solves ------------------------------------------------------------------------

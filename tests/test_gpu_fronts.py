@@ -8,6 +8,7 @@ import sys
 import numpy as np
 import pytest
 import scipy.linalg as sla
+import scipy.sparse as sp
 
 from paper_2606_04725_amd import nmpc as N
 
@@ -38,8 +39,8 @@ def _matrix(pat, n, seed):
 def _check(p, seed, name):
     p.analyze()
     z = p.export_symbolic()
-    sp, rp, rows, perm = z["snode_ptr"], z["snode_rows_ptr"], z["snode_rows"], z["perm"]
-    w, m = np.diff(sp), np.diff(rp)
+    start, rp, rows, perm = z["snode_ptr"], z["snode_rows_ptr"], z["snode_rows"], z["perm"]
+    w, m = np.diff(start), np.diff(rp)
     large = m > 200   # such a front's packed triangle exceeds shared memory
     _note(f"{name}: {large.sum()} of {m.size} fronts large, up to {m.max()} rows and {w.max()} columns")
     kv, K = _matrix(p.patterns(), p.n, seed)
@@ -57,7 +58,7 @@ def _check(p, seed, name):
         P = lv[off:off + m[s] * w[s]].reshape(w[s], m[s]).T
         off += m[s] * w[s]
         R = rows[rp[s]:rp[s + 1]]
-        want = L[np.ix_(R, np.arange(sp[s], sp[s + 1]))]
+        want = L[np.ix_(R, np.arange(start[s], start[s + 1]))]
         low = np.tril(np.ones((m[s], w[s]), bool))
         d = np.max(np.abs(P[low] - want[low]))
         assert d <= tol, (s, int(w[s]), int(m[s]), d, tol)
@@ -73,6 +74,33 @@ def _check(p, seed, name):
 def test_large_front_factor_and_solve(G, H):
     m, w = _check(N.Problem(N.plate_structure(G, H, 0.01)), 7 * G + H, f"plate {G} x {G} x {H}")
     assert np.any(m > 200)
+
+
+def test_front_wider_than_an_outer_panel():
+    """Fronts of more than 512 columns with rows below: the trailing update after
+    the first 512 columns crosses from the panel into the update block."""
+    p = N.Problem(N.plate_structure(28, 37, 0.01))
+    p.analyze()
+    z = p.export_symbolic()
+    w, m = np.diff(z["snode_ptr"]), np.diff(z["snode_rows_ptr"])
+    assert np.any((w > 512) & (m > w))
+    _note(f"plate 28 x 28 x 37: widest front {w.max()} columns, {m.max()} rows at most")
+    pat = p.patterns()
+    rng = np.random.default_rng(5)
+    r, c = pat["k_rows"].astype(np.int64), pat["k_cols"].astype(np.int64)
+    v = rng.uniform(-1.0, 1.0, r.size)
+    off = r != c
+    weight = np.bincount(r[off], np.abs(v[off]), p.n) + np.bincount(c[off], np.abs(v[off]), p.n)
+    v[~off] = 1.0 + weight[r[~off]]
+    ok, _ = p.factor(v, eta=0.25)
+    assert ok
+    b = rng.normal(size=p.n)
+    x = p.linear_solve(b)
+    M = sp.coo_matrix((np.concatenate([v, v[off]]), (np.concatenate([r, c[off]]), np.concatenate([c, r[off]]))),
+                      shape=(p.n, p.n)).tocsr() + 0.25 * sp.identity(p.n)
+    # backward error of a Cholesky solve: at most the largest front's order times the unit roundoff
+    back = np.max(np.abs(M @ x - b)) / (np.max(np.abs(M).sum(1)) * np.max(np.abs(x)) + np.max(np.abs(b)))
+    assert back <= m.max() * U, back
 
 
 @pytest.mark.parametrize("trays,H", [(4, 1), (6, 3), (10, 20), (23, 41), (60, 24)])
