@@ -456,9 +456,9 @@ nmpc_status nmpc_adjoint_dev(nmpc_problem* p, const double* seed_u1, const doubl
  * of traj (steps x H, NULL = kept); the setpoint is kept; then the problem is
  * re-solved warm (as nmpc_solve with warm = 1).  The parameter update, the
  * reset of the interior-point control block and passes_per_step passes of the
- * method are one captured graph, replayed once per step; the host then reads
- * two integers and replays single passes until the solve stops, so a step
- * costs one host round trip when it converges within passes_per_step passes.
+ * method are one captured graph, replayed once per step; the host then polls
+ * its report and replays single passes until the solve stops, so a step costs
+ * one host round trip when it converges within passes_per_step passes.
  * Every pointer is a device address on the handle's GPU owned by the caller;
  * stream as for the _dev entry points.  Requires a held Lifted-KKT solution
  * for the current parameters (BAD_ORDER otherwise) and options with

@@ -295,7 +295,7 @@ __device__ __attribute__((always_inline)) inline void update_block(double* F, Pa
 // that holds a right-hand side is solved (and updated) like any other: the
 // factored columns of that row are the forward substitution.
 // A pivot that is not positive and finite sets *fail (eq. 12: the matrix is not
-// numerically positive definite); the arithmetic continues with pivot 1.
+// numerically positive definite); the values are not finite from there on.
 // spare: a shared-memory slot (an index into F) that takes what lies outside.
 __device__ __attribute__((always_inline)) inline void partial_cholesky(double* F, PackedIdx ix, int w, int spare, int* fail) {
     constexpr int P = 16;

@@ -17,11 +17,11 @@
 // v_mfma_f64_16x16x4f64 per 4 columns); the outer panel keeps the update
 // blocks' read-modify-write traffic to one pass per kBigOuter columns.
 //
-// Solves: forward, one workgroup gathers the right-hand side and the children's
-// update vectors and solves with the diagonal block, then the rows below are a
-// GEMV split over workgroups; backward, the transposed GEMV with the rows below
-// is split over column blocks, then one workgroup solves with the transposed
-// diagonal block.
+// Solves: forward, the right-hand side and the children's update vectors are
+// gathered by rows over workgroups, then chunk by chunk one workgroup solves with
+// the diagonal block and the rows after it are a GEMV split over workgroups;
+// backward, the transposed GEMV with the rows below is split over column blocks,
+// then chunk by chunk one workgroup solves with the transposed diagonal block.
 #include <cmath>
 
 #include "kernels.h"
@@ -32,7 +32,7 @@ namespace nmpc {
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kRowBlock = kBlock / 4;   // TRSM rows per workgroup (four lanes per row)
+constexpr int kRowBlock = kBlock / 4;   // rows below a panel per workgroup
 constexpr int kTile = 64;        // trailing-update tile
 constexpr int kSolveRows = 64;   // GEMV rows per workgroup
 constexpr int kSolveCols = 16;   // transposed-GEMV columns per workgroup
@@ -156,7 +156,11 @@ k_big_assemble(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ task
 // with several workgroups goes to dfac, from where the next update launch puts
 // it into the panel: another workgroup may still have to read the original.
 // A pivot that is not positive and finite sets the instance's failure flag
-// (eq. 12) and the arithmetic continues with pivot 1.
+// (eq. 12) and the factor's values are not finite from there on.
+// Wave 0's chain bounds it: of 40 thousand cycles 19 went to the four 16-column
+// factorizations, 8 to the loads.  16.9 us per launch in the Cholesky of the 28 x
+// 37 plate (20.3 with a test for every pivot and the next columns' tiles one
+// after another; diagonal block and rows in launches of their own took 45).
 constexpr int kPanelRowWaves = 4;
 constexpr int kPanelThreads = (kPanelRowWaves + 2) * kWave;
 constexpr int kLdx = 17;   // leading dimension of a wave's 16 rows in shared memory
@@ -603,7 +607,7 @@ k_bigfwd_gather(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tas
 // blocks of 64 columns: the block's triangle staged in shared memory, wave 0
 // solves it while the other waves load the entries of the chunk's later rows,
 // one per thread, which then take the block's update.  The next block's triangle
-// is loaded ahead (Cholesky of the 28 x 37 plate: 48 us per launch with the loads
+// is loaded ahead (28 x 37 plate: 13.6 us per launch; 47.5 with the loads
 // after the solve and a division per column).
 __global__ void __launch_bounds__(kBlock)
 k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
@@ -654,7 +658,8 @@ k_bigfwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks,
 // forward, task a = chunk, b = row block: 64 rows i >= c1, v[i] -= L[i, c0:c1)
 // x[c0, c1), in xp (i < w) or in the update vector (i >= w); a row per lane, a
 // quarter of the chunk's columns per wave, the quarters added in order (a row
-// per thread over the whole chunk left most of the chip idle: 10.5 us per launch).
+// per thread over the whole chunk left most of the chip idle: 10.5 us per launch,
+// now 5.7).
 __global__ void __launch_bounds__(kBlock)
 k_bigfwd_gemv(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
     static_assert(kSolveRows == kWave && kChunk % (kBlock / kWave) == 0, "a row per lane, equal shares of the columns");
@@ -689,7 +694,7 @@ k_bigfwd_gemv(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks
 // block's kSolveCols columns: the rows' solution is gathered into shared memory
 // once (kBelow rows at a time), then wave v takes columns k0 + v, k0 + v + 4,
 // ..., all at once, lanes over the rows (a butterfly sums the lanes).  Gathered
-// per column it took 18 us per launch (32 x 32 x 50 plate).
+// per column it took 18 us per launch (32 x 32 x 50 plate), now 9.
 constexpr int kBelow = 2048;
 __global__ void __launch_bounds__(kBlock)
 k_bigbwd_below(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
@@ -757,7 +762,7 @@ __device__ inline bool bsum_live(const Front& F, int c) { return F.m > F.w || (c
 // the other waves bring its rows of the chunk's earlier columns into shared
 // memory (coalesced), from where a thread per column takes the update.  With each
 // thread reading its own column, 64 cache lines per load, a launch took 26 us
-// (32 x 32 x 50 plate).  Writes xp and the unpermuted solution.
+// (32 x 32 x 50 plate), now 13.  Writes xp and the unpermuted solution.
 __global__ void __launch_bounds__(kBlock)
 k_bigbwd_tri(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred, int which) {
     constexpr int kWaves = kBlock / kWave - 1;   // that load
