@@ -133,6 +133,7 @@ struct Batch {
     std::vector<GenFns> gen;
     Report rep{};                  // device counters, pinned words and control blocks (hctl)
     uint16_t seq = 0, seq_cg = 0;  // reports enqueued
+    bool reports_open = false;     // a call that waits for them is running, or ended in an error
     Ctl* hctl = nullptr;           // pinned
     hipEvent_t ev[9] = {};
     // captured graphs, index timed + 2 * part: part 0 the pass, part 1 the
@@ -616,6 +617,19 @@ hipError_t wait_report(Batch& B, int which, uint16_t& seq, unsigned long long& w
         next_query = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
     }
     word &= (1ull << kRepSeq) - 1;
+    return hipSuccess;
+}
+
+// Before a call's first report: after one that ended in an error some reports
+// may have been enqueued uncounted, so their numbers are taken from the words.
+hipError_t open_reports(Batch& B) {
+    if (B.reports_open) {
+        const hipError_t e = hipStreamSynchronize(B.stream);
+        if (e != hipSuccess) return e;
+        B.seq = (uint16_t)(B.rep.host[0] >> kRepSeq);
+        B.seq_cg = (uint16_t)(B.rep.host[1] >> kRepSeq);
+    }
+    B.reports_open = true;
     return hipSuccess;
 }
 
@@ -1332,6 +1346,7 @@ nmpc_status batch_solve(Batch& B, int warm, const nmpc_options& o, nmpc_result* 
     const bool timed = o.timing != 0;
     const bool hyk = o.kkt == NMPC_KKT_HYKKT;
     hipStream_t st = B.stream;
+    HIP_TRY(open_reports(B));
     for (int i = 0; i < ni; ++i) {
         Ctl c{};
         c.hyk = hyk ? 1 : 0;
@@ -1441,6 +1456,7 @@ nmpc_status batch_solve(Batch& B, int warm, const nmpc_options& o, nmpc_result* 
     }
     // an instance that ended in the last evaluation opened one more iteration
     if (report_ended(word)) ++passes;
+    B.reports_open = false;
     int worst = NMPC_OK;
     for (int i = 0; i < ni; ++i) {
         const Ctl& c = B.hctl[i];
@@ -1576,6 +1592,7 @@ nmpc_status device_closed_loop(Problem& p, int steps, const double* traj, const 
     }
     D.adj_ready = false;
     D.gamma_last = o.gamma;
+    HIP_TRY(open_reports(B));
     HIP_TRY(join_in(D, caller));
     HIP_TRY(hipMemsetAsync(B.loop_ctr, 0, sizeof(int), st));   // not captured
     const long max_passes = (long)(o.max_iter + 1) * (2L * o.ls_max + o.soc_max + 64) + 8;
@@ -1612,6 +1629,7 @@ nmpc_status device_closed_loop(Problem& p, int steps, const double* traj, const 
     if (traj) HIP_TRY(hipMemcpyAsync(p.traj.data(), I.zF, p.traj.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     HIP_TRY(join_out(D, caller));
+    B.reports_open = false;
     return status;
 }
 
