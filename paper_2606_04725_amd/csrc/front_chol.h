@@ -86,7 +86,7 @@ __device__ __attribute__((always_inline)) inline double solve_steps(double v, do
 // for a pivot that is not positive and finite.
 __device__ __attribute__((always_inline)) inline double pivot_rsqrt(double piv) {
     const double y = __builtin_amdgcn_rsq(piv);
-    const double e = fma(-piv, y * y, 1.0);
+    const double h = y * y, e = fma(-piv, fma(y, y, -h), fma(-piv, h, 1.0));   // 1 - piv y^2, the square's rounding included
     return fma(fma(e, 0.375, 0.5), y * e, y);
 }
 
@@ -196,8 +196,8 @@ __device__ __attribute__((always_inline)) inline void trapezoid_tile(double* F, 
     const int ra = min(i0 + li, m - 1), rb = min(j0 + li, m - 1);
     const int jc = j0 + li, cb = ix.base(min(jc, w - 1));
     int at[4];
-    f64x4 acc;
-    double av[4], bv[4];
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};   // from zero: its roundings are the products' size, not the entries'
+    double own[4], av[4], bv[4];
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4) {
         const double* col = F + ix.base(kb + 4 * s4 + lk);
@@ -208,12 +208,12 @@ __device__ __attribute__((always_inline)) inline void trapezoid_tile(double* F, 
     for (int r = 0; r < 4; ++r) {
         const int ir = i0 + 4 * r + lk;
         at[r] = (ir < m && jc <= ir && jc < w) ? cb + ir : spare;
-        acc[r] = F[at[r]];
+        own[r] = F[at[r]];
     }
 #pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[s4], bv[s4], acc, 0, 0, 0);
+    for (int s4 = 0; s4 < 4; ++s4) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s4], bv[s4], acc, 0, 0, 0);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) F[at[r]] = acc[r];
+    for (int r = 0; r < 4; ++r) F[at[r]] = own[r] - acc[r];
 }
 
 // The update block of the front (rows and columns [w, m)) minus L21 L21^T,
@@ -235,7 +235,7 @@ __device__ __attribute__((always_inline)) inline void update_block(double* F, Pa
         const int i0 = w + 16 * ti, j0 = w + 32 * tp;
         const int ra = min(i0 + li, m - 1), rb0 = min(j0 + li, m - 1), rb1 = min(j0 + 16 + li, m - 1);
         int at[2][4];
-        f64x4 acc[2][2];
+        f64x4 own[2], acc[2][2];   // from zero, as in the tiles of the panels
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int jc = j0 + 16 * q + li, cb = ix.base(min(jc, m - 1));
@@ -243,8 +243,8 @@ __device__ __attribute__((always_inline)) inline void update_block(double* F, Pa
             for (int r = 0; r < 4; ++r) {
                 const int ir = i0 + 4 * r + lk;
                 at[q][r] = (ir < m && jc <= ir) ? cb + ir : spare;
-                acc[q][0][r] = F[at[q][r]];
-                acc[q][1][r] = 0.0;
+                own[q][r] = F[at[q][r]];
+                acc[q][0][r] = acc[q][1][r] = 0.0;
             }
         }
         // eight columns at a time: six operands, then the products; rows past
@@ -259,7 +259,7 @@ __device__ __attribute__((always_inline)) inline void update_block(double* F, Pa
                 a[u] = col[ra];
                 b0[u] = col[rb0];
                 b1[u] = col[rb1];
-                a[u] = kk < w ? -a[u] : 0.0;
+                a[u] = kk < w ? a[u] : 0.0;
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -270,7 +270,7 @@ __device__ __attribute__((always_inline)) inline void update_block(double* F, Pa
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) F[at[q][r]] = acc[q][0][r] + acc[q][1][r];
+            for (int r = 0; r < 4; ++r) F[at[q][r]] = own[q][r] - (acc[q][0][r] + acc[q][1][r]);
         tp += nw;
         while (ti < nt && tp > ti / 2) {
             tp -= ti / 2 + 1;

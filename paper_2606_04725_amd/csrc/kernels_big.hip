@@ -284,13 +284,14 @@ k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, 
         if (wv == 0) {
             bad |= factor_16(D, rd, c0);
         } else if (works) {   // the solved blocks' part, while wave 0 factors
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] = X[(4 * r + lk) + (c0 + li) * kLdx];
+            // (summed from zero: its roundings are the products' size, not the entries')
             for (int i = 0; i < c0; i += 4) {
-                const double av = -X[li + (i + lk) * kLdx];
+                const double av = X[li + (i + lk) * kLdx];
                 const double bv = D[(c0 + li) + (i + lk) * kLdd];
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
             }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = X[(4 * r + lk) + (c0 + li) * kLdx] - acc[r];
         }
         __syncthreads();
         if (wv == 0) {
