@@ -1216,11 +1216,9 @@ nmpc_status device_init(Problem& p, std::string& err) {
     DTRY(upload_c(A, I.lb, st.lb));
     DTRY(upload_c(A, I.ub, st.ub));
     DTRY(upload_c(A, I.perm, sy.perm));
-    DTRY(upload_c(A, I.S.sn_ptr, sy.sn_ptr));
     DTRY(upload_c(A, I.S.rows_ptr, sy.sn_rows_ptr));
     DTRY(upload_c(A, I.S.rows, sy.sn_rows));
     DTRY(upload_c(A, I.S.child_ptr, sy.child_ptr));
-    DTRY(upload_c(A, I.S.child_list, sy.child_list));
     {
         std::vector<ChildRec> rec(sy.child_list.size());
         for (size_t k = 0; k < rec.size(); ++k) {
@@ -1232,15 +1230,10 @@ nmpc_status device_init(Problem& p, std::string& err) {
         DTRY(upload_c(A, I.S.child_rec, rec));
         D.child_rec = std::move(rec);
     }
-    DTRY(upload_c(A, I.S.l_off, sy.l_off));
-    DTRY(upload_c(A, I.S.u_off, u_off));
     DTRY(upload_c(A, I.S.uv_off, sy.uv_off));
-    DTRY(upload_c(A, I.S.rel_off, sy.rel_off));
     DTRY(upload_c(A, I.S.rel, sy.rel));
-    DTRY(upload_c(A, I.S.k_ptr, sy.k_ptr));
     DTRY(upload_c(A, I.S.k_fpos, k_fpos));
     DTRY(upload_c(A, I.kcol_ptr, sy.kcol_ptr));
-    DTRY(upload_c(A, I.S.fused, fused));
     DTRY(upload_c(A, I.S.big_col, big_col));
     DTRY(upload_c(A, I.S.big_ptr, big_ptr));
     DTRY(upload_c(A, I.S.big_ent, big_ent));

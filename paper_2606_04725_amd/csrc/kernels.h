@@ -41,7 +41,7 @@ struct StageConst {
 };
 
 // Per-supernode read-only symbolic data of one instance.
-// What the extend-add of the child at one position of child_list reads:
+// What the extend-add of one child reads:
 // its update block (u_off), its rows' positions in the parent (rel_off), its
 // update vector (uv_off) and its number of rows below its columns (nc).
 struct ChildRec {
@@ -50,20 +50,13 @@ struct ChildRec {
 };
 
 struct SnView {
-    const int32_t* sn_ptr;
     const int64_t* rows_ptr;
     const int32_t* rows;
     const int32_t* child_ptr;
-    const int32_t* child_list;
-    const ChildRec* child_rec;    // per child_list position
-    const int64_t* l_off;
-    const int64_t* u_off;
+    const ChildRec* child_rec;    // the children of supernode s from child_ptr[s]
     const int64_t* uv_off;
-    const int64_t* rel_off;
     const int32_t* rel;
-    const int32_t* k_ptr;
     const int32_t* k_fpos;
-    const int32_t* fused;         // 1: the Newton step's forward solve runs inside the factor kernel
     // children of the large supernodes (factorization or solves): entries of row
     // and column j are [big_ptr[big_col[s] + j], big_ptr[big_col[s] + j + 1])
     const int32_t* big_col;
