@@ -26,13 +26,13 @@
 
 #include "kernels.h"
 #include "front_chol.h"
+#include "front_rules.h"
 
 namespace nmpc {
 
 namespace {
 
 constexpr int kWave = 64;
-constexpr int kRowBlock = kBlock / 4;   // rows below a panel per workgroup
 constexpr int kTile = 64;        // trailing-update tile
 constexpr int kSolveRows = 64;   // GEMV rows per workgroup
 constexpr int kSolveCols = 16;   // transposed-GEMV columns per workgroup
@@ -161,7 +161,6 @@ k_big_assemble(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ task
 // factorizations, 8 to the loads.  16.9 us per launch in the Cholesky of the 28 x
 // 37 plate (20.3 with a test for every pivot and the next columns' tiles one
 // after another; diagonal block and rows in launches of their own took 45).
-constexpr int kPanelRowWaves = 4;
 constexpr int kPanelThreads = (kPanelRowWaves + 2) * kWave;
 constexpr int kLdx = 17;   // leading dimension of a wave's 16 rows in shared memory
 constexpr int kLdd = kBigPanel + 1;
@@ -233,7 +232,7 @@ __device__ __attribute__((always_inline)) inline void solve_16(f64x4& acc, const
 
 __global__ void __launch_bounds__(kPanelThreads)
 k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
-    static_assert(kBigPanel == kWave && kRowBlock == 16 * kPanelRowWaves, "a lane per row of D, 16 rows per wave");
+    static_assert(kBigPanel == kWave, "a lane per row of D");
     __shared__ double D[kTri];
     __shared__ double rd[kBigPanel];
     __shared__ double Xs[kPanelRowWaves + 1][kLdx * kBigPanel];
@@ -245,7 +244,7 @@ k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, 
     const bool fw = fwd_fused(tk, pred);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, li = lane & 15, lk = lane >> 4;
     const bool rhs_wave = wv == kPanelRowWaves + 1;
-    const int rw = kb + pw + tk.b * kRowBlock + 16 * (wv - 1);   // first row of a row wave
+    const int rw = panel_first_row(kb, pw, tk.b, wv);   // first row of a row wave
     const bool row_wave = wv >= 1 && !rhs_wave && rw < F.m;
     const bool works = row_wave || (rhs_wave && fw);
     double* X = Xs[wv >= 1 ? wv - 1 : 0];
