@@ -82,11 +82,14 @@ __device__ __attribute__((always_inline)) inline double solve_steps(double v, do
     return v;
 }
 
-// 1 / sqrt(pivot), the hardware estimate and one third-order step; not finite
-// for a pivot that is not positive and finite.
+// 1 / sqrt(pivot), the hardware estimate y and one third-order step in 1 - pivot
+// y^2; not finite for a pivot that is not positive and finite.  The product
+// pivot y is the size of the root, so that it and its rounding, which the
+// residual takes in, are normal numbers for every positive pivot: y^2 overflows
+// for pivots below 5.6e-309, and is subnormal itself for those above 4.5e307.
 __device__ __attribute__((always_inline)) inline double pivot_rsqrt(double piv) {
     const double y = __builtin_amdgcn_rsq(piv);
-    const double h = y * y, e = fma(-piv, fma(y, y, -h), fma(-piv, h, 1.0));   // 1 - piv y^2, the square's rounding included
+    const double p = piv * y, e = fma(-fma(piv, y, -p), y, fma(-p, y, 1.0));
     return fma(fma(e, 0.375, 0.5), y * e, y);
 }
 
