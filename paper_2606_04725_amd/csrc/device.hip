@@ -132,8 +132,7 @@ struct Batch {
     // instances with another tag)
     std::vector<GenFns> gen;
     Report rep{};                  // device counters, pinned words and control blocks (hctl)
-    uint16_t seq = 0, seq_cg = 0;  // reports enqueued
-    bool reports_open = false;     // a call that waits for them is running, or ended in an error
+    ReportCount reports;
     Ctl* hctl = nullptr;           // pinned
     hipEvent_t ev[9] = {};
     // captured graphs, index timed + 2 * part: part 0 the pass, part 1 the
@@ -527,7 +526,7 @@ void enqueue_eval(Batch& B, const DevOpts& o) {
     launch_phaseA(B.dI, B.spaces, B.ninst, kPredEval, o, true, B.rep, B.stream);
 }
 
-hipError_t wait_report(Batch& B, int which, uint16_t& seq, unsigned long long& word);
+hipError_t wait_report(Batch& B, int which, unsigned long long& word);
 
 // One pass of Algorithm 2 over every running instance, from the condensed
 // system to the evaluation of the next iterate.  An instance whose first trial
@@ -553,11 +552,12 @@ hipError_t enqueue_pass(Batch& B, const DevOpts& o, bool timed, bool hyk = false
     if (hyk) {
         launch_hk_cg_start(B.dI, B.spaces, B.ninst, o, B.rep, st);
         for (int k = 0; k <= o.cg_max + 1; ++k) {
-            unsigned long long running = 0;
-            ++B.seq_cg;
-            const hipError_t e = wait_report(B, 1, B.seq_cg, running);
+            unsigned long long word = 0;
+            hipError_t e = hipGetLastError();   // a launch that failed makes no report
+            ++B.reports.last[1];
+            if (e == hipSuccess) e = wait_report(B, 1, word);
             if (e != hipSuccess) return e;
-            if (running == 0) break;
+            if (report_running(word) == 0) break;
             launch_hk_cg_pre(B.dI, B.spaces, st);
             solve_launches(B, kPhS, 5);
             launch_hk_cg_post(B.dI, B.spaces, B.ninst, o, B.rep, st);
@@ -592,50 +592,49 @@ void enqueue_corrections(Batch& B, const DevOpts& o, bool timed) {
     if (timed) (void)hipEventRecord(B.ev[8], st);
 }
 
-// Wait for the report seq (0: the passes', 1: the conjugate gradients') and
-// return its counts.  The word is polled; every few milliseconds the stream is
-// asked whether it has drained or failed, and what a drained stream left is
-// taken as the report and its number.
-hipError_t wait_report(Batch& B, int which, uint16_t& seq, unsigned long long& word) {
+// Wait for the last report enqueued (0: the passes', 1: the conjugate
+// gradients').  The word is polled; every few milliseconds the stream is asked
+// whether it has drained or failed.  The caller has checked the launches before
+// it; an error that is there already is not the query's and stays.
+hipError_t wait_report(Batch& B, int which, unsigned long long& word) {
     const unsigned long long* w = B.rep.host + which;
     auto next_query = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
-    for (unsigned spin = 1;; ++spin) {
-        word = __atomic_load_n(w, __ATOMIC_ACQUIRE);
-        if ((uint16_t)(word >> kRepSeq) == seq) break;
-        __builtin_ia32_pause();
-        if (spin % 256) continue;
-        sched_yield();
-        if (std::chrono::steady_clock::now() < next_query) continue;
-        const hipError_t e = hipStreamQuery(B.stream);
-        if (e == hipSuccess) {
-            word = __atomic_load_n(w, __ATOMIC_ACQUIRE);
-            seq = (uint16_t)(word >> kRepSeq);
-            break;
-        }
-        if (e != hipErrorNotReady) return e;
-        (void)hipGetLastError();
-        next_query = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
-    }
-    word &= (1ull << kRepSeq) - 1;
-    return hipSuccess;
+    unsigned spin = 0;
+    hipError_t failure = hipSuccess;
+    const ReportState r = await_report(
+        B.reports.last[which], [&] { return __atomic_load_n(w, __ATOMIC_ACQUIRE); },
+        [&] {
+            __builtin_ia32_pause();
+            if (++spin % 256) return StreamState::kNotAsked;
+            sched_yield();
+            if (std::chrono::steady_clock::now() < next_query) return StreamState::kNotAsked;
+            const bool clean = hipPeekAtLastError() == hipSuccess;
+            hipError_t e = hipStreamQuery(B.stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(B.stream);
+            if (e == hipSuccess) return StreamState::kDrained;
+            if (e != hipErrorNotReady) {
+                failure = e;
+                return StreamState::kFailed;
+            }
+            if (clean) (void)hipGetLastError();   // the query's own answer
+            next_query = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+            return StreamState::kBusy;
+        },
+        word);
+    if (r == ReportState::kMissing) return hipErrorLaunchFailure;
+    return r == ReportState::kFailed ? failure : hipSuccess;
 }
 
-// Before a call's first report: after one that ended in an error some reports
-// may have been enqueued uncounted, so their numbers are taken from the words.
+// Before a call's first report.
 hipError_t open_reports(Batch& B) {
-    if (B.reports_open) {
+    if (B.reports.open) {
         const hipError_t e = hipStreamSynchronize(B.stream);
         if (e != hipSuccess) return e;
-        B.seq = (uint16_t)(B.rep.host[0] >> kRepSeq);
-        B.seq_cg = (uint16_t)(B.rep.host[1] >> kRepSeq);
+        B.reports.resume(B.rep.host);
     }
-    B.reports_open = true;
+    B.reports.open = true;
     return hipSuccess;
 }
-
-int report_running(unsigned long long w) { return (int)(w & ((1u << kRepWaiting) - 1)); }
-int report_waiting(unsigned long long w) { return (int)((w >> kRepWaiting) & ((1u << (kRepEnded - kRepWaiting)) - 1)); }
-bool report_ended(unsigned long long w) { return (w >> kRepEnded) & 1; }
 
 // Capture one part (0: the pass, 1: the corrections) as a graph, once per
 // batch, timing mode and options.
@@ -1404,8 +1403,8 @@ nmpc_status batch_solve(Batch& B, int warm, const nmpc_options& o, nmpc_result* 
     enqueue_eval(B, dop);
     if (timed) (void)hipEventRecord(B.ev[7], st);
     HIP_TRY(hipGetLastError());
-    ++B.seq;
-    HIP_TRY(wait_report(B, 0, B.seq, word));
+    ++B.reports.last[0];
+    HIP_TRY(wait_report(B, 0, word));
     if (timed) {
         HIP_TRY(hipStreamSynchronize(st));
         add_time(0, 6, 7);
@@ -1424,12 +1423,12 @@ nmpc_status batch_solve(Batch& B, int warm, const nmpc_options& o, nmpc_result* 
                 enqueue_corrections(B, dop, timed);
                 HIP_TRY(hipGetLastError());
             }
-            ++B.seq;
+            ++B.reports.last[0];
         }
         if (use_graph) HIP_TRY(hipGraphLaunch(B.exec[k], st));
         else HIP_TRY(enqueue_pass(B, dop, timed, hyk));
-        ++B.seq;
-        HIP_TRY(wait_report(B, 0, B.seq, word));
+        ++B.reports.last[0];
+        HIP_TRY(wait_report(B, 0, word));
         ++passes;
         if (timed) {
             HIP_TRY(hipStreamSynchronize(st));
@@ -1449,7 +1448,7 @@ nmpc_status batch_solve(Batch& B, int warm, const nmpc_options& o, nmpc_result* 
     }
     // an instance that ended in the last evaluation opened one more iteration
     if (report_ended(word)) ++passes;
-    B.reports_open = false;
+    B.reports.open = false;
     int worst = NMPC_OK;
     for (int i = 0; i < ni; ++i) {
         const Ctl& c = B.hctl[i];
@@ -1592,9 +1591,9 @@ nmpc_status device_closed_loop(Problem& p, int steps, const double* traj, const 
     int status = NMPC_OK;
     for (int k = 0; k < steps; ++k) {
         HIP_TRY(hipGraphLaunch(B.loop_exec, st));
-        B.seq = (uint16_t)(B.seq + 1 + bodies);
+        B.reports.last[0] += (uint16_t)(1 + bodies);
         unsigned long long word = 0;
-        HIP_TRY(wait_report(B, 0, B.seq, word));
+        HIP_TRY(wait_report(B, 0, word));
         long npass = bodies;
         while (report_running(word) > 0) {
             if (npass >= max_passes) {
@@ -1603,11 +1602,11 @@ nmpc_status device_closed_loop(Problem& p, int steps, const double* traj, const 
             }
             if (report_waiting(word) > 0) {
                 HIP_TRY(hipGraphLaunch(B.exec[2], st));
-                ++B.seq;
+                ++B.reports.last[0];
             }
             HIP_TRY(hipGraphLaunch(B.exec[0], st));
-            ++B.seq;
-            HIP_TRY(wait_report(B, 0, B.seq, word));
+            ++B.reports.last[0];
+            HIP_TRY(wait_report(B, 0, word));
             ++npass;
         }
         *iters_total += B.hctl[0].it;
@@ -1622,7 +1621,7 @@ nmpc_status device_closed_loop(Problem& p, int steps, const double* traj, const 
     if (traj) HIP_TRY(hipMemcpyAsync(p.traj.data(), I.zF, p.traj.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     HIP_TRY(join_out(D, caller));
-    B.reports_open = false;
+    B.reports.open = false;
     return status;
 }
 

@@ -15,6 +15,7 @@
 #include "distill_layout.h"
 #include "plate_layout.h"
 #include "reflux_layout.h"
+#include "report.h"
 
 namespace nmpc {
 
@@ -114,18 +115,15 @@ struct Ctl {
 };
 
 // Where the device reports to the host without a copy or a wait for the stream:
-// pinned words that a kernel's last workgroup stores and the host polls.  A
-// word's top 16 bits count the reports (a stale one is told from the awaited
-// one), counts are below.  cnt: device counters, zero before the first report.
+// pinned words (report.h) that a kernel's last workgroup stores and the host
+// polls, the reports numbered so that a stale one is told from the awaited one.
+// cnt: device counters, zero before the first report.
 constexpr int kRepCounters = 6;   // ticket, running, waiting, ended; reports of the passes, of the CG
 struct Report {
     unsigned* cnt;
     unsigned long long* host;   // [0] passes, [1] conjugate gradients
     Ctl* ctl;                   // control blocks of finished instances, per instance
 };
-// pass word: instances running (24 bits), waiting for corrections (22 bits), 1 if
-// an instance ended in this evaluation
-constexpr int kRepWaiting = 24, kRepEnded = 46, kRepSeq = 48;
 
 __host__ __device__ inline bool ctl_active(const Ctl* c, int pred) {
     if (pred == kPredAll) return true;

@@ -292,10 +292,8 @@ __global__ void __launch_bounds__(kBlock) k_decideA(const InstPtrs* __restrict__
         end = atomicExch(rep.cnt + 3, 0u);
         atomicExch(rep.cnt, 0u);
     }
-    const unsigned long long seq = ++rep.cnt[4] & 0xffffu;
-    const unsigned long long word = (seq << kRepSeq) | ((unsigned long long)(end != 0) << kRepEnded) |
-                                    ((unsigned long long)wait << kRepWaiting) | run;
-    __hip_atomic_store(rep.host, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(rep.host, report_word(++rep.cnt[4], run, wait, end != 0), __ATOMIC_RELEASE,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- phase B: condensed system ingredients --------------------------------------
@@ -1377,8 +1375,8 @@ __global__ void __launch_bounds__(kBlock) k_hk_count(const InstPtrs* __restrict_
     if (mine) atomicAdd(&cnt, mine);
     __syncthreads();
     if (threadIdx.x != 0) return;
-    const unsigned long long seq = ++rep.cnt[5] & 0xffffu;
-    __hip_atomic_store(rep.host + 1, (seq << kRepSeq) | (unsigned long long)cnt, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(rep.host + 1, report_word(++rep.cnt[5], (unsigned)cnt, 0, false), __ATOMIC_RELEASE,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // right-hand side of the final solve: b1 + gamma_h J_c^T b2 - J_c^T x
