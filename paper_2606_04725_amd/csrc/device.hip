@@ -834,8 +834,9 @@ nmpc_status device_init(Problem& p, std::string& err) {
         I.nsp = 2;
         I.ntr = st.H;
     }
-    // Supernode classes.  Small: the front fits in shared memory (one workgroup
-    // factors it there).  Large: it does not (from 201 rows on), and the
+    // Supernode classes.  Small: the front fits in shared memory and its rows in
+    // a workgroup's lanes (one workgroup factors it there).  Large: it does not
+    // (from 201 rows on, where the 160 KB of shared memory end), and the
     // multi-workgroup path works on it in place: on one workgroup in a global
     // buffer, which fronts of up to 256 rows once had, a level of them took
     // 167 us (32 x 32 x 50 plate), their share of the large path about 15 us.
@@ -846,19 +847,11 @@ nmpc_status device_init(Problem& p, std::string& err) {
     std::vector<char> big_fac(nsn, 0), big_sol(nsn, 0);
     auto rows_of = [&](int sn) { return (int64_t)(sy.sn_rows_ptr[sn + 1] - sy.sn_rows_ptr[sn]); };
     auto width_of = [&](int sn) { return (int64_t)(sy.sn_ptr[sn + 1] - sy.sn_ptr[sn]); };
-    // a shared-memory front is a packed lower triangle of one more row (the
-    // fused forward solve's)
-    auto fac_bytes = [&](int sn) {
-        const size_t mr = (size_t)rows_of(sn);
-        return (mr + 1) * (mr + 2) / 2 * sizeof(double);
-    };
-    auto sol_bytes = [&](int sn) {
-        const size_t mr = (size_t)rows_of(sn), w = (size_t)width_of(sn);
-        return (mr * (w | 1) + mr + 2 * w) * sizeof(double);
-    };
+    auto fac_bytes = [&](int sn) { return front_bytes(rows_of(sn)); };
+    auto sol_bytes = [&](int sn) { return front_solve_bytes(rows_of(sn), width_of(sn)); };
     for (int sn = 0; sn < nsn; ++sn) {
-        big_fac[sn] = fac_bytes(sn) > lim;
-        big_sol[sn] = sol_bytes(sn) > lim;
+        big_fac[sn] = !one_workgroup_front(rows_of(sn), lim);
+        big_sol[sn] = !one_workgroup_solve(rows_of(sn), width_of(sn), lim);
     }
     // Fused forward solves: a supernode whose children all run it runs the
     // Newton step's forward solve with its factorization (their update vectors

@@ -5,11 +5,11 @@
 #include <cmath>
 #include <type_traits>
 
+#include "front_rules.h"
+
 namespace nmpc {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kCholWave = 64;
 
 // A front's lower triangle packed by columns: column j holds rows j .. m-1, and
 // base(j) + i is the position of entry (i, j), i >= j.  Front orders stay far
@@ -134,13 +134,12 @@ __device__ __attribute__((always_inline)) inline bool factor_rows(double (&a)[16
 // .. kb + 63, wave v the 16 rows from kb (again, for their pivots) and 48 more.
 // Rows below the block go back at once, the block after the next barrier
 // (store_pivot_block, from a of wave 0): other waves may still read it.
-constexpr int kRowsPerWave = kCholWave - 16;
 __device__ __attribute__((always_inline)) inline void panel_solve(double* F, PackedIdx ix, int kb, int kw, int* fail,
                                                                  double (&a)[16]) {
     const int lane = threadIdx.x & (kCholWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kCholWave);
-    const int m = ix.m, r0 = kb + (wv == 0 ? 0 : kRowsPerWave * wv);   // row of lane 16 is r0 + 16
-    if (wv != 0 && r0 + 16 >= m) return;
-    const int r = lane < 16 ? kb + lane : r0 + lane;
+    const int m = ix.m, own = panel_wave_begin(kb, wv);   // the row of lane 16
+    if (wv != 0 && own >= m) return;
+    const int r = lane < 16 ? kb + lane : own - 16 + lane;
     {
         // loads without a branch: rows clamped into the front, columns into the
         // panel; entries above the block's diagonal read some other entry of

@@ -13,6 +13,7 @@
 
 #include "../../include/nmpc.h"
 #include "distill_layout.h"
+#include "front_rules.h"
 #include "plate_layout.h"
 #include "reflux_layout.h"
 #include "report.h"
@@ -20,7 +21,7 @@
 namespace nmpc {
 
 constexpr int kBlock = 256;          // threads per block of every vector kernel
-constexpr int kFactorBlock = 256;    // threads per supernode group
+constexpr int kFactorBlock = kSolveThreads;   // threads per supernode group of the solves
 constexpr int kPanel = 8;            // columns per blocked step of a forward solve
 constexpr int kMaxQ = 12;            // reduced quantities per phase
 constexpr int kMaxSeed = 16;         // controls per stage the sensitivity seed can hold
@@ -344,9 +345,8 @@ void launch_adj_refine(int step, const InstPtrs* I, const IpmSpaces& S, double e
 // group, for instances matching pred (kPredFactor during a solve) with eta
 // from the control block, or every instance with eta_force (pred kPredAll).
 // The fronts stay in shared memory (lds_bytes).
-// variant: threads per workgroup, 0: 256, 1: 512 (the same arithmetic).  Fewer
-// would leave rows of the largest front without a lane.
-constexpr int kFactorVariants = 2;
+// variant: threads per workgroup, kFactorThreads (the same arithmetic).
+constexpr int kFactorVariants = sizeof(kFactorThreads) / sizeof(kFactorThreads[0]);
 void launch_factor_groups(int variant, int pred, double eta_force, const FactorTask* t, int groups, size_t lds_bytes,
                           hipStream_t st);
 void launch_fwd_groups(int pred, int which, const InstPtrs* I, const SolveTask* t, int groups, size_t lds_bytes,

@@ -417,7 +417,7 @@ __device__ __attribute__((always_inline)) void bwd_one(const __attribute__((addr
     const auto* Ls = global(T->L);
     const auto* rows = global(T->rows) + w;
     const int ri = rows[min(tid, max(nb, 1) - 1) - (nb == 0)];   // without rows below: the last column's own
-    // the panel fits in shared memory, so w < nthr
+    // a thread per column (one_workgroup_solve)
     const int tc = min(tid, w - 1);
     const int pk = global(T->perm)[tc];
     const double dg = Ls[tc + tc * m];
@@ -592,8 +592,8 @@ k_bwd_groups(const InstPtrs* __restrict__ Ia, const SolveTask* __restrict__ task
 }  // namespace
 
 hipError_t linalg_configure(size_t max_lds_bytes) {
-    const void* fns[] = {reinterpret_cast<const void*>(k_factor_groups<256>),
-                         reinterpret_cast<const void*>(k_factor_groups<512>),
+    const void* fns[] = {reinterpret_cast<const void*>(k_factor_groups<kFactorThreads[0]>),
+                         reinterpret_cast<const void*>(k_factor_groups<kFactorThreads[1]>),
                          reinterpret_cast<const void*>(k_fwd_groups), reinterpret_cast<const void*>(k_bwd_groups)};
     for (const void* fn : fns) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds_bytes);
@@ -605,10 +605,9 @@ hipError_t linalg_configure(size_t max_lds_bytes) {
 void launch_factor_groups(int variant, int pred, double eta_force, const FactorTask* t, int groups, size_t lds_bytes,
                           hipStream_t st) {
     if (groups <= 0) return;
-    if (variant == 1)
-        hipLaunchKernelGGL(k_factor_groups<512>, dim3(groups), dim3(512), lds_bytes, st, t, pred, eta_force);
-    else
-        hipLaunchKernelGGL(k_factor_groups<256>, dim3(groups), dim3(256), lds_bytes, st, t, pred, eta_force);
+    static_assert(kFactorVariants == 2, "a launch per variant");
+    const auto kernel = variant == 1 ? k_factor_groups<kFactorThreads[1]> : k_factor_groups<kFactorThreads[0]>;
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kFactorThreads[variant == 1 ? 1 : 0]), lds_bytes, st, t, pred, eta_force);
 }
 
 void launch_fwd_groups(int pred, int which, const InstPtrs* I, const SolveTask* t, int groups, size_t lds_bytes,

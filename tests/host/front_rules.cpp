@@ -31,7 +31,35 @@ static void panel_rows() {
             }
 }
 
+// Every row of a front that one workgroup factors has a lane, whatever the
+// shared memory of the device, with any of the kernel's workgroups.
+static void one_workgroup() {
+    for (size_t kb : {64, 100, 160, 164, 168, 176, 192, 256, 320, 1024})
+        for (int rows = 1; rows <= 600; ++rows) {
+            const size_t lds = kb * 1024;
+            if (kb == 160)   // gfx950: shared memory alone decides
+                need(one_workgroup_front(rows, lds) == (rows <= 200), "class", rows, 0, 0, 0);
+            for (int w : {1, 8, 16, 17, 100, 142, 143, 255, 256, 257, 600}) {
+                if (w > rows) continue;
+                if (one_workgroup_solve(rows, w, lds)) need(w <= kSolveThreads && front_solve_bytes(rows, w) <= lds, "solve", rows, w, 0, 0);
+                if (kb == 160) need(one_workgroup_solve(rows, w, lds) == (front_solve_bytes(rows, w) <= lds), "solve class", rows, w, 0, 0);
+            }
+            if (!one_workgroup_front(rows, lds)) continue;
+            need(front_bytes(rows) <= lds, "bytes", rows, 0, 0, 0);
+            const int m = rows + 1;   // with the right-hand side
+            for (int threads : kFactorThreads)
+                for (int first = 0; first < rows; first += 16)
+                    for (int r = first + 16; r < m; ++r) {
+                        int held = 0;
+                        for (int wave = 0; wave < threads / kCholWave; ++wave)
+                            held += r >= panel_wave_begin(first, wave) && r < panel_wave_end(first, wave);
+                        need(held == 1, "row without a lane", rows, threads, first, r);
+                    }
+        }
+}
+
 int main() {
+    one_workgroup();
     panel_rows();
     std::printf("ok\n");
     return 0;
