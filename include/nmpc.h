@@ -346,9 +346,10 @@ nmpc_status nmpc_eval(nmpc_problem* p, const double* y, const double* lam, const
 
 /* NumCholesky (eqs. 20-21) of a caller-given matrix: k_vals[nnz_k] are the
  * lower KKT values in slot order; eta is added to the diagonal.  On return
- * *ok = 1 when every pivot was positive and finite.  l_vals (may be NULL)
- * receives the supernodal factor: for supernode s, a column-major
- * rows(s) x width(s) panel, panels in supernode order (stored_l values).
+ * *ok = 1 when every pivot was positive and finite; one that is not counts as 1
+ * in the factor.  l_vals (may be NULL) receives the supernodal factor: for
+ * supernode s, a column-major rows(s) x width(s) panel, panels in supernode
+ * order (stored_l values).
  * Requires nmpc_analyze. */
 nmpc_status nmpc_factor(nmpc_problem* p, const double* k_vals, double eta, int32_t* ok,
                         double* l_vals);

@@ -1724,6 +1724,10 @@ nmpc_status device_eval(Problem& p, const double* y, const double* lam, const do
     return NMPC_OK;
 }
 
+// A caller may read what a matrix that is not positive definite leaves: after a
+// failure it is factored once more with 1 in place of the pivots at fault (an
+// iteration, which factors again with a larger eta, never reads it, and its
+// kernels do not spend time on it).
 nmpc_status device_factor(Problem& p, const double* kv, double eta, int32_t* ok, double* lv, std::string& err) {
     Device& D = *p.dev;
     Batch& B = *D.self;
@@ -1732,6 +1736,15 @@ nmpc_status device_factor(Problem& p, const double* kv, double eta, int32_t* ok,
     int failed = 0;
     HIP_TRY(factor_once(B, eta, failed));
     *ok = failed ? 0 : 1;
+    if (failed) {
+        for (BLaunch L : B.fac) {
+            if (L.kind == kStepGroupFactor) L.variant = kFactorReplace;
+            if (L.kind == kBigPanelStep) L.kind = kBigPanelReplace;
+            run_launch(B, L, kPredAll, eta, 0);
+        }
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(B.stream));
+    }
     if (lv) HIP_TRY(hipMemcpy(lv, D.hI.L, D.stored_l * sizeof(double), hipMemcpyDeviceToHost));
     return NMPC_OK;
 }

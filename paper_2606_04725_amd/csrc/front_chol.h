@@ -105,9 +105,26 @@ __device__ __attribute__((always_inline)) inline double pivot_rsqrt(double piv) 
 // columns take their updates.  A pivot that is not positive and finite makes its
 // reciprocal root, and through the updates every later one, not finite: only the
 // last of the kw is tested (tested and replaced one by one they cost 7
-// instructions of a pivot's 27).
-template <int P>
+// instructions of a pivot's 27).  Replace does that: such a pivot counts as 1,
+// and what a matrix that is not positive definite leaves is a factor all the
+// same; nothing is reported then.
+template <int P, bool Replace>
 __device__ __attribute__((always_inline)) inline bool factor_rows(double (&a)[16], int kw) {
+    if constexpr (Replace) {
+        const int lane = threadIdx.x & (kCholWave - 1);
+        static_for<P>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            double piv = wave_lane<k>(a[k]);
+            if (!(piv > 0.0) || !(piv < INFINITY)) piv = 1.0;
+            a[k] = (lane == k ? piv : a[k]) * pivot_rsqrt(piv);
+            static_for<P - 1 - k>([&](auto jc) {
+                constexpr int j = k + 1 + decltype(jc)::value;
+                a[j] = fma(-a[k], wave_lane<j>(a[k]), a[j]);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        return false;
+    }
     double inv = pivot_rsqrt(wave_lane<0>(a[0])), last = inv;
     static_for<P>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
@@ -134,6 +151,7 @@ __device__ __attribute__((always_inline)) inline bool factor_rows(double (&a)[16
 // .. kb + 63, wave v the 16 rows from kb (again, for their pivots) and 48 more.
 // Rows below the block go back at once, the block after the next barrier
 // (store_pivot_block, from a of wave 0): other waves may still read it.
+template <bool Replace>
 __device__ __attribute__((always_inline)) inline void panel_solve(double* F, PackedIdx ix, int kb, int kw, int* fail,
                                                                  double (&a)[16]) {
     const int lane = threadIdx.x & (kCholWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kCholWave);
@@ -151,7 +169,7 @@ __device__ __attribute__((always_inline)) inline void panel_solve(double* F, Pac
             at += c + 1 < kw ? m - 1 - (kb + c) : 0;   // to the same row of the next column
         }
     }
-    const bool bad = kw > 8 ? factor_rows<16>(a, kw) : factor_rows<8>(a, kw);
+    const bool bad = kw > 8 ? factor_rows<16, Replace>(a, kw) : factor_rows<8, Replace>(a, kw);
     if (bad && threadIdx.x == 0) *global(fail) = 1;
     if (lane >= (wv == 0 ? kw : 16) && r < m) {
         int at = ix.base(kb) + r;
@@ -297,8 +315,10 @@ __device__ __attribute__((always_inline)) inline void update_block(double* F, Pa
 // that holds a right-hand side is solved (and updated) like any other: the
 // factored columns of that row are the forward substitution.
 // A pivot that is not positive and finite sets *fail (eq. 12: the matrix is not
-// numerically positive definite); the values are not finite from there on.
+// numerically positive definite) and the values are not finite from there on,
+// or, with Replace, it counts as 1 and nothing is reported.
 // spare: a shared-memory slot (an index into F) that takes what lies outside.
+template <bool Replace>
 __device__ __attribute__((always_inline)) inline void partial_cholesky(double* F, PackedIdx ix, int w, int spare, int* fail) {
     constexpr int P = 16;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kCholWave), nw = blockDim.x / kCholWave;
@@ -319,7 +339,7 @@ __device__ __attribute__((always_inline)) inline void partial_cholesky(double* F
                     trapezoid_tile(F, ix, w, kb - P, spare, ti + 1, tj + 1);
                 }
         }
-        panel_solve(F, ix, kb, kw, fail, a);
+        panel_solve<Replace>(F, ix, kb, kw, fail, a);
         __syncthreads();
         if (wv == 0) store_pivot_block(F, ix, kb, kw, spare, a);
         if (t0 < w) {

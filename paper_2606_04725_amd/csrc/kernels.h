@@ -347,6 +347,7 @@ void launch_adj_refine(int step, const InstPtrs* I, const IpmSpaces& S, double e
 // The fronts stay in shared memory (lds_bytes).
 // variant: threads per workgroup, kFactorThreads (the same arithmetic).
 constexpr int kFactorVariants = sizeof(kFactorThreads) / sizeof(kFactorThreads[0]);
+constexpr int kFactorReplace = kFactorVariants;   // a pivot that is not positive and finite counts as 1, unreported
 void launch_factor_groups(int variant, int pred, double eta_force, const FactorTask* t, int groups, size_t lds_bytes,
                           hipStream_t st);
 void launch_fwd_groups(int pred, int which, const InstPtrs* I, const SolveTask* t, int groups, size_t lds_bytes,
@@ -383,6 +384,7 @@ static_assert(sizeof(BigTask) == 64, "one scalar load of 16 words");
 enum BigKind : int {
     kBigAssemble = 1,   // a: first of kBigAsmCols columns, b: chunk of rows
     kBigPanelStep = 3,  // a: kb, b: row block
+    kBigPanelReplace = 4,  // the same, a pivot that is not positive and finite counts as 1
     kBigUpdate = 5,     // a: kb, b: lower-triangle tile; b < 0: keep the diagonal block of columns a
     kBigFwdGather = 2,  // a: row block
     kBigFwdTri = 6,     // a: chunk

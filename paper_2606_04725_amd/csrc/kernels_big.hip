@@ -156,7 +156,8 @@ k_big_assemble(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ task
 // with several workgroups goes to dfac, from where the next update launch puts
 // it into the panel: another workgroup may still have to read the original.
 // A pivot that is not positive and finite sets the instance's failure flag
-// (eq. 12) and the factor's values are not finite from there on.
+// (eq. 12) and the factor's values are not finite from there on, or, with
+// Replace, it counts as 1 and nothing is reported.
 // Wave 0's chain bounds it: of 40 thousand cycles 19 went to the four 16-column
 // factorizations, 8 to the loads.  16.9 us per launch in the Cholesky of the 28 x
 // 37 plate (20.3 with a test for every pivot and the next columns' tiles one
@@ -167,12 +168,13 @@ constexpr int kLdd = kBigPanel + 1;
 
 // 16 pivot columns of D (shared memory, kLdd) from column c0, by one wave (a row
 // from c0 on per lane); the reciprocals of the diagonal to rd.
+template <bool Replace>
 __device__ __attribute__((always_inline)) inline bool factor_16(double* D, double* rd, int c0) {
     const int lane = threadIdx.x & (kWave - 1), row = min(c0 + lane, kBigPanel - 1);
     double a[16];
 #pragma unroll
     for (int c = 0; c < 16; ++c) a[c] = D[row + (c0 + c) * kLdd];
-    const bool bad = factor_rows<16>(a, 16);
+    const bool bad = factor_rows<16, Replace>(a, 16);
     if (c0 + lane < kBigPanel) {
 #pragma unroll
         for (int c = 0; c < 16; ++c) D[row + (c0 + c) * kLdd] = a[c];   // above the diagonal: never read again
@@ -230,6 +232,7 @@ __device__ __attribute__((always_inline)) inline void solve_16(f64x4& acc, const
     for (int q = 0; q < 4; ++q) acc[q] *= r;
 }
 
+template <bool Replace>
 __global__ void __launch_bounds__(kPanelThreads)
 k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, int pred) {
     static_assert(kBigPanel == kWave, "a lane per row of D");
@@ -281,7 +284,7 @@ k_big_panel(const InstPtrs* __restrict__ Ia, const BigTask* __restrict__ tasks, 
         const int c0 = 16 * p;
         f64x4 acc = {0.0, 0.0, 0.0, 0.0};
         if (wv == 0) {
-            bad |= factor_16(D, rd, c0);
+            bad |= factor_16<Replace>(D, rd, c0);
         } else if (works) {   // the solved blocks' part, while wave 0 factors
             // (summed from zero: its roundings are the products' size, not the entries')
             for (int i = 0; i < c0; i += 4) {
@@ -859,7 +862,10 @@ void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs*
             hipLaunchKernelGGL(k_big_assemble, dim3(count), dim3(kBigAsmCols * kWave), 0, st, I, tasks, pred, eta_force);
             break;
         case kBigPanelStep:
-            hipLaunchKernelGGL(k_big_panel, dim3(count), dim3(kPanelThreads), 0, st, I, tasks, pred);
+            hipLaunchKernelGGL(k_big_panel<false>, dim3(count), dim3(kPanelThreads), 0, st, I, tasks, pred);
+            break;
+        case kBigPanelReplace:
+            hipLaunchKernelGGL(k_big_panel<true>, dim3(count), dim3(kPanelThreads), 0, st, I, tasks, pred);
             break;
         case kBigUpdate:
             hipLaunchKernelGGL(k_big_update<false>, dim3(count), dim3(kBlock), 0, st, I, tasks, pred);

@@ -99,7 +99,7 @@ __device__ __attribute__((always_inline)) inline bool in_phase(const Ctl* ctl, i
 // The front is a packed lower triangle in shared memory, of order m + 1: its last
 // row holds the fused forward solve's right-hand side (zeros without it), which
 // so takes every step as one more row, and its last entry is the spare slot.
-template <int Cols>
+template <int Cols, bool Replace>
 __device__ __attribute__((always_inline)) void factor_one(const __attribute__((address_space(4))) FactorTask* T, double eta,
                            double* F, bool fwd) {
     const int w = T->w, m = T->m;
@@ -221,7 +221,7 @@ __device__ __attribute__((always_inline)) void factor_one(const __attribute__((a
         ib = ic;
         hb = hc;
     }
-    partial_cholesky(F, ix, w, spare, &T->ctl->fail);
+    partial_cholesky<Replace>(F, ix, w, spare, &T->ctl->fail);
     // the update block (rows and columns w and on) takes its update before the
     // panel goes out: global stores in flight would hold the update's first
     // shared-memory loads until they complete (their data registers are reused)
@@ -268,7 +268,7 @@ __device__ __attribute__((always_inline)) void factor_one(const __attribute__((a
 // Variants (threads per workgroup) the autotuner chooses from.
 // (two waves per SIMD at least: at most 256 registers, so that the matrix cores'
 // accumulators stay in the vector registers)
-template <int Threads>
+template <int Threads, bool Replace>
 __global__ void __launch_bounds__(Threads, 2)
 k_factor_groups(const FactorTask* __restrict__ tasks, int pred, double eta_force) {
     extern __shared__ double lds[];
@@ -277,7 +277,7 @@ k_factor_groups(const FactorTask* __restrict__ tasks, int pred, double eta_force
     const double eta = pred == kPredAll ? eta_force : global(T->ctl)->eta;
     const bool fwd = pred == kPredFactor;   // in a pass: the Newton step's right-hand side is assembled
     while (true) {
-        factor_one<8>(T, eta, lds, fwd);
+        factor_one<8, Replace>(T, eta, lds, fwd);
         const int next = T->next;
         if (next == 0) break;
         T = record_at(tasks, next);
@@ -592,8 +592,9 @@ k_bwd_groups(const InstPtrs* __restrict__ Ia, const SolveTask* __restrict__ task
 }  // namespace
 
 hipError_t linalg_configure(size_t max_lds_bytes) {
-    const void* fns[] = {reinterpret_cast<const void*>(k_factor_groups<kFactorThreads[0]>),
-                         reinterpret_cast<const void*>(k_factor_groups<kFactorThreads[1]>),
+    const void* fns[] = {reinterpret_cast<const void*>(k_factor_groups<kFactorThreads[0], false>),
+                         reinterpret_cast<const void*>(k_factor_groups<kFactorThreads[1], false>),
+                         reinterpret_cast<const void*>(k_factor_groups<kFactorThreads[1], true>),
                          reinterpret_cast<const void*>(k_fwd_groups), reinterpret_cast<const void*>(k_bwd_groups)};
     for (const void* fn : fns) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds_bytes);
@@ -606,8 +607,9 @@ void launch_factor_groups(int variant, int pred, double eta_force, const FactorT
                           hipStream_t st) {
     if (groups <= 0) return;
     static_assert(kFactorVariants == 2, "a launch per variant");
-    const auto kernel = variant == 1 ? k_factor_groups<kFactorThreads[1]> : k_factor_groups<kFactorThreads[0]>;
-    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kFactorThreads[variant == 1 ? 1 : 0]), lds_bytes, st, t, pred, eta_force);
+    const auto kernel = variant == 0 ? k_factor_groups<kFactorThreads[0], false>
+                        : variant == 1 ? k_factor_groups<kFactorThreads[1], false> : k_factor_groups<kFactorThreads[1], true>;
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kFactorThreads[variant == 0 ? 0 : 1]), lds_bytes, st, t, pred, eta_force);
 }
 
 void launch_fwd_groups(int pred, int which, const InstPtrs* I, const SolveTask* t, int groups, size_t lds_bytes,

@@ -3,9 +3,10 @@ fronts with fewer columns than a block of 16, pivots over the whole range of
 positive doubles."""
 import numpy as np
 import pytest
+import scipy.linalg as sla
 
 from paper_2606_04725_amd import nmpc as N
-from test_gpu_fronts import U, _check, _note
+from test_gpu_fronts import U, _check, _matrix, _note
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +44,58 @@ def test_every_positive_pivot_is_accepted(kind):
     for v in (0.0, -5e-324, -1.0, np.inf, np.nan):
         ok, _ = p.factor(np.where(diag, v, 0.0), want_l=False)
         assert not ok, v
+
+
+@pytest.mark.parametrize("kind", ["small fronts", "large fronts"])
+def test_factor_continues_past_a_bad_pivot(kind):
+    """A pivot that is not positive and finite counts as 1: the factor returned is
+    that of the matrix whose entry there makes it so (positive definite here: the
+    entries off the diagonal are small), and solves with it."""
+    p = N.Problem(_structure(kind))
+    p.analyze()
+    z, pat = p.export_symbolic(), p.patterns()
+    start, rp, rows, perm = z["snode_ptr"], z["snode_rows_ptr"], z["snode_rows"], z["perm"]
+    w, m = np.diff(start), np.diff(rp)
+    big = m > 200
+    assert np.any(big) == (kind == "large fronts")
+    v, K = _matrix(pat, p.n, 17)
+    r, c = pat["k_rows"].astype(np.int64), pat["k_cols"].astype(np.int64)
+    off = r != c
+    v[off] *= 0.1
+    K = np.zeros((p.n, p.n))
+    K[r, c] = v
+    K[c, r] = v
+    A = K[np.ix_(perm, perm)]
+    slot = np.empty(p.n, np.int64)
+    slot[r[~off]] = np.flatnonzero(~off)
+    # columns of one front of the kind: the first, one inside and the last of a
+    # block of 16, the first of the next one, the front's last
+    s = int(np.argmax(np.where(big, w, 0) if kind == "large fronts" else w))
+    low = np.arange(m.max())[:, None] >= np.arange(w.max())[None, :]
+    for col in sorted({0, 5, min(15, int(w[s]) - 1), min(16, int(w[s]) - 1), int(w[s]) - 1}):
+        b = int(start[s]) + col
+        A1 = A.copy()
+        A1[b, b] = 1.0
+        if b > 0:
+            A1[b, b] += np.sum(sla.solve_triangular(sla.cholesky(A[:b, :b], lower=True), A[:b, b], lower=True) ** 2)
+        L = sla.cholesky(A1, lower=True)
+        ev = np.linalg.eigvalsh(A1)
+        tol = 2 * p.n * U * (ev[-1] / ev[0]) * np.max(np.abs(L))
+        for bad in (-1e6, 0.0, np.inf, np.nan):
+            _note(f"{kind}: front {s} ({m[s]} rows, {w[s]} columns), column {col}, entry {bad}")
+            kv = v.copy()
+            kv[slot[perm[b]]] = bad
+            ok, lv = p.factor(kv)
+            assert not ok
+            o = 0
+            for q in range(len(w)):
+                P = lv[o:o + m[q] * w[q]].reshape(w[q], m[q]).T
+                o += m[q] * w[q]
+                want = L[np.ix_(rows[rp[q]:rp[q + 1]], np.arange(start[q], start[q + 1]))]
+                at = low[:m[q], :w[q]]
+                assert np.max(np.abs(P[at] - want[at])) <= tol, (q, int(m[q]), int(w[q]))
+            rhs = np.random.default_rng(col).normal(size=p.n)
+            x = np.empty(p.n)
+            x[:] = p.linear_solve(rhs)[perm]
+            back = np.max(np.abs(A1 @ x - rhs[perm])) / (np.max(np.abs(A1).sum(1)) * np.max(np.abs(x)) + np.max(np.abs(rhs)))
+            assert back <= m.max() * U, back
