@@ -15,6 +15,7 @@ using nmpc::Problem;
 struct nmpc_problem {
     Problem impl;
 };
+static_assert(sizeof(nmpc_problem) == sizeof(Problem), "a handle is its problem's address");
 
 struct nmpc_batch {
     nmpc::Batch* impl = nullptr;

@@ -2322,3 +2322,12 @@ nmpc_status device_autotune(Problem& p, int reps, int* changed, std::string& err
 }
 
 }  // namespace nmpc
+
+// Not part of the C ABI: every one-workgroup factor launch of a problem with the
+// given variant, which the autotuner may pick for any of them, for tests.
+extern "C" int32_t nmpc_internal_front_variant(nmpc::Problem* p, int32_t variant) {
+    if (!p || !p->dev || variant < 0 || variant >= nmpc::kFactorVariants) return NMPC_ERR_INVALID_ARG;
+    nmpc::apply_variants(*p->dev, std::vector<int>(p->dev->fac.size(), variant));
+    p->dev->adj_ready = false;
+    return NMPC_OK;
+}

@@ -1,10 +1,13 @@
 """Front kernels where their rules change, against dense references: large
 fronts with fewer columns than a block of 16, pivots over the whole range of
-positive doubles."""
+positive doubles and past it, both workgroup sizes on every one-workgroup front."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import scipy.linalg as sla
 
+from paper_2606_04725_amd import capi
 from paper_2606_04725_amd import nmpc as N
 from test_gpu_fronts import U, _check, _matrix, _note
 
@@ -99,3 +102,45 @@ def test_factor_continues_past_a_bad_pivot(kind):
             x[:] = p.linear_solve(rhs)[perm]
             back = np.max(np.abs(A1 @ x - rhs[perm])) / (np.max(np.abs(A1).sum(1)) * np.max(np.abs(x)) + np.max(np.abs(rhs)))
             assert back <= m.max() * U, back
+
+
+def _force(p, variant):
+    f = capi.lib().nmpc_internal_front_variant
+    f.restype, f.argtypes = C.c_int32, [C.c_void_p, C.c_int32]
+    assert f(p._h, variant) == 0
+
+
+@pytest.mark.parametrize("kind,a,b", [("column", 4, 1), ("column", 100, 15), ("plate", 12, 14), ("plate", 24, 4)])
+def test_every_workgroup_size_on_every_front(kind, a, b):
+    """The autotuner may give 256 or 512 threads to any one-workgroup launch: both
+    against the dense factor, and the same bits.  The plates have fronts at the
+    edges of a wave's rows (64, 65, 112 to 114, 159 to 161) and of the class (200)."""
+    st = N.distillation_structure(a, b, 0.05, 2.5) if kind == "column" else N.plate_structure(a, b, 0.01)
+    p = N.Problem(st)
+    p.analyze()
+    z, pat = p.export_symbolic(), p.patterns()
+    start, rp, rows, perm = z["snode_ptr"], z["snode_rows_ptr"], z["snode_rows"], z["perm"]
+    w, m = np.diff(start), np.diff(rp)
+    kv, K = _matrix(pat, p.n, 7 * a + b)
+    A = K[np.ix_(perm, perm)] + 0.25 * np.eye(p.n)
+    L = sla.cholesky(A, lower=True)
+    # as in the checks of the default variants: dominant by 1.25, rows of norm <= 2 |diagonal|
+    tol = 2 * p.n * U * (2.0 * np.max(np.diag(A)) / 1.25) * np.max(np.abs(L))
+    low = np.arange(m.max())[:, None] >= np.arange(w.max())[None, :]
+    seen = []
+    for variant in (0, 1):
+        _force(p, variant)
+        _note(f"{kind} {a} x {b}: fronts of {m.min()} to {m[m <= 200].max()} rows, variant {variant}")
+        ok, lv = p.factor(kv, eta=0.25)
+        assert ok
+        o = 0
+        for q in range(len(w)):
+            P = lv[o:o + m[q] * w[q]].reshape(w[q], m[q]).T
+            o += m[q] * w[q]
+            want = L[np.ix_(rows[rp[q]:rp[q + 1]], np.arange(start[q], start[q + 1]))]
+            at = low[:m[q], :w[q]]
+            d = np.max(np.abs(P[at] - want[at]))
+            assert d <= tol, (q, int(w[q]), int(m[q]), d, tol)
+            P[~at] = 0.0   # above the diagonal nothing is defined
+        seen.append((lv, p.linear_solve(np.ones(p.n))))
+    assert np.array_equal(seen[0][0], seen[1][0]) and np.array_equal(seen[0][1], seen[1][1])
