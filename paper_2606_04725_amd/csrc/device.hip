@@ -60,7 +60,6 @@ struct Step {
     int variant = 0, preset = 0;    // front-kernel variant of a group factor step: now (autotuned), and by rule
     std::vector<LocalGroup> groups;
     std::vector<int4> tasks;        // large path: (slot, supernode, a, b); the batch makes the records
-    size_t lds = 0;                 // shared memory of a large-supernode solve kernel
 };
 
 struct Device {
@@ -105,11 +104,12 @@ struct GenFns {
     bool operator==(const GenFns& o) const { return eval == o.eval && guess == o.guess && reduce == o.reduce; }
 };
 
-// Emitted kernel launch of a batch schedule: a group launch (groups[off ..
-// off + count)) or a large-supernode step (tasks[off .. off + count)).
+// Emitted kernel launch of a batch schedule: a group launch (a workgroup per
+// record ftasks or stasks[off .. off + count), which leads to the others of its
+// group) or a large-supernode step (tasks[off .. off + count)).
 struct BLaunch {
     int kind, off, count;
-    size_t bytes;
+    size_t bytes;   // shared memory of a group launch
     int variant;
     int step;       // index of the instances' step it comes from
 };
@@ -398,7 +398,6 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
             size_t b_fac = 0, b_sol = 0;
             int gkind = 0, variant = 0, vfront = -1;
             std::vector<std::vector<BigTask>> by_kind(32);
-            std::vector<size_t> kind_lds(32, 0);
             for (int i = 0; i < ni; ++i) {
                 const auto& L = members[i]->*list;
                 if (j >= L.size()) continue;
@@ -424,7 +423,6 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
                     }
                 } else {
                     for (const int4& t : st.tasks) by_kind[st.kind].push_back(record(*members[i], i, t));
-                    kind_lds[st.kind] = std::max(kind_lds[st.kind], st.lds);
                 }
             }
             if (!g_fac.empty())
@@ -434,7 +432,7 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
                 dst.push_back(BLaunch{gkind, emit_walks(sl, g_sol, solve_task), (int)g_sol.size(), b_sol, 0, (int)j});
             for (int k = 0; k < 32; ++k) {
                 if (by_kind[k].empty()) continue;
-                dst.push_back(BLaunch{k, (int)tl.size(), (int)by_kind[k].size(), kind_lds[k], 0, (int)j});
+                dst.push_back(BLaunch{k, (int)tl.size(), (int)by_kind[k].size(), 0, 0, (int)j});
                 tl.insert(tl.end(), by_kind[k].begin(), by_kind[k].end());
             }
         }
@@ -502,7 +500,7 @@ void run_launch(Batch& B, const BLaunch& L, int pred, double eta_force, int whic
             launch_bwd_groups(pred, which, B.dI, B.stasks + L.off, L.count, L.bytes, B.stream);
             break;
         default:
-            launch_big(L.kind, pred, eta_force, which, B.dI, B.tasks + L.off, L.count, L.bytes, B.stream);
+            launch_big(L.kind, pred, eta_force, which, B.dI, B.tasks + L.off, L.count, B.stream);
     }
 }
 
@@ -903,12 +901,11 @@ nmpc_status device_init(Problem& p, std::string& err) {
     };
     auto ceil_div = [](int64_t a, int64_t b) { return (int)((a + b - 1) / b); };
     const int RB = big_row_block(), TL = big_tile(), SR = big_solve_rows(), SC = big_solve_cols(), CH = big_chunk();
-    auto push = [&](std::vector<Step>& dst, int kind, std::vector<int4>&& t, size_t lds = 0) {
+    auto push = [&](std::vector<Step>& dst, int kind, std::vector<int4>&& t) {
         if (t.empty()) return;
         Step stp;
         stp.kind = kind;
         stp.tasks = std::move(t);
-        stp.lds = lds;
         dst.push_back(std::move(stp));
     };
     auto big_factor_steps = [&](const std::vector<int32_t>& bigs) {

@@ -397,7 +397,7 @@ enum BigKind : int {
 // One step for every task of a list (predicate and eta as for the groups;
 // which selects the solve vectors).
 void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs* I, const BigTask* tasks, int count,
-                size_t lds_bytes, hipStream_t st);
+                hipStream_t st);
 constexpr int kBigAsmCols = 4;   // columns per workgroup of the assembly, one per wave
 int big_row_block();
 int big_gather_rows();   // rows per workgroup of the forward gather

@@ -855,7 +855,7 @@ int big_solve_cols() { return kSolveCols; }
 int big_chunk() { return kChunk; }
 
 void launch_big(int kind, int pred, double eta_force, int which, const InstPtrs* I, const BigTask* tasks, int count,
-                size_t lds_bytes, hipStream_t st) {
+                hipStream_t st) {
     if (count <= 0) return;
     switch (kind) {
         case kBigAssemble:
