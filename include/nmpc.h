@@ -318,7 +318,11 @@ nmpc_status nmpc_set_parameters(nmpc_problem* p, const double* x0, const double*
  * warm start is placed with nmpc_set_iterate, then warm = 1.
  * opts NULL = defaults.  res may be NULL.  Returns NMPC_OK, a positive
  * outcome, or an error (BAD_ORDER before analyze or warm without a previous
- * solve; NO_DEVICE without a GPU). */
+ * solve; NO_DEVICE without a GPU).
+ * The calling thread polls the device until the solve has ended (here, in
+ * nmpc_batch_solve and in nmpc_closed_loop_dev): it keeps a host core busy and
+ * yields it every few microseconds to another thread that can run.  A program
+ * with more solver threads than cores solves its problems as one batch. */
 nmpc_status nmpc_solve(nmpc_problem* p, int32_t warm, const nmpc_options* opts, nmpc_result* res);
 
 /* Copy the last iterate to host arrays (any may be NULL): y[n], lam[m_c]
