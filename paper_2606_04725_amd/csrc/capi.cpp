@@ -422,7 +422,7 @@ nmpc_status nmpc_get_solution(const nmpc_problem* p, double* y, double* lam, dou
                               double* zU, double* u1, double* x1) {
     if (!p) return fail(NMPC_ERR_INVALID_ARG, "get_solution: NULL handle");
     if (!p->impl.have_iterate || !p->impl.dev) return fail(NMPC_ERR_BAD_ORDER, "get_solution: no solution yet");
-    if (!y && !lam && !omega_d && !zL && !zU) {   // first-stage values only: two small copies
+    if (!y && !lam && !omega_d && !zL && !zU) {   // first-stage values only: one small copy
         std::string err;
         nmpc_status rc = nmpc::device_get_first_stage(p->impl, u1, x1, err);
         return rc == NMPC_OK ? rc : fail(rc, err);

@@ -25,6 +25,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <unordered_map>
@@ -65,6 +66,8 @@ struct Step {
 struct Device {
     const Problem* owner = nullptr;
     hipStream_t stream = nullptr;
+    double* stage = nullptr;       // pinned, an iterate or first-stage values on their way to the caller
+    size_t stage_len = 0;
     InstPtrs hI{};                 // host copy of the instance descriptor
     std::vector<Step> fac, fwd, bwd;
     std::vector<int64_t> u_off;    // update blocks' places in the pool
@@ -172,18 +175,27 @@ hipError_t dalloc(std::vector<void*>& allocs, T*& p, size_t count) {
     return e;
 }
 
+// A copy between host and device, complete on return, on a stream of the library:
+// the legacy stream would not wait for a solve's last kernel, and a copy on it
+// fails, and spoils the capture, while another thread's handle captures a graph.
 template <class T>
-hipError_t upload(std::vector<void*>& allocs, T*& p, const std::vector<T>& h) {
+hipError_t copy_now(T* dst, const T* src, size_t n, hipMemcpyKind kind, hipStream_t st) {
+    const hipError_t e = hipMemcpyAsync(dst, src, n * sizeof(T), kind, st);
+    return e != hipSuccess ? e : hipStreamSynchronize(st);
+}
+
+template <class T>
+hipError_t upload(std::vector<void*>& allocs, hipStream_t st, T*& p, const std::vector<T>& h) {
     hipError_t e = dalloc(allocs, p, h.size());
     if (e != hipSuccess) return e;
-    if (!h.empty()) e = hipMemcpy(p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice);
+    if (!h.empty()) e = copy_now(p, h.data(), h.size(), hipMemcpyHostToDevice, st);
     return e;
 }
 
 template <class T>
-hipError_t upload_c(std::vector<void*>& allocs, const T*& p, const std::vector<T>& h) {
+hipError_t upload_c(std::vector<void*>& allocs, hipStream_t st, const T*& p, const std::vector<T>& h) {
     T* q = nullptr;
-    hipError_t e = upload(allocs, q, h);
+    hipError_t e = upload(allocs, st, q, h);
     p = q;
     return e;
 }
@@ -292,7 +304,7 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
                 B->gen.push_back(f);
         }
     }
-    BTRY(upload(B->allocs, B->dI, hI));
+    BTRY(upload(B->allocs, B->stream, B->dI, hI));
     // index spaces
     for (int k = 0; k < kNumSpaces; ++k) {
         std::vector<int32_t> binst, bfirst(ni + 1, 0);
@@ -304,8 +316,8 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
         bfirst[ni] = (int32_t)binst.size();
         Space& sp = B->spaces.sp[k];
         sp.blocks = (int)binst.size();
-        BTRY(upload_c(B->allocs, sp.binst, binst));
-        BTRY(upload_c(B->allocs, sp.bfirst, bfirst));
+        BTRY(upload_c(B->allocs, B->stream, sp.binst, binst));
+        BTRY(upload_c(B->allocs, B->stream, sp.bfirst, bfirst));
     }
     // schedules: step j of the batch holds step j of every instance (the
     // forward lists aligned at the leaves, the backward lists at the roots), one
@@ -441,11 +453,11 @@ nmpc_status batch_build(const std::vector<Device*>& members, hipStream_t stream,
     merge(B->fwd, &Device::fwd);
     merge(B->fwd_rest, &Device::fwd_rest);
     merge(B->bwd, &Device::bwd);
-    BTRY(upload(B->allocs, B->ftasks, fl));
-    BTRY(upload(B->allocs, B->stasks, sl));
-    BTRY(upload(B->allocs, B->tasks, tl));
+    BTRY(upload(B->allocs, B->stream, B->ftasks, fl));
+    BTRY(upload(B->allocs, B->stream, B->stasks, sl));
+    BTRY(upload(B->allocs, B->stream, B->tasks, tl));
     BTRY(linalg_configure(lim));   // the device maximum, so every batch's launches fit
-    BTRY(upload(B->allocs, B->rep.cnt, std::vector<unsigned>(kRepCounters, 0u)));
+    BTRY(upload(B->allocs, B->stream, B->rep.cnt, std::vector<unsigned>(kRepCounters, 0u)));
     BTRY(hipHostMalloc((void**)&B->rep.host, 2 * sizeof(unsigned long long), hipHostMallocCoherent | hipHostMallocMapped));
     B->rep.host[0] = B->rep.host[1] = 0;
     BTRY(hipHostMalloc((void**)&B->hctl, sizeof(Ctl) * ni, hipHostMallocCoherent | hipHostMallocMapped));
@@ -720,6 +732,7 @@ void device_free(Problem& p) {
     if (D.mod) (void)hipModuleUnload(D.mod);
     if (D.ev_in) (void)hipEventDestroy(D.ev_in);
     if (D.ev_out) (void)hipEventDestroy(D.ev_out);
+    if (D.stage) (void)hipHostFree(D.stage);
     if (D.stream) (void)hipStreamDestroy(D.stream);
     delete p.dev;
     p.dev = nullptr;
@@ -813,7 +826,7 @@ nmpc_status device_init(Problem& p, std::string& err) {
         if (!M.pc_minus_identity) {
             double* pc = nullptr;
             DTRY(dalloc(D.allocs, pc, M.pc.size()));
-            DTRY(hipMemcpy(pc, M.pc.data(), M.pc.size() * sizeof(double), hipMemcpyHostToDevice));
+            DTRY(copy_now(pc, M.pc.data(), M.pc.size(), hipMemcpyHostToDevice, D.stream));
             I.gm.pc = pc;
             DTRY(dalloc(D.allocs, D.gm_jac, (size_t)st.nu * st.nx));
         }
@@ -1197,17 +1210,17 @@ nmpc_status device_init(Problem& p, std::string& err) {
     D.fused = fused;
     D.nodes = nodes;
     std::vector<void*>& A = D.allocs;
-    DTRY(upload_c(A, I.jptr, st.jptr));
-    DTRY(upload_c(A, I.jcol, st.jcol));
-    DTRY(upload_c(A, I.jt_ptr, sy.jt_ptr));
-    DTRY(upload_c(A, I.jt_slot, sy.jt_slot));
-    DTRY(upload_c(A, I.jt_row, sy.jt_row));
-    DTRY(upload_c(A, I.lb, st.lb));
-    DTRY(upload_c(A, I.ub, st.ub));
-    DTRY(upload_c(A, I.perm, sy.perm));
-    DTRY(upload_c(A, I.S.rows_ptr, sy.sn_rows_ptr));
-    DTRY(upload_c(A, I.S.rows, sy.sn_rows));
-    DTRY(upload_c(A, I.S.child_ptr, sy.child_ptr));
+    DTRY(upload_c(A, D.stream, I.jptr, st.jptr));
+    DTRY(upload_c(A, D.stream, I.jcol, st.jcol));
+    DTRY(upload_c(A, D.stream, I.jt_ptr, sy.jt_ptr));
+    DTRY(upload_c(A, D.stream, I.jt_slot, sy.jt_slot));
+    DTRY(upload_c(A, D.stream, I.jt_row, sy.jt_row));
+    DTRY(upload_c(A, D.stream, I.lb, st.lb));
+    DTRY(upload_c(A, D.stream, I.ub, st.ub));
+    DTRY(upload_c(A, D.stream, I.perm, sy.perm));
+    DTRY(upload_c(A, D.stream, I.S.rows_ptr, sy.sn_rows_ptr));
+    DTRY(upload_c(A, D.stream, I.S.rows, sy.sn_rows));
+    DTRY(upload_c(A, D.stream, I.S.child_ptr, sy.child_ptr));
     {
         std::vector<ChildRec> rec(sy.child_list.size());
         for (size_t k = 0; k < rec.size(); ++k) {
@@ -1216,23 +1229,23 @@ nmpc_status device_init(Problem& p, std::string& err) {
             rec[k] = ChildRec{u_off[c], sy.rel_off[c], sy.uv_off[c],
                               (int32_t)(sy.sn_rows_ptr[c + 1] - sy.sn_rows_ptr[c]) - wc, c};
         }
-        DTRY(upload_c(A, I.S.child_rec, rec));
+        DTRY(upload_c(A, D.stream, I.S.child_rec, rec));
         D.child_rec = std::move(rec);
     }
-    DTRY(upload_c(A, I.S.uv_off, sy.uv_off));
-    DTRY(upload_c(A, I.S.rel, sy.rel));
-    DTRY(upload_c(A, I.S.k_fpos, k_fpos));
-    DTRY(upload_c(A, I.kcol_ptr, sy.kcol_ptr));
-    DTRY(upload_c(A, I.S.big_col, big_col));
-    DTRY(upload_c(A, I.S.big_ptr, big_ptr));
-    DTRY(upload_c(A, I.S.big_ent, big_ent));
-    DTRY(upload_c(A, I.S.chunk_pos, chunk_pos));
-    DTRY(upload_c(A, I.k_wslot, sy.k_wslot));
-    DTRY(upload_c(A, I.k_diag, sy.k_diag));
-    DTRY(upload_c(A, I.kc_ptr, sy.kc_ptr));
-    DTRY(upload_c(A, I.kc_a, sy.kc_a));
-    DTRY(upload_c(A, I.kc_b, sy.kc_b));
-    DTRY(upload_c(A, I.kc_r, sy.kc_r));
+    DTRY(upload_c(A, D.stream, I.S.uv_off, sy.uv_off));
+    DTRY(upload_c(A, D.stream, I.S.rel, sy.rel));
+    DTRY(upload_c(A, D.stream, I.S.k_fpos, k_fpos));
+    DTRY(upload_c(A, D.stream, I.kcol_ptr, sy.kcol_ptr));
+    DTRY(upload_c(A, D.stream, I.S.big_col, big_col));
+    DTRY(upload_c(A, D.stream, I.S.big_ptr, big_ptr));
+    DTRY(upload_c(A, D.stream, I.S.big_ent, big_ent));
+    DTRY(upload_c(A, D.stream, I.S.chunk_pos, chunk_pos));
+    DTRY(upload_c(A, D.stream, I.k_wslot, sy.k_wslot));
+    DTRY(upload_c(A, D.stream, I.k_diag, sy.k_diag));
+    DTRY(upload_c(A, D.stream, I.kc_ptr, sy.kc_ptr));
+    DTRY(upload_c(A, D.stream, I.kc_a, sy.kc_a));
+    DTRY(upload_c(A, D.stream, I.kc_b, sy.kc_b));
+    DTRY(upload_c(A, D.stream, I.kc_r, sy.kc_r));
     double *x0 = nullptr, *zF = nullptr, *up = nullptr, *setp = nullptr;
     DTRY(dalloc(A, x0, st.nx));
     DTRY(dalloc(A, zF, st.H));
@@ -1284,15 +1297,17 @@ nmpc_status device_init(Problem& p, std::string& err) {
                 wf_col[fill[c]++] = r;
             }
         }
-        DTRY(upload_c(A, I.wf_ptr, wf_ptr));
-        DTRY(upload_c(A, I.wf_slot, wf_slot));
-        DTRY(upload_c(A, I.wf_col, wf_col));
+        DTRY(upload_c(A, D.stream, I.wf_ptr, wf_ptr));
+        DTRY(upload_c(A, D.stream, I.wf_slot, wf_slot));
+        DTRY(upload_c(A, D.stream, I.wf_col, wf_col));
     }
     int pblocks = 0;
     for (int k = 0; k < kNumSpaces; ++k) pblocks = std::max(pblocks, nblocks(space_size(I, k)));
     DTRY(dalloc(A, I.part, (size_t)kMaxQ * std::max(1, pblocks)));
     DTRY(dalloc(A, I.filter, (size_t)2 * kFilterCapMax));
     DTRY(dalloc(A, I.dfac, (size_t)kBigDiag * max_bigs));
+    D.stage_len = std::min<size_t>(3 * ((size_t)I.n + I.ml), 65536);
+    DTRY(hipHostMalloc((void**)&D.stage, D.stage_len * sizeof(double), hipHostMallocDefault));
 #undef DTRY
     std::vector<Device*> one{&D};
     nmpc_status rc = batch_build(one, D.stream, D.self, err);
@@ -1438,6 +1453,7 @@ nmpc_status batch_solve(Batch& B, int warm, const nmpc_options& o, nmpc_result* 
     }
     // an instance that ended in the last evaluation opened one more iteration
     if (report_ended(word)) ++passes;
+    if (B.own_stream) HIP_TRY(hipStreamSynchronize(st));   // the instances' own streams follow
     B.reports.open = false;
     int worst = NMPC_OK;
     for (int i = 0; i < ni; ++i) {
@@ -1659,22 +1675,75 @@ hipError_t factor_once(Batch& B, double eta, int& failed) {
 
 }  // namespace
 
+namespace {
+struct Out {
+    double* dst;
+    const double* src;
+    size_t n;
+};
+constexpr int kOuts = 6;
+struct OutList {
+    const double* src[kOuts];
+    int end[kOuts];   // of its values in the pinned memory
+};
+// The arrays of a list, one after another, into pinned memory.
+__global__ void __launch_bounds__(kBlock) k_export(OutList o, double* __restrict__ dst) {
+    const int t = blockIdx.x * kBlock + threadIdx.x;
+    int from = 0;
+#pragma unroll
+    for (int k = 0; k < kOuts; ++k) {
+        if (t >= from && t < o.end[k]) dst[t] = o.src[k][t - from];
+        from = o.end[k];
+    }
+}
+
+// Device arrays (at most kOuts) to the caller's memory, on the handle's stream.
+// Where they fit, a kernel puts them into the handle's pinned memory: a copy per
+// array on this stream waits for the solve's last kernel from another engine
+// (iterate of the 21 x 21 x 12 plate after a solve: 98 us, now 38; 76 with copies
+// on the legacy stream).  Larger ones are copied once the stream is idle.
+hipError_t copy_out(Device& D, std::initializer_list<Out> list) {
+    size_t total = 0;
+    for (const Out& o : list) total += o.n;
+    const bool staged = total <= D.stage_len;
+    hipError_t e = hipSuccess;
+    if (staged) {
+        OutList l{};
+        int k = 0, at = 0;
+        for (const Out& o : list) {
+            l.src[k] = o.src;
+            l.end[k++] = at += (int)o.n;
+        }
+        for (; k < kOuts; ++k) l.end[k] = at;
+        if (at > 0) hipLaunchKernelGGL(k_export, dim3((at + kBlock - 1) / kBlock), dim3(kBlock), 0, D.stream, l, D.stage);
+        e = hipGetLastError();
+    } else {
+        e = hipStreamSynchronize(D.stream);
+        for (const Out& o : list)
+            if (e == hipSuccess) e = hipMemcpyAsync(o.dst, o.src, o.n * sizeof(double), hipMemcpyDeviceToHost, D.stream);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(D.stream);
+    if (e != hipSuccess || !staged) return e;
+    const double* from = D.stage;
+    for (const Out& o : list) {
+        if (o.n > 0) std::memcpy(o.dst, from, o.n * sizeof(double));
+        from += o.n;
+    }
+    return hipSuccess;
+}
+}  // namespace
+
 nmpc_status device_get_iterate(const Problem& p, double* y, double* s, double* om, double* be, double* zl,
                                double* zu, std::string& err) {
     const InstPtrs& I = p.dev->hI;
-    HIP_TRY(hipMemcpy(y, I.y, I.n * sizeof(double), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(s, I.s, I.ml * sizeof(double), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(om, I.om, I.ml * sizeof(double), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(be, I.be, I.ml * sizeof(double), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(zl, I.zl, I.n * sizeof(double), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(zu, I.zu, I.n * sizeof(double), hipMemcpyDeviceToHost));
+    const size_t n = I.n, ml = I.ml;
+    HIP_TRY(copy_out(*p.dev, {{y, I.y, n}, {s, I.s, ml}, {om, I.om, ml}, {be, I.be, ml}, {zl, I.zl, n}, {zu, I.zu, n}}));
     return NMPC_OK;
 }
 
 nmpc_status device_get_first_stage(const Problem& p, double* u1, double* x1, std::string& err) {
-    const InstPtrs& I = p.dev->hI;
-    if (u1) HIP_TRY(hipMemcpy(u1, I.y + I.nx, I.nu * sizeof(double), hipMemcpyDeviceToHost));
-    if (x1) HIP_TRY(hipMemcpy(x1, I.y, I.nx * sizeof(double), hipMemcpyDeviceToHost));
+    const InstPtrs& I = p.dev->hI;   // y begins with the first stage's states, then its controls
+    HIP_TRY(copy_out(*p.dev, {{x1, I.y, x1 ? (size_t)I.nx : 0}, {u1, I.y + I.nx, u1 ? (size_t)I.nu : 0}}));
     return NMPC_OK;
 }
 
@@ -1682,13 +1751,15 @@ nmpc_status device_set_iterate(Problem& p, const double* y, const double* s, con
                                const double* zl, const double* zu, std::string& err) {
     Device& D = *p.dev;
     const InstPtrs& I = D.hI;
+    const hipStream_t st = D.stream;
     D.adj_ready = false;
-    HIP_TRY(hipMemcpy(I.y, y, I.n * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(I.s, s, I.ml * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(I.om, om, I.ml * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(I.be, be, I.ml * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(I.zl, zl, I.n * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(I.zu, zu, I.n * sizeof(double), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpyAsync(I.y, y, I.n * sizeof(double), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(I.s, s, I.ml * sizeof(double), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(I.om, om, I.ml * sizeof(double), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(I.be, be, I.ml * sizeof(double), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(I.zl, zl, I.n * sizeof(double), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(I.zu, zu, I.n * sizeof(double), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));
     return NMPC_OK;
 }
 
@@ -1742,7 +1813,7 @@ nmpc_status device_factor(Problem& p, const double* kv, double eta, int32_t* ok,
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipStreamSynchronize(B.stream));
     }
-    if (lv) HIP_TRY(hipMemcpy(lv, D.hI.L, D.stored_l * sizeof(double), hipMemcpyDeviceToHost));
+    if (lv) HIP_TRY(copy_now(lv, D.hI.L, D.stored_l, hipMemcpyDeviceToHost, B.stream));
     return NMPC_OK;
 }
 
@@ -2265,7 +2336,7 @@ nmpc_status device_autotune(Problem& p, int reps, int* changed, std::string& err
         }
         for (int64_t t = 0; t < nk; ++t)
             if (sy.k_diag[t] >= 0) kv[t] = 1.0 + rowsum[sy.k_diag[t]];
-        HIP_TRY(hipMemcpy(D.hI.kv, kv.data(), nk * sizeof(double), hipMemcpyHostToDevice));
+        HIP_TRY(copy_now(D.hI.kv, kv.data(), nk, hipMemcpyHostToDevice, B.stream));
         const size_t nl = B.fac.size();
         std::vector<hipEvent_t> ev(nl + 1);
         for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
